@@ -4,13 +4,17 @@
 // w_e d_pooled[t_e, p_e].
 //
 // The T * bag entries are keyed by physical row and stably sorted (sort.hip), so the entries of
-// one row form a run in their original order.  Runs are cut into pieces of at most 64 entries;
-// a wave takes a piece, reads V[row] 16 bytes per lane at a time, and for each entry of the
-// piece in order computes its weight gradient (a wave reduction per core) and adds w_e d_pooled
-// into an fp32 accumulator, which it adds into dV[row] (a whole run) or stores as a partial row
-// that a second pass adds in order.  Every row has one writer and a fixed summation order: the
-// result does not depend on timing, and no atomics are needed.  The compact form writes one
-// gradient row per run (distinct row) from zero instead of adding into a dense table.
+// one row form a run in their original order.  Most rows of a large table are chosen once, some
+// by thousands of tokens, and the two are separate work:
+//  * token_bwd_kernel walks the entries token by token with the token's d_pooled row in
+//    registers: it reads every entry's value row once for the weight gradient, and writes the
+//    gradient row of an entry that is alone on its row there and then (w_e d_pooled);
+//  * row_bwd_kernel sums the rows with several entries: their runs are cut into pieces of at most
+//    64 entries, and a piece adds its entries' w_e d_pooled in order into its row, or, where it
+//    continues a run, stores a partial row that seg_join_kernel adds in order.
+// Every row has one writer and a fixed summation order: the result does not depend on timing, and
+// no float atomics are needed.  The compact form writes one gradient row per run (distinct row)
+// from zero instead of adding into a dense table.
 //
 // Backward of the scores (eqs. (2)-(4), (10), (16)) with the selection held fixed: one wave
 // per (token, head) turns the weight gradients into grid-score gradients (SoftMax Jacobian where
@@ -35,16 +39,31 @@ constexpr int NWAVES = THREADS / kWave;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(THREADS) void bwd_keys_kernel(const int32_t* __restrict__ idx,
-                                                           const int32_t* __restrict__ perm,
-                                                           int64_t n_values, int M,
-                                                           uint32_t* __restrict__ keys,
-                                                           uint32_t* __restrict__ vals) {
-  for (int e = blockIdx.x * THREADS + threadIdx.x; e < M; e += gridDim.x * THREADS) {
+// Each entry's physical row as the sort's key, its d_pooled row into prow[e], and the tile's
+// histogram of its first digit (the sort's first counting pass, for which the keys need not be
+// read again).
+__global__ __launch_bounds__(kSortThreads) void bwd_keys_kernel(const int32_t* __restrict__ idx,
+                                                                const int32_t* __restrict__ perm,
+                                                                uint32_t n_values, int bag, int expand,
+                                                                uint32_t* __restrict__ prow, SortPlan sp) {
+  __shared__ uint32_t cnt[1 << kSortMaxDigitBits];
+  const int nd = 1 << sp.dbits;
+  const uint32_t mask = static_cast<uint32_t>(nd - 1);
+  for (int d = threadIdx.x; d < nd; d += kSortThreads) cnt[d] = 0;
+  __syncthreads();
+  const int base = blockIdx.x * sp.tile, end = min(base + sp.tile, sp.M);
+  for (int e = base + static_cast<int>(threadIdx.x); e < end; e += kSortThreads) {
     const int32_t x = idx[e];
-    keys[e] = perm != nullptr ? static_cast<uint32_t>(perm[x] % n_values) : static_cast<uint32_t>(x);
-    vals[e] = static_cast<uint32_t>(e);
+    const uint32_t v = perm != nullptr ? static_cast<uint32_t>(perm[x]) : static_cast<uint32_t>(x);
+    const uint32_t p = perm != nullptr ? v / n_values : 0u;
+    const uint32_t row = v - p * n_values;
+    sp.keys[e] = row;
+    prow[e] = static_cast<uint32_t>(e / bag) * expand + p;
+    atomicAdd(&cnt[row & mask], 1u);
   }
+  __syncthreads();
+  for (int d = threadIdx.x; d < nd; d += kSortThreads)
+    sp.hist[static_cast<size_t>(d) * sp.tiles + blockIdx.x] = cnt[d];
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -58,16 +77,17 @@ struct Chunk;
 template <>
 struct Chunk<float> {
   static constexpr int kElems = 4;
-  __device__ static inline void load(const float* p, float* x) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(p);
-    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+  __device__ static inline void widen(const u32x4& r, float* x) {
+    x[0] = __uint_as_float(r.x);
+    x[1] = __uint_as_float(r.y);
+    x[2] = __uint_as_float(r.z);
+    x[3] = __uint_as_float(r.w);
   }
 };
 template <>
 struct Chunk<uint16_t> {   // bf16 bit patterns
   static constexpr int kElems = 8;
-  __device__ static inline void load(const uint16_t* p, float* x) {
-    const u32x4 r = *reinterpret_cast<const u32x4*>(p);
+  __device__ static inline void widen(const u32x4& r, float* x) {
     const uint32_t q[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -77,329 +97,603 @@ struct Chunk<uint16_t> {   // bf16 bit patterns
   }
 };
 
-// The run [i, end) of sorted entries that starts at sorted position i (wave-uniform).
-__device__ __forceinline__ int run_end(const uint32_t* __restrict__ keys, int i, int M, uint32_t key) {
-  const int lane = threadIdx.x & (kWave - 1);
-  for (int base = i + 1; base < M; base += kWave) {
-    const int pos = base + lane;
-    const uint64_t same = __ballot(pos < M && keys[pos] == key);
-    if (same != ~0ull) return base + __builtin_ctzll(~same);
-  }
-  return M;
-}
+// ---------------------------------------------------------------- runs and pieces
 
-// The sorted entries are cut into pieces at the starts of runs and at every kSeg-th position, and
+// A run: the sorted entries of one key.  Runs are cut into pieces at every kSeg-th position, and
 // each piece is one wave's work, so that a row chosen by thousands of tokens does not leave one
-// wave walking them all while a row chosen once still gets a wave of its own.  The piece starts
-// are listed first (counted per chunk, the counts scanned, then written in order), and a fixed
-// grid of waves walks the list.  A piece that is a
-// whole run adds its sum into its row; a piece cut by a segment edge (segment g = positions
-// [g kSeg, (g + 1) kSeg)) stores its partial row: slot 2 g + 1 for the last piece of segment g
-// when it starts its run, slot 2 g for the first piece of segment g when it continues one.  A
-// second pass adds, for each run spanning segments, its head piece and then the first piece of
-// each later segment, in that order.
+// wave walking them all.  The piece starts are listed in order (counted per chunk, then written
+// from the sum of the earlier chunks' counts), and a fixed grid of waves walks the list.  A piece
+// that starts its run adds its sum into its row; one that continues it (the first piece of
+// segment g = positions [g kSeg, (g + 1) kSeg)) stores its partial row in slot g, and
+// seg_join_kernel adds, for each run spanning segments, the partial rows of its later segments, in
+// order.
 constexpr int kSeg = kWave;
 
-// The piece starting at sorted position i, if one does ([i, *pe), with whether it starts and
-// ends its run); false for positions inside a piece.  Wave-uniform.
-__device__ __forceinline__ bool piece_at(const uint32_t* __restrict__ keys, int i, int M,
-                                         uint32_t key, int* pe, bool* run_start, bool* run_end) {
-  const int lane = threadIdx.x & (kWave - 1);
-  *run_start = i == 0 || keys[i - 1] != key;
-  if (!*run_start && i % kSeg != 0) return false;
-  const int seg_end = min(M, (i / kSeg + 1) * kSeg);
-  const int pos = i + 1 + lane;
-  const uint64_t diff = __ballot(pos < seg_end && keys[pos] != key);
-  *pe = diff != 0ull ? i + 1 + __builtin_ctzll(diff) : seg_end;
-  *run_end = *pe == M || keys[*pe] != key;
-  return true;
+// Where sorted position i (< n) stands in its run.
+struct Place {
+  uint32_t key;
+  bool starts, alone;      // first of its run; the only entry of its run
+};
+__device__ __forceinline__ Place place_at(const uint2* __restrict__ sorted, int i, int n) {
+  Place p;
+  p.key = sorted[i].x;
+  p.starts = i == 0 || sorted[i - 1].x != p.key;
+  p.alone = p.starts && (i + 1 == n || sorted[i + 1].x != p.key);
+  return p;
 }
+
+// The end of the piece that starts at sorted position i of key `key`, and whether its run ends
+// there.  Wave-uniform.
+__device__ __forceinline__ int piece_end(const uint2* __restrict__ sorted, int i, int n, uint32_t key,
+                                         bool* ends_run) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int seg_end = min(n, (i / kSeg + 1) * kSeg);
+  const int pos = i + 1 + lane;
+  const uint64_t diff = __ballot(pos < seg_end && sorted[pos].x != key);
+  const int pe = diff != 0ull ? i + 1 + __builtin_ctzll(diff) : seg_end;
+  *ends_run = pe == n || sorted[pe].x != key;
+  return pe;
+}
+
+// The end of the run that holds sorted position i (wave-uniform).
+__device__ __forceinline__ int run_end(const uint2* __restrict__ sorted, int i, int n, uint32_t key) {
+  const int lane = threadIdx.x & (kWave - 1);
+  for (int base = i + 1; base < n; base += kWave) {
+    const int pos = base + lane;
+    const uint64_t same = __ballot(pos < n && sorted[pos].x == key);
+    if (same != ~0ull) return base + __builtin_ctzll(~same);
+  }
+  return n;
+}
+
+constexpr int kListSteps = 4;                           // positions per thread, THREADS apart
+constexpr int kListChunk = THREADS * kListSteps;        // positions per workgroup
+
+// ROWS (value rows): only runs of several entries are cut into pieces, the entries alone on their
+// row being the token kernel's; otherwise (keys) every run is.
+template <bool ROWS>
+__device__ __forceinline__ bool starts_piece(const Place& p, int i) {
+  return (!ROWS || !p.alone) && (p.starts || i % kSeg == 0);
+}
+
+// Per chunk of kListChunk positions: the pieces (x) and runs (y) that start in it.
+template <bool ROWS>
+__global__ __launch_bounds__(THREADS) void piece_count_kernel(const uint2* __restrict__ sorted,
+                                                              const uint32_t* __restrict__ n_sorted,
+                                                              uint2* __restrict__ cnt) {
+  __shared__ uint32_t wp[NWAVES], wr[NWAVES];
+  const int n = static_cast<int>(*n_sorted);
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  uint32_t c = 0, cr = 0;
+#pragma unroll
+  for (int q = 0; q < kListSteps; ++q) {
+    const int i = blockIdx.x * kListChunk + q * THREADS + threadIdx.x;
+    bool piece = false, run = false;
+    if (i < n) {
+      const Place p = place_at(sorted, i, n);
+      piece = starts_piece<ROWS>(p, i);
+      run = p.starts;
+    }
+    c += __popcll(__ballot(piece));
+    cr += __popcll(__ballot(run));
+  }
+  if (lane == 0) {
+    wp[wave] = c;
+    wr[wave] = cr;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    c = cr = 0;
+#pragma unroll
+    for (int v = 0; v < NWAVES; ++v) {
+      c += wp[v];
+      cr += wr[v];
+    }
+    cnt[blockIdx.x] = make_uint2(c, cr);
+  }
+}
+
+// What the ROWS form of piece_write_kernel leaves for the two gradient kernels.
+constexpr uint32_t kAlone = 0x80000000u;
+struct RowInfo {
+  uint32_t* entry;          // [M] by entry: its d_pooled row (below 2^31), replaced by its run's
+                            // number with kAlone where it is the run, without at a piece's start
+  uint2* rec;               // [M] by sorted position, runs of several entries: the d_pooled row and
+                            // the weight's bits (one core) or the entry (several)
+  const float* w;           // the weights with one core, else NULL
+  int32_t* rows_out;        // each run's row (compact form, else NULL)
+  int32_t* n_runs;          // their number (compact form, else NULL)
+};
+
+// cnt: the counts of piece_count_kernel.  Writes the pieces' first sorted positions in order into
+// list, their number into counts[0], and clears counts[1] (the spanning runs, appended later).
+template <bool ROWS>
+__global__ __launch_bounds__(THREADS) void piece_write_kernel(
+    const uint2* __restrict__ sorted, const uint32_t* __restrict__ n_sorted,
+    const uint2* __restrict__ cnt, uint32_t* __restrict__ list, uint32_t* __restrict__ counts,
+    RowInfo info) {
+  __shared__ uint2 wsum[NWAVES];
+  __shared__ uint2 wcnt[kListSteps][NWAVES];
+  const int n = static_cast<int>(*n_sorted);
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  uint32_t bp = 0, br = 0;
+  for (int j = threadIdx.x; j < static_cast<int>(blockIdx.x); j += THREADS) {
+    const uint2 c = cnt[j];
+    bp += c.x;
+    br += c.y;
+  }
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    bp += __shfl_xor(bp, off, kWave);
+    br += __shfl_xor(br, off, kWave);
+  }
+  if (lane == 0) wsum[wave] = make_uint2(bp, br);
+  Place pl[kListSteps];
+  bool piece[kListSteps];
+  uint64_t mp[kListSteps], mr[kListSteps];
+#pragma unroll
+  for (int q = 0; q < kListSteps; ++q) {
+    const int i = blockIdx.x * kListChunk + q * THREADS + threadIdx.x;
+    piece[q] = false;
+    pl[q] = Place{0u, false, false};
+    if (i < n) {
+      pl[q] = place_at(sorted, i, n);
+      piece[q] = starts_piece<ROWS>(pl[q], i);
+    }
+    mp[q] = __ballot(piece[q]);
+    mr[q] = __ballot(pl[q].starts);
+    if (lane == 0) wcnt[q][wave] = make_uint2(__popcll(mp[q]), __popcll(mr[q]));
+  }
+  __syncthreads();
+  bp = br = 0;
+#pragma unroll
+  for (int v = 0; v < NWAVES; ++v) {
+    bp += wsum[v].x;
+    br += wsum[v].y;
+  }
+  const uint64_t lt = lanemask_lt();
+#pragma unroll
+  for (int q = 0; q < kListSteps; ++q) {
+    uint32_t ap = bp, ar = br;                            // before this wave's positions
+#pragma unroll
+    for (int v = 0; v < NWAVES; ++v) {
+      const uint2 c = wcnt[q][v];
+      ap += v < wave ? c.x : 0u;
+      ar += v < wave ? c.y : 0u;
+      bp += c.x;
+      br += c.y;
+    }
+    const int i = blockIdx.x * kListChunk + q * THREADS + threadIdx.x;
+    if (i >= n) continue;
+    const uint32_t run = ar + __popcll(mr[q] & lt) + (pl[q].starts ? 0u : ~0u);   // starts, less one
+    if (piece[q]) list[ap + __popcll(mp[q] & lt)] = static_cast<uint32_t>(i);
+    if (ROWS) {
+      const int ent = static_cast<int>(sorted[i].y);
+      if (!pl[q].alone)
+        info.rec[i] = make_uint2(info.entry[ent], info.w != nullptr ? __float_as_uint(info.w[ent]) : static_cast<uint32_t>(ent));
+      if (pl[q].alone || piece[q]) info.entry[ent] = run | (pl[q].alone ? kAlone : 0u);
+      if (info.rows_out != nullptr && pl[q].starts) info.rows_out[run] = static_cast<int32_t>(pl[q].key);
+    }
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    counts[0] = bp;
+    counts[1] = 0u;
+    if (ROWS && info.n_runs != nullptr) *info.n_runs = static_cast<int32_t>(br);
+  }
+}
+
+int list_chunks(int M) { return (M + kListChunk - 1) / kListChunk; }
+
+// ---------------------------------------------------------------- value rows, token by token
+
+constexpr int kTokenWaves = 8192;       // waves the launch aims at (eight per SIMD)
+
+// Sum over the aligned group of L lanes that a lane belongs to, valid in its last lane: DPP row
+// shifts within 16 lanes, then the row broadcasts (L > 16).
+template <int L>
+__device__ __forceinline__ float group_total(float x) {
+  int r = __builtin_bit_cast(int, x);
+#define UMEM_ADD(CTRL, ROWS)                                                                   \
+  r = __builtin_bit_cast(int, __builtin_bit_cast(float, r) +                                    \
+                         __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, r, CTRL, ROWS, 0xF, true)))
+  if (L >= 2) UMEM_ADD(0x111, 0xF);      // row_shr:1
+  if (L >= 4) UMEM_ADD(0x112, 0xF);      // row_shr:2
+  if (L >= 8) UMEM_ADD(0x114, 0xF);      // row_shr:4
+  if (L >= 16) UMEM_ADD(0x118, 0xF);     // row_shr:8
+  if (L >= 32) UMEM_ADD(0x142, 0xA);     // row_bcast:15 into rows 1 and 3
+  if (L >= 64) UMEM_ADD(0x143, 0xC);     // row_bcast:31 into rows 2 and 3
+#undef UMEM_ADD
+  return __builtin_bit_cast(float, r);
+}
+
+// One workgroup per token (gridDim.y of them share a bag); entries ordered by virtual block, CW
+// waves taking one entry's columns together (64 lanes x CPL chunks of 16 bytes each), the
+// workgroup's NWAVES / CW groups of waves contiguous ranges of its share of the bag.  For rows of
+// 1 KiB and more a wave keeps its columns of the block's d_pooled row in registers and reloads them
+// where the block changes; narrower rows are read L lanes each, 64 / L entries at once, with their
+// d_pooled rows from cache.  Entry j of a group's current 64 leaves its partial weight gradients in
+// LDS ([group][wave][core][j]), which are added in wave order behind a barrier per 64 entries.
+// SLICED: the wave that takes a block's first entry also leaves its d_pooled columns in `sliced`, by
+// column slice (row_bwd_kernel).  Wide rows are split between waves (CW = 4 at 4096 bf16 columns) because the d_pooled row of a
+// whole one takes 64 registers beside the value row: three waves per SIMD, one row in flight each.
+// Bound by HBM: each value row is read once and each lone entry's gradient row written once.  At
+// 2,048 tokens of 64 rows of 2 KiB (121,600 distinct) it moves 764 MB in 158 us, 4.8 TB/s, the rate
+// of a large device copy; at 512 tokens of 84 rows of 8 KiB 1.06 GB in 224 us.  A wave per row read
+// d_pooled again for each of them, from the MALL: 268 and 332 us.  Nontemporal stores of the
+// gradient rows took 274 us at 8 KiB rows (the same at 2 KiB), nontemporal row loads 192 at 2 KiB;
+// eight or two loads in flight a lane instead of four 163 and 161 us.
+template <typename Elem, int L, int CPL, int CW, bool SLICED, bool DENSE>
+__global__ __launch_bounds__(THREADS) void token_bwd_kernel(
+    const Elem* __restrict__ values, int dv, int bag, const int32_t* __restrict__ idx,
+    const float* __restrict__ w, const int32_t* __restrict__ perm, uint32_t n_values, int expand,
+    int cores, const float* __restrict__ d_pooled, const uint32_t* __restrict__ info,
+    float* __restrict__ d_rows, float* __restrict__ dw, float* __restrict__ sliced,
+    int slice_cols) {
+  using TR = Chunk<Elem>;
+  constexpr int EPC = TR::kElems;
+  constexpr int SUB = kWave / L;                   // entries a wave reads at once
+    constexpr int U = CPL >= 4 ? 1 : 4 / CPL;        // batches of them in flight
+  constexpr int NG = NWAVES / CW;                  // groups of waves
+  static_assert(L == kWave || (CW == 1 && CPL == 1 && !SLICED), "several entries at once only in narrow rows");
+  extern __shared__ __align__(16) int32_t lds[];   // [NWAVES][cores][64] sums, then [3][bag]
+  float* const sums = reinterpret_cast<float*>(lds);
+  const int t = blockIdx.x;
+  const int32_t* __restrict__ idx_t = idx + static_cast<size_t>(t) * bag;
+  const float* __restrict__ w_t = w + static_cast<size_t>(t) * bag * cores;
+  const uint32_t* __restrict__ info_t = info + static_cast<size_t>(t) * bag;
+  float* __restrict__ dw_t = dw + static_cast<size_t>(t) * bag * cores;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  int32_t *rows = lds + NWAVES * cores * kWave, *blk = rows + bag, *order = blk + bag;
+  if (expand > 1) {
+    __shared__ int bcount[kMaxExpand];
+    for (int p = tid; p < expand; p += THREADS) bcount[p] = 0;
+    __syncthreads();
+    for (int s = tid; s < bag; s += THREADS) {
+      const uint32_t v = static_cast<uint32_t>(perm[idx_t[s]]);
+      const uint32_t p = v / n_values;
+      rows[s] = static_cast<int32_t>(v - p * n_values);
+      blk[s] = static_cast<int32_t>(p);
+      atomicAdd(&bcount[p], 1);
+    }
+    __syncthreads();
+    // entries by block, stably (the workgroups that share a bag must agree on the order): wave 0
+    // places 64 at a time, each after its block's earlier ones
+    if (wave == 0) {
+      const int c = lane < expand ? bcount[lane] : 0;
+      const int incl = wave_inclusive_scan(c);
+      wave_lds_order();
+      if (lane < expand) bcount[lane] = incl - c;
+      wave_lds_order();
+      const uint64_t lt = lanemask_lt();
+      for (int s0 = 0; s0 < bag; s0 += kWave) {
+        const int s = s0 + lane;
+        const int p = s < bag ? blk[s] : 0;
+        uint64_t peers = __ballot(s < bag);
+        for (int b = 0; (1 << b) < expand; ++b) {
+          const bool one = (p >> b) & 1;
+          const uint64_t ones = __ballot(one);
+          peers &= one ? ones : ~ones;
+        }
+        const int at = bcount[p];
+        const int rank = __popcll(peers & lt);
+        if (s < bag) order[at + rank] = s;
+        wave_lds_order();
+        if (s < bag && rank == 0) bcount[p] = at + __popcll(peers);
+        wave_lds_order();
+      }
+    }
+  } else {                                         // the bag as it is
+    for (int s = tid; s < bag; s += THREADS) {
+      rows[s] = idx_t[s];
+      blk[s] = 0;
+      order[s] = s;
+    }
+  }
+  __syncthreads();
+  const int parts = NG * gridDim.y, group = wave / CW;
+  const int per = (bag + parts - 1) / parts;
+  const int part = blockIdx.y * NG + group;
+  const int beg = min(bag, part * per), end = min(bag, beg + per);
+  const int sub = lane / L, cl = lane % L;
+  const int chunk0 = (wave % CW) * CPL * kWave + cl;    // the lane's first 16-byte chunk of the row
+  const int per_core = dv / cores;
+  int slice[CPL];                                  // this lane's chunks' core (0 with one core)
+#pragma unroll
+  for (int c = 0; c < CPL; ++c) slice[c] = cores > 1 ? ((chunk0 + L * c) * EPC) / per_core : 0;
+  // the cores this wave's columns belong to
+  const int core_lo = L == kWave ? __builtin_amdgcn_readfirstlane(slice[0]) : 0;
+  const int core_hi = L == kWave ? __builtin_amdgcn_readlane(slice[CPL - 1], kWave - 1) : cores - 1;
+  float dp[CPL][EPC];                              // L == 64: the current block's d_pooled columns
+  int held = -1;
+  for (int r0 = 0; r0 < per; r0 += kWave) {        // rounds of up to 64 entries a group
+    for (int k = 0; k < cores; ++k) sums[(wave * cores + k) * kWave + lane] = 0.0f;
+    wave_lds_order();
+    const int rbeg = beg + r0, rend = min(end, rbeg + kWave);
+    for (int j0 = rbeg; j0 < rend; j0 += SUB * U) {
+      u32x4 raw[U][CPL];
+      int ent[U], row[U], blk_of[U];
+      uint32_t inf[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = j0 + SUB * u + sub;
+        ent[u] = -1;
+        row[u] = blk_of[u] = 0;
+        inf[u] = 0u;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) raw[u][c] = u32x4{0u, 0u, 0u, 0u};
+        if (j < rend) {
+          int s = order[j];
+          if (L == kWave) s = __builtin_amdgcn_readfirstlane(s);    // one entry for the wave
+          int r = rows[s];
+          int p = blk[s];
+          if (L == kWave) {
+            r = __builtin_amdgcn_readfirstlane(r);
+            p = __builtin_amdgcn_readfirstlane(p);
+          }
+          ent[u] = s;
+          row[u] = r;
+          blk_of[u] = p;
+          inf[u] = info_t[s];
+          const Elem* src = values + static_cast<size_t>(r) * dv;
+#pragma unroll
+          for (int c = 0; c < CPL; ++c)
+            raw[u][c] = *reinterpret_cast<const u32x4*>(src + (chunk0 + L * c) * EPC);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (L == kWave && j0 + u >= rend) break;   // (wave-uniform)
+        const bool on = ent[u] >= 0;
+        const int p = blk_of[u];
+        if (L != kWave || p != held) {
+          const float* src = d_pooled + (static_cast<size_t>(t) * expand + p) * dv;
+#pragma unroll
+          for (int c = 0; c < CPL; ++c)
+#pragma unroll
+            for (int e = 0; e < EPC; e += 4) {
+              const f32x4 v = *reinterpret_cast<const f32x4*>(src + (chunk0 + L * c) * EPC + e);
+              dp[c][e] = v.x;
+              dp[c][e + 1] = v.y;
+              dp[c][e + 2] = v.z;
+              dp[c][e + 3] = v.w;
+              if (SLICED && (j0 + u == 0 || blk[order[max(j0 + u - 1, 0)]] != p)) {
+                const int col = (chunk0 + L * c) * EPC + e;       // slices are whole 16-byte pieces
+                const size_t at = (static_cast<size_t>(col / slice_cols) * gridDim.x + t) * expand + p;
+                *reinterpret_cast<f32x4*>(sliced + at * slice_cols + col % slice_cols) = v;
+              }
+            }
+          held = p;
+        }
+        float dot[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+          float x[EPC];
+          TR::widen(raw[u][c], x);
+          dot[c] = 0.0f;
+#pragma unroll
+          for (int e = 0; e < EPC; ++e) dot[c] = fmaf(dp[c][e], x[e], dot[c]);
+        }
+        for (int k = core_lo; k <= core_hi; ++k) {
+          float v = 0.0f;
+#pragma unroll
+          for (int c = 0; c < CPL; ++c) v += slice[c] == k ? dot[c] : 0.0f;
+          v = group_total<L>(v);
+          if (cl == L - 1 && on) sums[(wave * cores + k) * kWave + (j0 + SUB * u + sub - rbeg)] = v;
+        }
+        if (on && (inf[u] & kAlone) != 0u) {       // alone on its row: the gradient row is here
+          float* dst = d_rows + static_cast<size_t>(DENSE ? static_cast<uint32_t>(row[u]) : inf[u] & ~kAlone) * dv;
+          f32x4 old[DENSE ? CPL : 1][EPC / 4];
+          if constexpr (DENSE) {
+#pragma unroll
+            for (int c = 0; c < CPL; ++c)
+#pragma unroll
+              for (int e = 0; e < EPC; e += 4)
+                old[c][e / 4] = *reinterpret_cast<const f32x4*>(dst + (chunk0 + L * c) * EPC + e);
+          }
+#pragma unroll
+          for (int c = 0; c < CPL; ++c) {
+            const float wt = w_t[static_cast<size_t>(ent[u]) * cores + slice[c]];
+#pragma unroll
+            for (int e = 0; e < EPC; e += 4) {
+              f32x4 v = DENSE ? old[DENSE ? c : 0][e / 4] : f32x4{0.f, 0.f, 0.f, 0.f};
+              v.x += wt * dp[c][e];
+              v.y += wt * dp[c][e + 1];
+              v.z += wt * dp[c][e + 2];
+              v.w += wt * dp[c][e + 3];
+              *reinterpret_cast<f32x4*>(dst + (chunk0 + L * c) * EPC + e) = v;
+            }
+          }
+        }
+      }
+    }
+    if (CW > 1) __syncthreads();                   // (every wave takes every round)
+    else wave_lds_order();
+    // the group's waves share its entries' sums out: lane = entry, wave % CW, + CW, ... = core
+    for (int k = wave % CW; k < cores; k += CW) {
+      const int j = rbeg + lane;
+      if (j < rend) {
+        float v = sums[(group * CW * cores + k) * kWave + lane];
+#pragma unroll
+        for (int x = 1; x < CW; ++x) v += sums[((group * CW + x) * cores + k) * kWave + lane];
+        const int s = order[j];
+        dw_t[static_cast<size_t>(s) * cores + k] = v;
+      }
+    }
+    if (CW > 1) __syncthreads();                   // before the next round clears the sums
+    else wave_lds_order();
+  }
+}
+
+// ---------------------------------------------------------------- value rows of several entries
 
 constexpr int kListWaves = 8192;        // waves of the grids that walk the key lists (b2)
-// ... and the value-row lists (b1): four waves per SIMD, which the piece kernel's registers allow;
-// more value-row loads in flight pay where rows repeat (measured at tucker-ive-4M: 473 -> 453 us)
-constexpr int kValueListWaves = 16384;
-constexpr int kInFlight = 4;            // a piece's entries whose loads are issued together
+constexpr int kRowWaves = 16384;         // ... and the row lists
+constexpr int kJoinWaves = 4096;        // ... and of the join
+constexpr int kInFlight = 4;            // a key piece's entries whose loads are issued together
+constexpr int kRowInFlight = 4;         // a row piece's
 
-constexpr int kListPer = 16;                           // positions per thread
-constexpr int kListChunk = THREADS * kListPer;          // positions per workgroup
+// A row piece before it is walked: where it starts, its rows and entries and their records (one per
+// lane), and the rows on either side.
+struct RowPiece {
+  uint32_t at;           // first sorted position
+  uint2 own;             // lane: (row, entry) of position first + lane
+  uint2 rec;             // lane: its RowInfo::rec
+  uint32_t prev, next;   // the rows at first - 1 and first + 64
+};
 
-__device__ __forceinline__ bool is_piece_start(const uint32_t* __restrict__ keys, int i, int M,
-                                               uint32_t sentinel) {
-  if (i >= M) return false;
-  const uint32_t k = keys[i];
-  return k != sentinel && (i % kSeg == 0 || keys[i - 1] != k);
-}
-
-// Exclusive prefix of v over the workgroup's threads, in thread order (every thread calls it).
-__device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t* lds, uint32_t* total) {
-  const int tid = threadIdx.x;
-  lds[tid] = v;
-  __syncthreads();
-  for (int off = 1; off < THREADS; off <<= 1) {
-    const uint32_t add = tid >= off ? lds[tid - off] : 0u;
-    __syncthreads();
-    lds[tid] += add;
-    __syncthreads();
-  }
-  const uint32_t incl = lds[tid];
-  *total = lds[THREADS - 1];
-  __syncthreads();
-  return incl - v;
-}
-
-// A run of the sorted keys starts here (the compact row output numbers runs, not rows).
-__device__ __forceinline__ bool is_run_start(const uint32_t* __restrict__ keys, int i, int M) {
-  return i < M && (i == 0 || keys[i - 1] != keys[i]);
-}
-
-// Per chunk of kListChunk positions: its piece starts into offs[chunk] and, with runs wanted, its
-// run starts into offs[chunks + chunk]; one exclusive scan over both halves follows.
-__global__ __launch_bounds__(THREADS) void piece_count_kernel(const uint32_t* __restrict__ keys,
-                                                              int M, uint32_t sentinel,
-                                                              uint32_t* __restrict__ offs,
-                                                              int runs) {
-  __shared__ uint32_t lds[THREADS];
-  const int beg = blockIdx.x * kListChunk + threadIdx.x * kListPer;
-  uint32_t c = 0, cr = 0;
-  for (int k = 0; k < kListPer; ++k) {
-    c += is_piece_start(keys, beg + k, M, sentinel);
-    if (runs) cr += is_run_start(keys, beg + k, M);
-  }
-  uint32_t total;
-  block_prefix(c, lds, &total);
-  if (threadIdx.x == 0) offs[blockIdx.x] = total;
-  if (runs) {
-    block_prefix(cr, lds, &total);
-    if (threadIdx.x == 0) offs[gridDim.x + blockIdx.x] = total;
-  }
-}
-
-// offs: the scanned counts.  Writes the piece starts in order into list, their number into
-// counts[0] (counts[1] cleared); with run_of given also every position's run number, each run's
-// key into rows_out[run] (ascending) and the number of runs into *n_runs.
-__global__ __launch_bounds__(THREADS) void piece_write_kernel(const uint32_t* __restrict__ keys,
-                                                              int M, uint32_t sentinel,
-                                                              const uint32_t* __restrict__ offs,
-                                                              uint32_t* __restrict__ list,
-                                                              uint32_t* __restrict__ counts,
-                                                              uint32_t* __restrict__ run_of,
-                                                              int32_t* __restrict__ rows_out,
-                                                              int32_t* __restrict__ n_runs) {
-  __shared__ uint32_t lds[THREADS];
-  const int beg = blockIdx.x * kListChunk + threadIdx.x * kListPer;
-  uint32_t c = 0;
-  for (int k = 0; k < kListPer; ++k) c += is_piece_start(keys, beg + k, M, sentinel);
-  uint32_t total;
-  uint32_t at = offs[blockIdx.x] + block_prefix(c, lds, &total);
-  for (int k = 0; k < kListPer; ++k)
-    if (is_piece_start(keys, beg + k, M, sentinel)) list[at++] = static_cast<uint32_t>(beg + k);
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    counts[0] = offs[blockIdx.x] + total;
-    counts[1] = 0u;                                       // the spanning runs, appended later
-  }
-  if (run_of == nullptr) return;                          // (uniform over the grid)
-  uint32_t cr = 0;
-  for (int k = 0; k < kListPer; ++k) cr += is_run_start(keys, beg + k, M);
-  const uint32_t pieces = offs[gridDim.x];                // the scan's offset of the run half
-  uint32_t total_r;
-  uint32_t r = offs[gridDim.x + blockIdx.x] - pieces + block_prefix(cr, lds, &total_r);
-  for (int k = 0; k < kListPer && beg + k < M; ++k) {
-    if (is_run_start(keys, beg + k, M)) rows_out[r++] = static_cast<int32_t>(keys[beg + k]);
-    run_of[beg + k] = r - 1;                              // position 0 starts a run: r >= 1 here
-  }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
-    *n_runs = static_cast<int32_t>(offs[gridDim.x + blockIdx.x] - pieces + total_r);
-}
-
-size_t list_workspace_bytes(int M) {
-  const size_t chunks = (static_cast<size_t>(M) + kListChunk - 1) / kListChunk;
-  return (2 * chunks + 1) * sizeof(uint32_t) + scan_workspace_bytes(static_cast<int>(2 * chunks)) + 64;
-}
-
-// The piece starts of the sorted keys into list (in order) and their number into counts[0];
-// counts[1] cleared.  With run_of given (keys without the sentinel), also the runs as
-// piece_write_kernel states.  ws: list_workspace_bytes(M).
-hipError_t list_pieces(const uint32_t* keys, int M, uint32_t sentinel, uint32_t* list,
-                       uint32_t* counts, void* ws, hipStream_t s, uint32_t* run_of = nullptr,
-                       int32_t* rows_out = nullptr, int32_t* n_runs = nullptr) {
-  const int chunks = (M + kListChunk - 1) / kListChunk;
-  const int runs = run_of != nullptr ? 1 : 0;
-  uint32_t* offs = static_cast<uint32_t*>(ws);
-  uint32_t* sums = offs + 2 * chunks + 1;
-  hipLaunchKernelGGL(piece_count_kernel, dim3(chunks), dim3(THREADS), 0, s, keys, M, sentinel, offs,
-                     runs);
-  hipError_t e = scan_exclusive(offs, (1 + runs) * chunks, sums, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(piece_write_kernel, dim3(chunks), dim3(THREADS), 0, s, keys, M, sentinel, offs,
-                     list, counts, run_of, rows_out, n_runs);
-  return hipGetLastError();
-}
-
-// With run_of given (compact row output), a row's gradient goes to out[run_of[position] * dv],
-// written from zero; otherwise it is added into out[row * dv].  Either way the value stored is
-// (the row's previous value, or 0) + the row's sum, so a compact row holds exactly what the
-// dense form adds into a zeroed row.
-template <typename Elem>
-__global__ __launch_bounds__(THREADS) void gather_bwd_seg_kernel(
-    const uint32_t* __restrict__ rows, const uint32_t* __restrict__ ents, int M,
-    const Elem* __restrict__ values, int dv, const int32_t* __restrict__ idx,
-    const float* __restrict__ w, const int32_t* __restrict__ perm, int64_t n_values, int expand,
-    int cores, int bag, const float* __restrict__ d_pooled, float* __restrict__ d_values,
-    float* __restrict__ dw, float* __restrict__ partial, const uint32_t* __restrict__ list,
-    uint32_t* __restrict__ counts, uint32_t* __restrict__ heads, const uint32_t* __restrict__ run_of) {
-  constexpr int EPC = Chunk<Elem>::kElems;            // elements per 16-byte piece
+// The pieces of the runs of several entries: their w_e d_pooled rows summed in order.  GL lanes
+// of 16 bytes take an entry, 64 / GL entries at once, each lane group every (64 / GL)-th entry in
+// order, the groups then meeting by a fixed butterfly.  The next piece's record is read two pieces
+// ahead and its entries one piece ahead, so that a piece waits for its d_pooled rows only.
+// Bound by the re-reads of d_pooled: a run's tokens are random, so its rows come from all over.
+// SLICED: d_pooled is read from the copy that token_bwd_kernel left by column slice, [slice]
+// [pooled row][4 GL columns], slice s by XCD s % 8 (workgroups go to XCDs round-robin): an XCD
+// then reads a few columns of every row, a contiguous block that its 4 MiB L2 holds.  (The same
+// slices read from d_pooled itself lie a row apart, on two of the L2's sixteen channels.)  Otherwise
+// a wave walks all columns of its piece.  At 4,096 tokens of 256 entries on 7,600 rows (2 KiB of
+// d_pooled an entry): 146 us beside the token kernel's 108, against 342 us for one kernel that did
+// both from d_pooled as it is.  8,192 waves 169 us, 32,768 146; two entries in flight a lane group
+// 252, eight 153; slices of half the columns (2 MiB of d_pooled an XCD) no faster.
+template <int GL, bool SLICED>
+__global__ __launch_bounds__(THREADS) void row_bwd_kernel(
+    const uint2* __restrict__ sorted, const uint32_t* __restrict__ n_sorted,
+    const uint2* __restrict__ rec, const uint32_t* __restrict__ info, const float* __restrict__ w,
+    int cores, int dv, size_t pooled_rows, const float* __restrict__ d_pooled, float* __restrict__ out, int compact,
+    float* __restrict__ partial, const uint32_t* __restrict__ list, uint32_t* __restrict__ counts,
+    uint32_t* __restrict__ heads) {
+  constexpr int S = kWave / GL, kCols = 4 * GL;
   const int lane = threadIdx.x & (kWave - 1);
+  const int sub = lane / GL;
+  const int n = static_cast<int>(*n_sorted);
   const uint32_t n_pieces = counts[0];
-  for (uint32_t k = blockIdx.x * NWAVES + threadIdx.x / kWave; k < n_pieces;
-       k += gridDim.x * NWAVES) {                     // wave-uniform: no barrier in this kernel
-  const int ps = static_cast<int>(list[k]);
-  const uint32_t row = rows[ps];
-  int pe;
-  bool run_start, run_end;
-  piece_at(rows, ps, M, row, &pe, &run_start, &run_end);
-  if (run_start && !run_end && lane == 0)            // a run spanning segments: list its head
-    heads[atomicAdd(counts + 1, 1u)] = static_cast<uint32_t>(ps);
-  const int g = ps / kSeg;
-  const int slice_w = dv / cores;
-  // the piece's entries, one per lane: entry number and the d_pooled row (token, virtual block)
-  const int n_e = pe - ps;
-  int my_ent = 0, my_prow = 0;
-  if (lane < n_e) {
-    my_ent = static_cast<int>(ents[ps + lane]);
-    const int p = perm != nullptr ? static_cast<int>(perm[idx[my_ent]] / n_values) : 0;
-    my_prow = (my_ent / bag) * expand + p;
-  }
-  const Elem* vrow = values + static_cast<size_t>(row) * dv;
-  float* drow = d_values + static_cast<size_t>(run_of != nullptr ? run_of[ps] : row) * dv;
-  // lane j holds entry j's weight gradient per core, summed over the column steps in order and
-  // written once at the end of the piece
-  float my_dw[kMaxCores];
+  const int per_core = dv / cores;
+  // sliced: each XCD walks the whole list for its own slices
+  const uint32_t xcds = SLICED ? 8u : 1u;
+  const uint32_t first = (blockIdx.x / xcds) * NWAVES + threadIdx.x / kWave;
+  const uint32_t step = (gridDim.x / xcds) * NWAVES;
+  const int c_first = SLICED ? static_cast<int>(blockIdx.x & 7u) * kCols : 0;
+  if (first >= n_pieces) return;                     // (whole waves: no barrier in this kernel)
+  auto fetch = [&](uint32_t at, RowPiece& p) {
+    p.at = at;
+    const int ps = static_cast<int>(at);
+    const int pos = min(ps + lane, n - 1);
+    p.own = sorted[pos];
+    p.rec = rec[pos];
+    p.prev = sorted[max(ps - 1, 0)].x;
+    p.next = sorted[min(ps + kWave, n - 1)].x;
+  };
+  for (int c0 = c_first; c0 < (SLICED ? dv : 1); c0 += 8 * kCols) {
+    RowPiece nxt;
+    fetch(list[first], nxt);
+    uint32_t after = first + step < n_pieces ? list[first + step] : 0u;
+    for (uint32_t k = first; k < n_pieces; k += step) {  // wave-uniform
+      const RowPiece cur = nxt;
+      if (k + step < n_pieces) fetch(after, nxt);
+      if (k + 2 * step < n_pieces) after = list[k + 2 * step];
+      const int ps = static_cast<int>(cur.at);
+      const uint32_t row = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(cur.own.x)));
+      const bool starts = ps == 0 || cur.prev != row;
+      const int seg_end = min(n, (ps / kSeg + 1) * kSeg);
+      const uint64_t other = __ballot(ps + lane < seg_end && cur.own.x != row);
+      const int n_e = other != 0ull ? __builtin_ctzll(other) : seg_end - ps;
+      // the row after the piece (a piece that stops before its segment's end stops at another row)
+      const uint32_t past = n_e == kWave ? cur.next : static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(cur.own.x), n_e & (kWave - 1)));
+      const bool ends = ps + n_e >= n || past != row;
+      if (c0 == 0 && starts && !ends && lane == 0) heads[atomicAdd(counts + 1, 1u)] = k;
+      const int my_prow = static_cast<int>(cur.rec.x);
+      const int my_we = static_cast<int>(cur.rec.y);
+      const uint32_t run = compact ? info[__builtin_amdgcn_readfirstlane(static_cast<int>(cur.own.y))] & ~kAlone : row;
+      for (int c = c0; c < (SLICED ? c0 + 1 : dv); c += kCols) {
+        const int col = c + (lane % GL) * 4;
+        const int core = cores > 1 ? col / per_core : 0;   // four columns lie in one core's slice
+        const float* src = SLICED ? d_pooled + static_cast<size_t>(c0 / kCols) * pooled_rows * kCols + (col - c0)
+                                  : d_pooled + col;
+        const int pitch = SLICED ? kCols : dv;
+        float* dst = out + static_cast<size_t>(run) * dv + col;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        f32x4 old = {0.f, 0.f, 0.f, 0.f};
+        if (starts && !compact && sub == 0) old = *reinterpret_cast<const f32x4*>(dst);
+        for (int j0 = 0; j0 < n_e; j0 += S * kRowInFlight) {  // wave-uniform
+          f32x4 v[kRowInFlight];
+          float wt[kRowInFlight];
 #pragma unroll
-  for (int c = 0; c < kMaxCores; ++c) my_dw[c] = 0.0f;
-  for (int c0 = 0; c0 < dv; c0 += kWave * EPC) {
-    const int col = c0 + lane * EPC;
-    const bool active = col < dv;
-    const int sl = active ? col / slice_w : 0;        // a piece lies in one column slice
-    float x[EPC], acc[EPC];
+          for (int u = 0; u < kRowInFlight; ++u) {         // all loads first
+            const int j = j0 + S * u + sub;
+            const int jj = min(j, n_e - 1);
+            const int pr = __shfl(my_prow, jj, kWave);
+            const int we = __shfl(my_we, jj, kWave);
+            v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+            wt[u] = __int_as_float(we);
+            if (cores > 1) wt[u] = j < n_e ? w[static_cast<size_t>(we) * cores + core] : 0.0f;
+            if (j < n_e) v[u] = *reinterpret_cast<const f32x4*>(src + static_cast<size_t>(pr) * pitch);
+          }
 #pragma unroll
-    for (int k = 0; k < EPC; ++k) {
-      x[k] = 0.0f;
-      acc[k] = 0.0f;
-    }
-    if (active) Chunk<Elem>::load(vrow + col, x);
-    // a whole run adds into its gradient row: read that row now, under the entries' loads
-    // (a compact row starts from zero)
-    const bool whole = run_start && run_end;
-    f32x4 old[EPC / 4];
-#pragma unroll
-    for (int k = 0; k < EPC / 4; ++k)
-      old[k] = (active && whole && run_of == nullptr) ? *reinterpret_cast<const f32x4*>(drow + col + 4 * k)
-                                                      : f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int j0 = 0; j0 < n_e; j0 += kInFlight) {    // wave-uniform
-      int ent[kInFlight];
-      float wt[kInFlight];
-      f32x4 v[kInFlight][EPC / 4];
-#pragma unroll
-      for (int u = 0; u < kInFlight; ++u) {          // all loads first
-        const int j = min(j0 + u, n_e - 1);
-        ent[u] = __builtin_amdgcn_readlane(my_ent, j);
-        const int prow = __builtin_amdgcn_readlane(my_prow, j);
-        wt[u] = 0.0f;
-#pragma unroll
-        for (int k = 0; k < EPC / 4; ++k) v[u][k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if (active && j0 + u < n_e) {                // (past the piece's end: no loads)
-          wt[u] = w[static_cast<size_t>(ent[u]) * cores + sl];
-          const f32x4* src = reinterpret_cast<const f32x4*>(d_pooled + static_cast<size_t>(prow) * dv + col);
-#pragma unroll
-          for (int k = 0; k < EPC / 4; ++k) v[u][k] = src[k];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kInFlight; ++u) {          // then the entries in order
-        if (j0 + u >= n_e) break;
-        float dot = 0.0f;
-#pragma unroll
-        for (int k = 0; k < EPC; k += 4) {
-          const f32x4 vv = v[u][k / 4];
-          dot = fmaf(vv.x, x[k], dot);
-          dot = fmaf(vv.y, x[k + 1], dot);
-          dot = fmaf(vv.z, x[k + 2], dot);
-          dot = fmaf(vv.w, x[k + 3], dot);
-          acc[k] = fmaf(wt[u], vv.x, acc[k]);
-          acc[k + 1] = fmaf(wt[u], vv.y, acc[k + 1]);
-          acc[k + 2] = fmaf(wt[u], vv.z, acc[k + 2]);
-          acc[k + 3] = fmaf(wt[u], vv.w, acc[k + 3]);
+          for (int u = 0; u < kRowInFlight; ++u) {         // then this group's entries in order
+            const int j = j0 + S * u + sub;
+            if (j >= n_e) continue;                        // (no product with a row that is not there)
+            acc.x = fmaf(wt[u], v[u].x, acc.x);
+            acc.y = fmaf(wt[u], v[u].y, acc.y);
+            acc.z = fmaf(wt[u], v[u].z, acc.z);
+            acc.w = fmaf(wt[u], v[u].w, acc.w);
+          }
         }
 #pragma unroll
-        for (int c = 0; c < kMaxCores; ++c) {
-          if (c >= cores) break;
-          const float sc = wave_sum(sl == c ? dot : 0.0f);
-          if (lane == j0 + u) my_dw[c] = c0 == 0 ? sc : my_dw[c] + sc;
+        for (int off = GL; off < kWave; off <<= 1) {
+          acc.x += __shfl_xor(acc.x, off, kWave);
+          acc.y += __shfl_xor(acc.y, off, kWave);
+          acc.z += __shfl_xor(acc.z, off, kWave);
+          acc.w += __shfl_xor(acc.w, off, kWave);
+        }
+        if (sub == 0) {
+          if (starts) *reinterpret_cast<f32x4*>(dst) = old + acc;
+          else *reinterpret_cast<f32x4*>(partial + static_cast<size_t>(ps / kSeg) * dv + col) = acc;
         }
       }
     }
-    if (!active) continue;
-    if (whole) {                                      // a whole run: add into its row
-#pragma unroll
-      for (int k = 0; k < EPC; k += 4) {
-        f32x4 v = old[k / 4];
-        v.x += acc[k]; v.y += acc[k + 1]; v.z += acc[k + 2]; v.w += acc[k + 3];
-        *reinterpret_cast<f32x4*>(drow + col + k) = v;
-      }
-    } else {                                          // cut by a segment edge: its partial row
-      float* dst = partial + (static_cast<size_t>(2) * g + (run_start ? 1 : 0)) * dv + col;
-#pragma unroll
-      for (int k = 0; k < EPC; k += 4)
-        *reinterpret_cast<f32x4*>(dst + k) = f32x4{acc[k], acc[k + 1], acc[k + 2], acc[k + 3]};
-    }
-  }
-  if (lane < n_e) {                                   // this wave is the entries' only writer
-#pragma unroll
-    for (int c = 0; c < kMaxCores; ++c) {
-      if (c >= cores) break;
-      dw[static_cast<size_t>(my_ent) * cores + c] = my_dw[c];
-    }
-  }
   }
 }
 
-// One wave per run that spans segments: its partial rows, in segment order, added into the row.
-__global__ __launch_bounds__(THREADS) void seg_join_kernel(const uint32_t* __restrict__ keys, int M,
+// One wave per run that spans segments: the partial rows of its later segments, in order, added
+// into the row, which holds the sum of its first piece.
+// heads: the places in list of those runs' first pieces.
+__global__ __launch_bounds__(THREADS) void seg_join_kernel(const uint2* __restrict__ sorted,
+                                                           const uint32_t* __restrict__ n_sorted,
                                                            int width, const float* __restrict__ partial,
                                                            float* __restrict__ out,
+                                                           const uint32_t* __restrict__ list,
                                                            const uint32_t* __restrict__ heads,
                                                            const uint32_t* __restrict__ counts,
                                                            int H, int n, float* __restrict__ out2,
-                                                           const uint32_t* __restrict__ run_of) {
+                                                           const uint32_t* __restrict__ info) {
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t n_heads = counts[1];
   for (uint32_t hk = blockIdx.x * NWAVES + threadIdx.x / kWave; hk < n_heads;
        hk += gridDim.x * NWAVES) {
-  const int i = static_cast<int>(heads[hk]);
-  const uint32_t key = keys[i];
-  const int g0 = i / kSeg;
-  const int end = run_end(keys, i, M, key);
-  const int g1 = (end - 1) / kSeg;
-  // the row of this key: value rows directly, or (out2 given) key rows of the two axes
-  float* dst;
-  if (run_of != nullptr) {                           // compact rows: written from zero
-    dst = out + static_cast<size_t>(run_of[i]) * width;
-  } else if (out2 == nullptr) {
-    dst = out + static_cast<size_t>(key) * width;
-  } else {
-    const int axis = static_cast<int>(key / (static_cast<uint32_t>(H) * n));
-    dst = (axis ? out2 : out) + static_cast<size_t>(key - static_cast<uint32_t>(axis) * H * n) * width;
-  }
-  for (int c = lane * 4; c < width; c += kWave * 4) {
-    f32x4 acc = *reinterpret_cast<const f32x4*>(partial + (static_cast<size_t>(2) * g0 + 1) * width + c);
-    for (int g = g0 + 1; g <= g1; ++g)
-      acc += *reinterpret_cast<const f32x4*>(partial + static_cast<size_t>(2) * g * width + c);
-    f32x4* d = reinterpret_cast<f32x4*>(dst + c);
-    f32x4 v = run_of != nullptr ? f32x4{0.f, 0.f, 0.f, 0.f} : *d;
-    v += acc;
-    *d = v;
-  }
+    const int i = static_cast<int>(list[heads[hk]]);
+    const uint32_t key = sorted[i].x;
+    const int g0 = i / kSeg;
+    const int end = run_end(sorted, i, static_cast<int>(*n_sorted), key);
+    const int g1 = (end - 1) / kSeg;
+    // the row of this key: value rows directly, or (out2 given) key rows of the two axes
+    float* dst;
+    if (info != nullptr) {                             // compact rows: by run
+      dst = out + static_cast<size_t>(info[sorted[i].y] & ~kAlone) * width;
+    } else if (out2 == nullptr) {
+      dst = out + static_cast<size_t>(key) * width;
+    } else {
+      const int axis = static_cast<int>(key / (static_cast<uint32_t>(H) * n));
+      dst = (axis ? out2 : out) + static_cast<size_t>(key - static_cast<uint32_t>(axis) * H * n) * width;
+    }
+    for (int c = lane * 4; c < width; c += kWave * 4) {
+      f32x4* d = reinterpret_cast<f32x4*>(dst + c);
+      const f32x4 head = *d;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      for (int g = g0 + 1; g <= g1; ++g)
+        acc += *reinterpret_cast<const f32x4*>(partial + static_cast<size_t>(g) * width + c);
+      *d = head + acc;
+    }
   }
 }
 
@@ -407,7 +701,7 @@ __global__ __launch_bounds__(THREADS) void seg_join_kernel(const uint32_t* __res
 
 // One wave per (token, head); slot s = g * 64 + lane for the NG groups g of a lane.  The waves
 // of a workgroup share nothing, so the kernel has no workgroup barrier; each wave's own LDS
-// traffic is ordered by wave_sync.
+// traffic is ordered by wave_lds_order.
 template <int NG>
 struct ScoreBwdLds {
   int dist[2][NG * kWave];                     // distinct rows / columns, in slot order
@@ -417,12 +711,6 @@ struct ScoreBwdLds {
 
 template <int NG>
 constexpr int score_bwd_waves() { return NG >= 4 ? 2 : 4; }
-
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // The lanes whose key_other (valid_other) equals this lane's key: one ballot per key bit.
 __device__ __forceinline__ uint64_t key_match(uint32_t key, uint32_t key_other, bool valid_other,
@@ -442,8 +730,8 @@ __global__ __launch_bounds__(score_bwd_waves<NG>() * kWave) void score_bwd_kerne
     const float* __restrict__ core_all, const int32_t* __restrict__ idx,
     const float* __restrict__ w, const float* __restrict__ dw, int T, int H, int n, int key_bits,
     int dk, int rank, int m, int tucker, int softmax, int hc, float* __restrict__ dq_row,
-    float* __restrict__ dq_col, uint32_t* __restrict__ ekeys, uint32_t* __restrict__ evals,
-    float* __restrict__ edS, float* __restrict__ dc_part) {
+    float* __restrict__ dq_col, uint32_t* __restrict__ ekeys, float* __restrict__ edS,
+    float* __restrict__ dc_part) {
   constexpr int W = score_bwd_waves<NG>();
   __shared__ ScoreBwdLds<NG> lds[W];
   const int lane = threadIdx.x & (kWave - 1);
@@ -524,7 +812,7 @@ __global__ __launch_bounds__(score_bwd_waves<NG>() * kWave) void score_bwd_kerne
       if (valid[g] && f == g * kWave + lane) sh.dist[a][p] = static_cast<int>(key[a][g]);
     }
   }
-  wave_sync();
+  wave_lds_order();
   // ---- Tucker: per-slice scores of the distinct keys, four lanes per key row.  The quad is
   // split into one group per slice (4, 2 or 1 lanes for rank 1, 2, 3-4; rank 3 leaves a lane
   // idle); a lane strides its slice's 16-byte pieces by the group width, eight loads in flight,
@@ -572,7 +860,7 @@ __global__ __launch_bounds__(score_bwd_waves<NG>() * kWave) void score_bwd_kerne
       if (ok && part == 0)
         for (int r = rank; r < kMaxRank; ++r) sh.sd[a][k][r] = 0.0f;
     }
-    wave_sync();
+    wave_lds_order();
 #pragma unroll
     for (int g = 0; g < NG; ++g)
 #pragma unroll
@@ -632,7 +920,7 @@ __global__ __launch_bounds__(score_bwd_waves<NG>() * kWave) void score_bwd_kerne
       if (lane == 0) dc_part[th * hc * rank * rank + x] = v;
     }
   }
-  wave_sync();
+  wave_lds_order();
   // ---- dS per distinct key: its slots' terms in slot order, summed by the leading slot
 #pragma unroll
   for (int a = 0; a < 2; ++a)
@@ -656,7 +944,7 @@ __global__ __launch_bounds__(score_bwd_waves<NG>() * kWave) void score_bwd_kerne
 #pragma unroll
         for (int r = 0; r < kMaxRank; ++r) sh.sd[a][pos[a][g]][r] = acc[r];
     }
-  wave_sync();
+  wave_lds_order();
   // ---- dq = sum over distinct keys of dS K (eqs. (2) / (4) transposed)
   const int width = dk / R;
 #pragma unroll
@@ -723,7 +1011,7 @@ __global__ __launch_bounds__(score_bwd_waves<NG>() * kWave) void score_bwd_kerne
     }
   }
   // ---- key-gradient entries: slot ((t H + h) 2 + axis) m + k for the k-th distinct key; the
-  // rest of the axis' m slots hold the sentinel
+  // rest of the axis' m slots hold the sentinel, which the sort drops
   const uint32_t sentinel = static_cast<uint32_t>(2 * H) * n;
 #pragma unroll
   for (int a = 0; a < 2; ++a)
@@ -734,14 +1022,10 @@ __global__ __launch_bounds__(score_bwd_waves<NG>() * kWave) void score_bwd_kerne
       const size_t base = (th * 2 + a) * m;
       if (first[a][g] == s) {
         const size_t slot = base + pos[a][g];
-        evals[slot] = static_cast<uint32_t>(slot);
         ekeys[slot] = static_cast<uint32_t>((a * H + h) * n) + key[a][g];
         for (int r = 0; r < rank; ++r) edS[slot * rank + r] = sh.sd[a][pos[a][g]][r];
       }
-      if (s >= nd[a]) {
-        evals[base + s] = static_cast<uint32_t>(base + s);
-        ekeys[base + s] = sentinel;
-      }
+      if (s >= nd[a]) ekeys[base + s] = sentinel;
     }
 }
 
@@ -749,13 +1033,14 @@ __global__ __launch_bounds__(score_bwd_waves<NG>() * kWave) void score_bwd_kerne
 // entries of its run, in order, of dS[entry][slice] q[t, h, :]; pieces cut by a segment store
 // their partial row for seg_join_kernel.
 __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
-    const uint32_t* __restrict__ keys, const uint32_t* __restrict__ slots, int M, uint32_t sentinel,
+    const uint2* __restrict__ sorted, const uint32_t* __restrict__ n_sorted,
     const float* __restrict__ edS, const float* __restrict__ q_row, const float* __restrict__ q_col,
     float* __restrict__ dk_row, float* __restrict__ dk_col, int H, int n, int dk, int rank, int m,
     float* __restrict__ partial, const uint32_t* __restrict__ list,
     uint32_t* __restrict__ counts, uint32_t* __restrict__ heads) {
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t n_pieces = counts[0];
+  const int M = static_cast<int>(*n_sorted);
   // The pieces (in (axis, head, key) order) are split into eight contiguous ranges, one per XCD
   // (workgroups go to XCDs round-robin), so that an XCD's waves read the query rows of few
   // (axis, head) blocks and find them in its L2.
@@ -766,13 +1051,11 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
   for (uint32_t pk = lo + (blockIdx.x >> 3) * NWAVES + threadIdx.x / kWave; pk < hi;
        pk += xcd_waves) {
   const int ps = static_cast<int>(list[pk]);
-  const uint32_t key = keys[ps];                     // never the sentinel: not listed
-  int pe;
-  bool run_start, run_end;
-  piece_at(keys, ps, M, key, &pe, &run_start, &run_end);
-  if (run_start && !run_end && lane == 0)
-    heads[atomicAdd(counts + 1, 1u)] = static_cast<uint32_t>(ps);
-  const int g = ps / kSeg;
+  const uint32_t key = sorted[ps].x;
+  const bool run_start = ps == 0 || sorted[ps - 1].x != key;
+  bool run_end;
+  const int pe = piece_end(sorted, ps, M, key, &run_end);
+  if (run_start && !run_end && lane == 0) heads[atomicAdd(counts + 1, 1u)] = pk;
   const int axis = static_cast<int>(key / (static_cast<uint32_t>(H) * n));
   const int rem = static_cast<int>(key - static_cast<uint32_t>(axis) * H * n);
   const int h = rem / n;
@@ -780,9 +1063,8 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
   float* dK = (axis ? dk_col : dk_row) + static_cast<size_t>(rem) * dk;
   const int width = dk / rank;
   const int n_e = pe - ps;
-  const uint32_t my_slot = lane < n_e ? slots[ps + lane] : 0u;   // one entry per lane
-  const bool whole = run_start && run_end;
-  float* const part_row = partial + (static_cast<size_t>(2) * g + (run_start ? 1 : 0)) * dk;
+  const uint32_t my_slot = lane < n_e ? sorted[ps + lane].y : 0u;   // one entry per lane
+  float* const part_row = partial + static_cast<size_t>(ps / kSeg) * dk;
   if (dk <= 2 * kWave && (dk & (dk - 1)) == 0) {
     // Rows of at most 128 dims fill a fraction of the wave: G = dk / 4 lanes take one entry, and
     // the wave's S = 64 / G lane groups take entries s, s + S, s + 2 S, ... of the piece, each
@@ -791,7 +1073,7 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
     const int sub = lane / G, d = (lane % G) * 4;
     const int r = d / width;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    const f32x4 old = (whole && sub == 0) ? *reinterpret_cast<const f32x4*>(dK + d) : f32x4{0.f, 0.f, 0.f, 0.f};
+    const f32x4 old = (run_start && sub == 0) ? *reinterpret_cast<const f32x4*>(dK + d) : f32x4{0.f, 0.f, 0.f, 0.f};
     for (int j0 = 0; j0 < n_e; j0 += S * kInFlight) {   // wave-uniform
       f32x4 qv[kInFlight];
       float ds[kInFlight];
@@ -822,7 +1104,7 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
       acc.w += __shfl_xor(acc.w, off, kWave);
     }
     if (sub == 0) {
-      if (whole) *reinterpret_cast<f32x4*>(dK + d) = old + acc;
+      if (run_start) *reinterpret_cast<f32x4*>(dK + d) = old + acc;
       else *reinterpret_cast<f32x4*>(part_row + d) = acc;
     }
     continue;
@@ -832,8 +1114,8 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
     const bool active = d < dk;
     const int r = active ? d / width : 0;             // four consecutive dims lie in one slice
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    // a whole run adds into its key's gradient row: read it now, under the entries' loads
-    const f32x4 old = (active && whole) ? *reinterpret_cast<const f32x4*>(dK + d) : f32x4{0.f, 0.f, 0.f, 0.f};
+    // a piece that starts its run adds into its key's gradient row: read it now, under the entries' loads
+    const f32x4 old = (active && run_start) ? *reinterpret_cast<const f32x4*>(dK + d) : f32x4{0.f, 0.f, 0.f, 0.f};
     for (int j0 = 0; j0 < n_e; j0 += 2 * kInFlight) {  // wave-uniform
       f32x4 qv[2 * kInFlight];
       float ds[2 * kInFlight];
@@ -859,7 +1141,7 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
       }
     }
     if (!active) continue;
-    if (whole) *reinterpret_cast<f32x4*>(dK + d) = old + acc;
+    if (run_start) *reinterpret_cast<f32x4*>(dK + d) = old + acc;
     else *reinterpret_cast<f32x4*>(part_row + d) = acc;
   }
   }
@@ -892,14 +1174,79 @@ int bits_for(int64_t n) {
 
 }  // namespace
 
+// [entry info: M words][segment heads][counts][chunk counts][partial rows][as many again, for
+// d_pooled by column slice][sort: its pairs, the dead half of which holds the entries' records, and
+// M spare words, which hold the piece list: runs of several entries alone are cut into pieces, at
+// most M / 2 + nseg of them]
 size_t gather_backward_workspace_bytes(int T, int bag, int dv) {
   const int M = T * bag;
   if (M == 0) return 0;
   const size_t nseg = (static_cast<size_t>(M) + kSeg - 1) / kSeg;
-  return 4 * round_up256(static_cast<size_t>(M) * sizeof(uint32_t)) + round_up256(nseg * sizeof(uint32_t)) +
-         256 + round_up256(2 * nseg * dv * sizeof(float)) + round_up256(sort_workspace_bytes(M)) +
-         round_up256(list_workspace_bytes(M));
+  return round_up256(static_cast<size_t>(M) * sizeof(uint32_t)) + round_up256(nseg * sizeof(uint32_t)) +
+         256 + round_up256(list_chunks(M) * sizeof(uint2)) +
+         2 * round_up256(nseg * dv * sizeof(float)) + round_up256(sort_workspace_bytes(M));
 }
+
+namespace {
+
+template <typename Elem>
+hipError_t launch_tokens(const Elem* values, uint32_t n_values, int dv, int T, int bag,
+                         const int32_t* idx, const float* w, const int32_t* perm, int expand, int cores,
+                         const float* d_pooled, const uint32_t* info, float* d_rows, bool dense,
+                         float* dw, float* sliced, int slice_cols, hipStream_t s) {
+  const int chunks = dv * static_cast<int>(sizeof(Elem)) / 16;
+  const size_t lds = static_cast<size_t>(NWAVES) * cores * kWave * 4 + static_cast<size_t>(bag) * 12;
+  const dim3 block(THREADS);
+  // few tokens: several workgroups share a bag, until the launch has its waves or a group of waves
+  // would fall below four entries
+#define UMEM_TOKENS_AS(LL, CC, CW, SLICED, DENSE)                                                  \
+  hipLaunchKernelGGL((token_bwd_kernel<Elem, LL, CC, CW, SLICED, DENSE>), grid, block, lds, s, values, \
+                     dv, bag, idx, w, perm, n_values, expand, cores, d_pooled, info, d_rows, dw,  \
+                     sliced, slice_cols)
+#define UMEM_TOKENS(LL, CC, CW)                                                                   \
+  do {                                                                                            \
+    int split = 1;                                                                                \
+    while (T * NWAVES * split < kTokenWaves && bag * CW >= 4 * NWAVES * 2 * split) split *= 2;    \
+    const dim3 grid(T, split);                                                                    \
+    constexpr bool SL = LL == kWave;                                                              \
+    if (SL && sliced != nullptr && dense) UMEM_TOKENS_AS(LL, CC, CW, SL, true);                   \
+    else if (SL && sliced != nullptr) UMEM_TOKENS_AS(LL, CC, CW, SL, false);                      \
+    else if (dense) UMEM_TOKENS_AS(LL, CC, CW, false, true);                                      \
+    else UMEM_TOKENS_AS(LL, CC, CW, false, false);                                                \
+  } while (0)
+  switch (chunks) {
+    case 1: UMEM_TOKENS(1, 1, 1); break;
+    case 2: UMEM_TOKENS(2, 1, 1); break;
+    case 4: UMEM_TOKENS(4, 1, 1); break;
+    case 8: UMEM_TOKENS(8, 1, 1); break;
+    case 16: UMEM_TOKENS(16, 1, 1); break;
+    case 32: UMEM_TOKENS(32, 1, 1); break;
+    case 64: UMEM_TOKENS(64, 1, 1); break;
+    case 128: UMEM_TOKENS(64, 2, 1); break;
+    case 192: UMEM_TOKENS(64, 3, 1); break;
+    case 256: UMEM_TOKENS(64, 2, 2); break;
+    case 320: UMEM_TOKENS(64, 5, 1); break;
+    case 384: UMEM_TOKENS(64, 3, 2); break;
+    case 448: UMEM_TOKENS(64, 7, 1); break;
+    case 512: UMEM_TOKENS(64, 2, 4); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef UMEM_TOKENS
+#undef UMEM_TOKENS_AS
+  return hipGetLastError();
+}
+
+// Columns of row_bwd_kernel's slices (dv a multiple of 256): a multiple of eight slices of 32 to 256
+// columns, as wide as leaves each XCD no more than kSliceBytes of d_pooled to keep in its 4 MiB L2
+// at a time.
+constexpr int64_t kSliceBytes = 9 << 19;
+int slice_columns(int64_t pooled_rows, int dv) {
+  int cols = 32;
+  while (cols < 256 && dv % (16 * cols) == 0 && pooled_rows * 2 * cols * 4 <= kSliceBytes) cols *= 2;
+  return cols;
+}
+
+}  // namespace
 
 // rows_out == nullptr: d_values is the dense [n_values, dv] gradient, added into.  Otherwise the
 // compact form: d_values is [T * bag, dv], row r the gradient of rows_out[r], the r-th distinct
@@ -913,46 +1260,77 @@ hipError_t launch_gather_backward(int64_t n_values, int dv, int vdtype, const vo
   const int M = T * bag;
   if (M == 0) return hipSuccess;
   char* base = static_cast<char*>(ws);
-  uint32_t* keys = reinterpret_cast<uint32_t*>(base);
-  uint32_t* vals = reinterpret_cast<uint32_t*>(base + round_up256(static_cast<size_t>(M) * sizeof(uint32_t)));
+  uint32_t* info = reinterpret_cast<uint32_t*>(base);
+  base += round_up256(static_cast<size_t>(M) * sizeof(uint32_t));
   const size_t nseg = (static_cast<size_t>(M) + kSeg - 1) / kSeg;
-  char* p0 = base + 2 * round_up256(static_cast<size_t>(M) * sizeof(uint32_t));
-  uint32_t* list = reinterpret_cast<uint32_t*>(p0);
-  p0 += round_up256(static_cast<size_t>(M) * sizeof(uint32_t));
-  uint32_t* heads = reinterpret_cast<uint32_t*>(p0);
-  p0 += round_up256(nseg * sizeof(uint32_t));
-  uint32_t* counts = reinterpret_cast<uint32_t*>(p0);
-  p0 += 256;
-  float* partial = reinterpret_cast<float*>(p0);
-  void* sws = p0 + round_up256(2 * nseg * dv * sizeof(float));
-  void* lws = static_cast<char*>(sws) + round_up256(sort_workspace_bytes(M));
-  uint32_t* run_of = reinterpret_cast<uint32_t*>(static_cast<char*>(lws) + round_up256(list_workspace_bytes(M)));
-  const unsigned kb = static_cast<unsigned>(std::min((M + THREADS - 1) / THREADS, 4096));
-  hipLaunchKernelGGL(bwd_keys_kernel, dim3(kb), dim3(THREADS), 0, s, idx,
-                     expand > 1 ? perm : nullptr, n_values, M, keys, vals);
-  uint32_t *rows_sorted, *ents_sorted;
-  hipError_t e = sort_pairs(keys, vals, M, bits_for(n_values), sws, s, &rows_sorted, &ents_sorted);
-  if (e != hipSuccess) return e;
+  uint32_t* heads = reinterpret_cast<uint32_t*>(base);
+  base += round_up256(nseg * sizeof(uint32_t));
+  uint32_t* counts = reinterpret_cast<uint32_t*>(base);
+  base += 256;
+  uint2* chunk_cnt = reinterpret_cast<uint2*>(base);
+  base += round_up256(list_chunks(M) * sizeof(uint2));
+  float* partial = reinterpret_cast<float*>(base);
+  base += round_up256(nseg * dv * sizeof(float));
+  float* sliced = reinterpret_cast<float*>(base);
+  base += round_up256(nseg * dv * sizeof(float));
+  const SortPlan sp = sort_plan(M, bits_for(n_values), base);
+  const int32_t* pm = expand > 1 ? perm : nullptr;
+  const uint32_t nv = static_cast<uint32_t>(n_values);              // at most 2^31
   const int c = cores > 1 ? cores : 1;
-  const dim3 list_grid(kValueListWaves / NWAVES);
-  // row indices are below 2^31: the sentinel never occurs
   const bool compact = rows_out != nullptr;
-  e = list_pieces(rows_sorted, M, 0xFFFFFFFFu, list, counts, lws, s, compact ? run_of : nullptr,
-                  rows_out, n_rows);
+  hipLaunchKernelGGL(bwd_keys_kernel, dim3(sp.tiles), dim3(kSortThreads), 0, s, idx, pm, nv, bag, expand,
+                     info, sp);
+  uint2 *sorted, *rec;
+  uint32_t* list = sp.spare;
+  // (row indices are below 2^31: no key is skipped)
+  hipError_t e = sort_run(sp, 0xFFFFFFFFu, true, s, &sorted, &rec);
   if (e != hipSuccess) return e;
-  const uint32_t* ro = compact ? run_of : nullptr;
-  if (vdtype == UMEM_F32)
-    hipLaunchKernelGGL(gather_bwd_seg_kernel<float>, list_grid, dim3(THREADS), 0, s, rows_sorted,
-                       ents_sorted, M, static_cast<const float*>(values), dv, idx, w,
-                       expand > 1 ? perm : nullptr, n_values, expand, c, bag, d_pooled, d_values, dw,
-                       partial, list, counts, heads, ro);
-  else
-    hipLaunchKernelGGL(gather_bwd_seg_kernel<uint16_t>, list_grid, dim3(THREADS), 0, s, rows_sorted,
-                       ents_sorted, M, static_cast<const uint16_t*>(values), dv, idx, w,
-                       expand > 1 ? perm : nullptr, n_values, expand, c, bag, d_pooled, d_values, dw,
-                       partial, list, counts, heads, ro);
-  hipLaunchKernelGGL(seg_join_kernel, list_grid, dim3(THREADS), 0, s, rows_sorted, M, dv, partial,
-                     d_values, heads, counts, 0, 0, nullptr, ro);
+  const RowInfo ri{info, rec, c == 1 ? w : nullptr, rows_out, n_rows};
+  hipLaunchKernelGGL(piece_count_kernel<true>, dim3(list_chunks(M)), dim3(THREADS), 0, s, sorted, sp.n,
+                     chunk_cnt);
+  hipLaunchKernelGGL(piece_write_kernel<true>, dim3(list_chunks(M)), dim3(THREADS), 0, s, sorted, sp.n,
+                     chunk_cnt, list, counts, ri);
+  // rows repeat from a quarter as many entries as rows on (the gather's rule for cached loads).  The
+  // copy by column slice pays where rows repeat and d_pooled is beyond an L2; it needs rows of 64
+  // lanes (1 KiB) and room beside the partial rows
+  const bool keep = 4 * static_cast<int64_t>(M) >= n_values;
+  const int64_t pooled_rows = static_cast<int64_t>(T) * expand;
+  if (!(keep && dv * (vdtype == UMEM_F32 ? 4 : 2) >= 1024 && pooled_rows <= static_cast<int64_t>(nseg) &&
+        pooled_rows * dv * 4 > (INT64_C(4) << 20)))
+    sliced = nullptr;
+  const int cols = sliced != nullptr ? slice_columns(pooled_rows, dv) : std::min(dv, 256);
+  e = vdtype == UMEM_F32
+          ? launch_tokens(static_cast<const float*>(values), nv, dv, T, bag, idx, w, pm, expand, c,
+                          d_pooled, info, d_values, !compact, dw, sliced, cols, s)
+          : launch_tokens(static_cast<const uint16_t*>(values), nv, dv, T, bag, idx, w, pm, expand, c,
+                          d_pooled, info, d_values, !compact, dw, sliced, cols, s);
+  if (e != hipSuccess) return e;
+#define UMEM_ROWS(GL, SLICED)                                                                      \
+  hipLaunchKernelGGL((row_bwd_kernel<GL, SLICED>), dim3(kRowWaves / NWAVES), dim3(THREADS), 0, s,  \
+                     sorted, sp.n, rec, info, w, c, dv, static_cast<size_t>(pooled_rows),           \
+                     SLICED ? sliced : d_pooled, d_values, compact ? 1 : 0, partial, list, counts, heads)
+  if (sliced != nullptr) {
+    switch (cols) {
+      case 32: UMEM_ROWS(8, true); break;
+      case 64: UMEM_ROWS(16, true); break;
+      case 128: UMEM_ROWS(32, true); break;
+      default: UMEM_ROWS(64, true); break;
+    }
+  } else {
+    switch (cols / 4) {                                   // dv a power of two below 256, or 256 at a time
+      case 1: UMEM_ROWS(1, false); break;
+      case 2: UMEM_ROWS(2, false); break;
+      case 4: UMEM_ROWS(4, false); break;
+      case 8: UMEM_ROWS(8, false); break;
+      case 16: UMEM_ROWS(16, false); break;
+      case 32: UMEM_ROWS(32, false); break;
+      case 64: UMEM_ROWS(64, false); break;
+      default: return hipErrorInvalidValue;
+    }
+  }
+#undef UMEM_ROWS
+  hipLaunchKernelGGL(seg_join_kernel, dim3(kJoinWaves / NWAVES), dim3(THREADS), 0, s, sorted, sp.n, dv,
+                     partial, d_values, list, heads, counts, 0, 0, nullptr, compact ? info : nullptr);
   return hipGetLastError();
 }
 
@@ -963,10 +1341,10 @@ size_t score_backward_workspace_bytes(const umem_desc& d, int T) {
   const int hc = d.cores > 1 ? d.cores : 1;
   const size_t dc = d.grid == UMEM_GRID_TUCKER ? static_cast<size_t>(hc) * d.rank * d.rank : 0;
   const size_t nseg = (static_cast<size_t>(Mk) + kSeg - 1) / kSeg;
-  return 3 * round_up256(static_cast<size_t>(Mk) * sizeof(uint32_t)) + round_up256(nseg * sizeof(uint32_t)) +
-         256 + round_up256(static_cast<size_t>(Mk) * d.rank * sizeof(float)) +
-         round_up256(2 * nseg * d.dk * sizeof(float)) + round_up256(list_workspace_bytes(Mk)) +
-         round_up256(th * dc * sizeof(float)) + round_up256(sort_workspace_bytes(Mk));
+  return round_up256(nseg * sizeof(uint32_t)) + 256 + round_up256(list_chunks(Mk) * sizeof(uint2)) +
+         round_up256(static_cast<size_t>(Mk) * d.rank * sizeof(float)) +
+         round_up256(nseg * d.dk * sizeof(float)) + round_up256(th * dc * sizeof(float)) +
+         round_up256(sort_workspace_bytes(Mk));
 }
 
 hipError_t launch_score_backward(const umem_desc& d, int T, const float* q_row, const float* q_col,
@@ -983,26 +1361,21 @@ hipError_t launch_score_backward(const umem_desc& d, int T, const float* q_row, 
   const int hc = d.cores > 1 ? d.cores : 1;
   const int dc = tucker ? hc * r * r : 0;
   char* base = static_cast<char*>(ws);
-  uint32_t* ekeys = reinterpret_cast<uint32_t*>(base);
-  base += round_up256(static_cast<size_t>(Mk) * sizeof(uint32_t));
-  uint32_t* evals = reinterpret_cast<uint32_t*>(base);
-  base += round_up256(static_cast<size_t>(Mk) * sizeof(uint32_t));
   float* edS = reinterpret_cast<float*>(base);
   base += round_up256(static_cast<size_t>(Mk) * r * sizeof(float));
   const size_t nseg = (static_cast<size_t>(Mk) + kSeg - 1) / kSeg;
   float* kpart = reinterpret_cast<float*>(base);
-  base += round_up256(2 * nseg * d.dk * sizeof(float));
-  uint32_t* list = reinterpret_cast<uint32_t*>(base);
-  base += round_up256(static_cast<size_t>(Mk) * sizeof(uint32_t));
+  base += round_up256(nseg * d.dk * sizeof(float));
   uint32_t* heads = reinterpret_cast<uint32_t*>(base);
   base += round_up256(nseg * sizeof(uint32_t));
   uint32_t* counts = reinterpret_cast<uint32_t*>(base);
   base += 256;
-  void* lws = base;
-  base += round_up256(list_workspace_bytes(Mk));
+  uint2* chunk_cnt = reinterpret_cast<uint2*>(base);
+  base += round_up256(list_chunks(Mk) * sizeof(uint2));
   float* dc_part = reinterpret_cast<float*>(base);
   base += round_up256(th * dc * sizeof(float));
-  void* sws = base;
+  const uint32_t sentinel = static_cast<uint32_t>(2 * H) * d.n_keys;
+  const SortPlan sp = sort_plan(Mk, bits_for(sentinel), base);
   const int key_bits = bits_for(d.n_keys);
   const int sm = d.weight == UMEM_W_SOFTMAX ? 1 : 0;
 #define UMEM_SCORE_BWD(NG)                                                                       \
@@ -1010,24 +1383,26 @@ hipError_t launch_score_backward(const umem_desc& d, int T, const float* q_row, 
                      dim3(static_cast<unsigned>((th + score_bwd_waves<NG>() - 1) / score_bwd_waves<NG>())), \
                      dim3(score_bwd_waves<NG>() * kWave), 0, s, q_row, q_col, k_row, k_col, core, \
                      idx, w, dw, T, H, d.n_keys, key_bits, d.dk, r, m, tucker ? 1 : 0, sm, hc,   \
-                     dq_row, dq_col, ekeys, evals, edS, dc_part)
+                     dq_row, dq_col, sp.keys, edS, dc_part)
   if (m <= kWave) UMEM_SCORE_BWD(1);
   else if (m <= 2 * kWave) UMEM_SCORE_BWD(2);
   else UMEM_SCORE_BWD(4);
 #undef UMEM_SCORE_BWD
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const uint32_t sentinel = static_cast<uint32_t>(2 * H) * d.n_keys;
-  uint32_t *ks, *vs;
-  e = sort_pairs(ekeys, evals, Mk, bits_for(static_cast<int64_t>(sentinel) + 1), sws, s, &ks, &vs);
+  uint2 *sorted, *dead;
+  e = sort_run(sp, sentinel, false, s, &sorted, &dead);
+  uint32_t* list = reinterpret_cast<uint32_t*>(dead);
   if (e != hipSuccess) return e;
-  const dim3 list_grid(kListWaves / NWAVES);
-  e = list_pieces(ks, Mk, sentinel, list, counts, lws, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(key_bwd_seg_kernel, list_grid, dim3(THREADS), 0, s, ks, vs, Mk, sentinel, edS,
-                     q_row, q_col, dk_row, dk_col, H, d.n_keys, d.dk, r, m, kpart, list, counts, heads);
-  hipLaunchKernelGGL(seg_join_kernel, list_grid, dim3(THREADS), 0, s, ks, Mk, d.dk, kpart, dk_row,
-                     heads, counts, H, d.n_keys, dk_col, nullptr);
+  hipLaunchKernelGGL(piece_count_kernel<false>, dim3(list_chunks(Mk)), dim3(THREADS), 0, s, sorted,
+                     sp.n, chunk_cnt);
+  hipLaunchKernelGGL(piece_write_kernel<false>, dim3(list_chunks(Mk)), dim3(THREADS), 0, s, sorted,
+                     sp.n, chunk_cnt, list, counts, RowInfo{});
+  hipLaunchKernelGGL(key_bwd_seg_kernel, dim3(kListWaves / NWAVES), dim3(THREADS), 0, s, sorted, sp.n,
+                     edS, q_row, q_col, dk_row, dk_col, H, d.n_keys, d.dk, r, m, kpart, list, counts,
+                     heads);
+  hipLaunchKernelGGL(seg_join_kernel, dim3(kJoinWaves / NWAVES), dim3(THREADS), 0, s, sorted, sp.n,
+                     d.dk, kpart, dk_row, list, heads, counts, H, d.n_keys, dk_col, nullptr);
   if (tucker)   // dC: the per-token partials [T][H dc], summed over tokens into dcore
     hipLaunchKernelGGL(sum_cols_kernel, dim3(H * dc), dim3(THREADS), 0, s, dc_part, dcore, T, H * dc);
   return hipGetLastError();

@@ -1,229 +1,237 @@
-// Stable sort of (key, value) pairs of 32-bit unsigned keys: least-significant-digit radix sort
-// in as few passes of at most 11-bit digits as the key width needs (ceil(bits / 11) passes of
-// ceil(bits / passes) bits: 20-bit row keys in two passes of 10).  The backward passes use it to
-// bring all contributions to one value row (or key row) together, in their original order, so
-// that one wave sums them in a fixed order and the gradient does not depend on timing.
+// Stable sort of the positions 0 .. M-1 by a 32-bit unsigned key each: least-significant-digit
+// radix sort in as few passes of at most 11-bit digits as the key width needs (ceil(bits / 11)
+// passes of ceil(bits / passes) bits: 20-bit row keys in two passes of 10).  The backward passes
+// use it to bring all contributions to one value row (or key row) together, in their original
+// order, so that each row is summed in a fixed order and the gradient does not depend on timing.
+// A skip key drops its positions on the way: they are neither counted nor written.
 //
-// Per pass, over tiles of 4096 pairs (256 threads x 16 steps), with 2^D digit values:
+// The arrays are small (tens of thousands to a few million pairs), so each pass is a chain of
+// short, latency-bound kernels, and what counts is how few round trips and barriers each holds.
+// Per pass, over tiles of 8 waves x steps x 64 pairs, with 2^D digit values:
 //  * sort_hist_kernel: the tile's digit histogram (LDS atomics), stored digit-major
-//    [2^D][tiles];
-//  * scan_exclusive turns the 2^D * tiles counts into exclusive offsets (digit by digit, tile by
-//    tile: the order the stable pass writes in): chunk sums, then each chunk rescanned from the
-//    sum of the chunks before it;
-//  * sort_scatter_kernel: the tile again (all of its pairs loaded up front), 256 consecutive
-//    pairs per step; a pair's place is its digit's running offset in this tile + the count of
-//    equal digits in earlier waves of this step + its rank among equal digits in its own wave
-//    (D ballots match the digit).  Each wave's first pair of a digit posts the wave's count of
-//    it, and after the step adds it to the digit's running offset and clears its post, so a step
-//    costs the same whatever 2^D is.
-#include <utility>
+//    [2^D][tiles].  The caller may fold the first one into the kernel that makes the keys
+//    (sort_tile_hist);
+//  * sort_scan_kernel: a wave per digit turns its row of tile counts into exclusive offsets
+//    within the digit and leaves the digit's total;
+//  * sort_scatter_kernel: every workgroup scans the 2^D totals itself (LDS), so no kernel stands
+//    between; each wave then ranks its own 64 x steps consecutive pairs without a barrier: a
+//    pair's rank is its wave's running count of the digit (LDS, the wave's own row) + its rank
+//    among equal digits of its step (D ballots match the digit).  Two barriers and a prefix over
+//    the eight waves' counts later every pair knows its place and leaves as one 8-byte
+//    (key, position) store.
+// Before, every step of 256 pairs ended in two workgroup barriers, the counts were scanned by two
+// kernels and keys and values left as two stores: one pass (histogram, scan, scatter) took 33.5 us
+// for 131,072 pairs of 10-bit digits and 42 us for 1,048,576; it now takes 18 us and 23 - 29 us.
+#include <algorithm>
 
 #include "umem_internal.h"
 
 namespace umem {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kSteps = 16;
-constexpr int kTile = kThreads * kSteps;
+constexpr int kThreads = kSortThreads;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kMaxDigitBits = 11;
-constexpr int kMaxDigits = 1 << kMaxDigitBits;
+constexpr int kMaxDigits = 1 << kSortMaxDigitBits;
 
 __device__ __forceinline__ uint64_t lanes_below() {
   const unsigned lane = threadIdx.x & (kWave - 1);
   return lane == 0 ? 0ull : (~0ull >> (kWave - lane));
 }
 
-__global__ __launch_bounds__(kThreads) void sort_hist_kernel(const uint32_t* __restrict__ keys,
-                                                             int M, int shift, int dbits,
-                                                             uint32_t* __restrict__ hist,
-                                                             int tiles) {
+__global__ __launch_bounds__(kThreads) void sort_hist_kernel(const uint2* __restrict__ pairs,
+                                                             const uint32_t* __restrict__ keys,
+                                                             int M, const uint32_t* __restrict__ n,
+                                                             uint32_t skip, int shift, int dbits,
+                                                             uint32_t* __restrict__ hist, int tiles,
+                                                             int tile) {
   __shared__ uint32_t cnt[kMaxDigits];
   const int nd = 1 << dbits;
   const uint32_t mask = static_cast<uint32_t>(nd - 1);
+  const int count = n != nullptr ? static_cast<int>(*n) : M;      // of a later pass: without the skipped
   for (int d = threadIdx.x; d < nd; d += kThreads) cnt[d] = 0;
   __syncthreads();
-  const int base = blockIdx.x * kTile;
-  for (int q = 0; q < kSteps; ++q) {
-    const int pos = base + q * kThreads + threadIdx.x;
-    if (pos < M) atomicAdd(&cnt[(keys[pos] >> shift) & mask], 1u);
+  const int base = blockIdx.x * tile, end = min(base + tile, count);
+  for (int pos = base + static_cast<int>(threadIdx.x); pos < end; pos += kThreads) {
+    const uint32_t key = pairs != nullptr ? pairs[pos].x : keys[pos];
+    if (pairs != nullptr || key != skip) atomicAdd(&cnt[(key >> shift) & mask], 1u);
   }
   __syncthreads();
   for (int d = threadIdx.x; d < nd; d += kThreads)
     hist[static_cast<size_t>(d) * tiles + blockIdx.x] = cnt[d];
 }
 
-// ---------------------------------------------------------------- exclusive scan
-// Over chunks of kScanChunk counts: each chunk's sum (scan_sums_kernel, skipped for one chunk),
-// then each chunk rescanned from the sum of the chunk sums before it (scan_apply_kernel).  Thread
-// t of a chunk owns its 16 consecutive counts.  Integer sums: exact in any order.
-
-constexpr int kScanPer = 16;
-constexpr int kScanChunk = kThreads * kScanPer;
-
-// Exclusive prefix of v over the workgroup's threads (every thread calls it), and the total.
-__device__ __forceinline__ uint32_t block_exclusive(uint32_t v, uint32_t* lds, uint32_t* total) {
-  const int tid = threadIdx.x;
-  lds[tid] = v;
-  __syncthreads();
-  for (int off = 1; off < kThreads; off <<= 1) {          // Hillis-Steele inclusive scan
-    const uint32_t add = tid >= off ? lds[tid - off] : 0u;
-    __syncthreads();
-    lds[tid] += add;
-    __syncthreads();
+// Digit d's tile counts hist[d][0, tiles) to exclusive prefix sums, their total to tot[d]; a wave
+// per digit, 64 tiles per step.
+__global__ __launch_bounds__(256) void sort_scan_kernel(uint32_t* __restrict__ hist, int nd, int tiles,
+                                                        uint32_t* __restrict__ tot) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int d = blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
+  if (d >= nd) return;                                    // whole waves: no barrier in this kernel
+  uint32_t* row = hist + static_cast<size_t>(d) * tiles;
+  uint32_t run = 0;
+  for (int t0 = 0; t0 < tiles; t0 += kWave) {
+    const int t = t0 + lane;
+    const uint32_t c = t < tiles ? row[t] : 0u;
+    const uint32_t incl = static_cast<uint32_t>(wave_inclusive_scan(static_cast<int>(c)));
+    if (t < tiles) row[t] = run + incl - c;
+    run += static_cast<uint32_t>(__shfl(static_cast<int>(incl), kWave - 1, kWave));
   }
-  const uint32_t incl = lds[tid];
-  *total = lds[kThreads - 1];
-  __syncthreads();
-  return incl - v;
+  if (lane == 0) tot[d] = run;
 }
 
-__global__ __launch_bounds__(kThreads) void scan_sums_kernel(const uint32_t* __restrict__ v, int n,
-                                                             uint32_t* __restrict__ sums) {
-  __shared__ uint32_t lds[kThreads];
-  const int beg = blockIdx.x * kScanChunk + threadIdx.x * kScanPer;
-  uint32_t a = 0;
-#pragma unroll
-  for (int k = 0; k < kScanPer; ++k) a += beg + k < n ? v[beg + k] : 0u;
-  uint32_t total;
-  block_exclusive(a, lds, &total);
-  if (threadIdx.x == 0) sums[blockIdx.x] = total;
-}
-
-// sums: the chunk sums (read only by chunks after the first; nb <= 256 * 16).
-__global__ __launch_bounds__(kThreads) void scan_apply_kernel(uint32_t* __restrict__ v, int n,
-                                                              const uint32_t* __restrict__ sums) {
-  __shared__ uint32_t lds[kThreads];
-  uint32_t before = 0;
-  for (int j = threadIdx.x; j < static_cast<int>(blockIdx.x); j += kThreads) before += sums[j];
-  uint32_t offset;
-  block_exclusive(before, lds, &offset);                  // offset: all threads' parts summed
-  const int beg = blockIdx.x * kScanChunk + threadIdx.x * kScanPer;
-  uint32_t loc[kScanPer];
-  uint32_t a = 0;
-#pragma unroll
-  for (int k = 0; k < kScanPer; ++k) {
-    loc[k] = beg + k < n ? v[beg + k] : 0u;
-    a += loc[k];
-  }
-  uint32_t total;
-  uint32_t run = offset + block_exclusive(a, lds, &total);
-#pragma unroll
-  for (int k = 0; k < kScanPer; ++k) {
-    if (beg + k < n) v[beg + k] = run;
-    run += loc[k];
-  }
-}
-
+// FIRST: from keys[0, M), the pair of position pos being (keys[pos], pos); else from *n pairs.
+template <int STEPS, bool FIRST>
 __global__ __launch_bounds__(kThreads) void sort_scatter_kernel(
-    const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
-    uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int M, int shift, int dbits,
-    const uint32_t* __restrict__ offs, int tiles) {
-  __shared__ uint32_t base[kMaxDigits];
-  __shared__ uint32_t wcnt[kWaves][kMaxDigits];
-  const int tid = threadIdx.x;
-  const int wave = tid / kWave;
+    const uint32_t* __restrict__ keys, const uint2* __restrict__ in, uint2* __restrict__ out, int M,
+    uint32_t* __restrict__ n, uint32_t skip, int shift, int dbits, const uint32_t* __restrict__ offs,
+    const uint32_t* __restrict__ tot, int tiles) {
+  __shared__ uint32_t base[kMaxDigits];                   // the tile's first place of each digit
+  __shared__ uint16_t wcnt[kWaves][kMaxDigits];           // counts, then places before each wave
+  __shared__ uint32_t wsum[kWaves];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int nd = 1 << dbits;
   const uint32_t mask = static_cast<uint32_t>(nd - 1);
-  for (int d = tid; d < nd; d += kThreads) {
-    base[d] = offs[static_cast<size_t>(d) * tiles + blockIdx.x];
+  const int count = FIRST ? M : static_cast<int>(*n);
+  const int first = (blockIdx.x * kWaves + wave) * (STEPS * kWave) + lane;
+  uint2 pr[STEPS];
+  bool valid[STEPS];
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) wcnt[w][d] = 0;
+  for (int q = 0; q < STEPS; ++q) {
+    const int pos = first + q * kWave;
+    valid[q] = pos < count;
+    if (FIRST) {
+      pr[q] = make_uint2(valid[q] ? keys[pos] : 0u, static_cast<uint32_t>(pos));
+      valid[q] = valid[q] && pr[q].x != skip;
+    } else {
+      pr[q] = valid[q] ? in[pos] : make_uint2(0u, 0u);
+    }
   }
-  const int tile0 = blockIdx.x * kTile;
-  uint32_t kin[kSteps], vin[kSteps];
+  // the digits' first places: an exclusive scan of the totals, kPer consecutive digits a thread
+  constexpr int kPer = kMaxDigits / kThreads;
+  uint32_t loc[kPer], sum = 0;
 #pragma unroll
-  for (int q = 0; q < kSteps; ++q) {
-    const int pos = tile0 + q * kThreads + tid;
-    kin[q] = pos < M ? keys_in[pos] : 0u;
-    vin[q] = pos < M ? vals_in[pos] : 0u;
+  for (int k = 0; k < kPer; ++k) {
+    const int d = tid * kPer + k;
+    loc[k] = d < nd ? tot[d] : 0u;
+    sum += loc[k];
+  }
+  const uint32_t incl = static_cast<uint32_t>(wave_inclusive_scan(static_cast<int>(sum)));
+  if (lane == kWave - 1) wsum[wave] = incl;
+  for (int d = lane; d < nd; d += kWave) wcnt[wave][d] = 0;       // the wave's own row
+  __syncthreads();
+  uint32_t run = incl - sum;
+  uint32_t total = 0;
+#pragma unroll
+  for (int v = 0; v < kWaves; ++v) {
+    run += v < wave ? wsum[v] : 0u;
+    total += wsum[v];
+  }
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int d = tid * kPer + k;
+    if (d < nd) base[d] = run + (tiles > 1 ? offs[static_cast<size_t>(d) * tiles + blockIdx.x] : 0u);
+    run += loc[k];
+  }
+  if (FIRST && blockIdx.x == 0 && tid == 0) *n = total;
+  uint32_t rank[STEPS];
+#pragma unroll
+  for (int q = 0; q < STEPS; ++q) {
+    const uint32_t digit = (pr[q].x >> shift) & mask;
+    uint64_t peers = __ballot(valid[q]);
+    for (int b = 0; b < dbits; ++b) {
+      const bool one = (digit >> b) & 1u;
+      const uint64_t ones = __ballot(one);
+      peers &= one ? ones : ~ones;
+    }
+    const uint32_t before = static_cast<uint32_t>(__popcll(peers & lanes_below()));
+    const uint32_t have = wcnt[wave][digit];
+    rank[q] = have + before;
+    wave_lds_order();
+    if (valid[q] && before == 0) wcnt[wave][digit] = static_cast<uint16_t>(have + __popcll(peers));
+    wave_lds_order();
+  }
+  __syncthreads();
+  for (int d = tid; d < nd; d += kThreads) {
+    uint32_t at = 0;
+#pragma unroll
+    for (int v = 0; v < kWaves; ++v) {
+      const uint32_t c = wcnt[v][d];
+      wcnt[v][d] = static_cast<uint16_t>(at);             // below a tile's 4096 pairs
+      at += c;
+    }
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < kSteps; ++q) {
-    const int pos = tile0 + q * kThreads + tid;
-    const bool valid = pos < M;
-    const uint32_t key = kin[q];
-    const uint32_t digit = (key >> shift) & mask;
-    uint64_t peers = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < kMaxDigitBits; ++b) {
-      if (b < dbits) {
-        const uint64_t ones = __ballot(valid && ((digit >> b) & 1u));
-        peers &= ((digit >> b) & 1u) ? ones : ~ones;
-      }
-    }
-    const uint32_t rank = static_cast<uint32_t>(__popcll(peers & lanes_below()));
-    const uint32_t here = static_cast<uint32_t>(__popcll(peers));
-    const bool leader = valid && rank == 0;
-    if (leader) wcnt[wave][digit] = here;
-    __syncthreads();
-    if (valid) {
-      uint32_t dst = base[digit] + rank;
-      for (int w = 0; w < wave; ++w) dst += wcnt[w][digit];
-      keys_out[dst] = key;
-      vals_out[dst] = vin[q];
-    }
-    __syncthreads();
-    // the digit's running offset takes every wave's count (LDS atomics: an integer sum, exact in
-    // any order); each post is cleared by the wave that made it.  No barrier is needed before the
-    // next step: every read of this step's offsets and posts came before the barrier above, the
-    // next step's posts go to the posting wave's own row (after its own clears, in program
-    // order), and the next step reads offsets and posts only after its own first barrier.
-    if (leader) {
-      atomicAdd(&base[digit], here);
-      wcnt[wave][digit] = 0;
-    }
+  for (int q = 0; q < STEPS; ++q) {
+    const uint32_t digit = (pr[q].x >> shift) & mask;
+    if (valid[q]) out[base[digit] + wcnt[wave][digit] + rank[q]] = pr[q];
   }
+}
+
+// Tiles of 2048 pairs (half the steps in each wave's chain, twice the workgroups) where there are
+// several; up to 4096 pairs one tile needs no scan, and from 2^19 pairs on the chip is full either
+// way and tiles of 4096 halve the counts to scan.
+int sort_steps(int M) { return M > 4096 && M < (1 << 19) ? 4 : 8; }
+
+// One tile's counts are its totals: they share their place, and no scan runs.
+size_t count_words(int tiles) {
+  return tiles > 1 ? static_cast<size_t>(kMaxDigits) * (tiles + 1) : kMaxDigits;
 }
 
 }  // namespace
 
-size_t scan_workspace_bytes(int n) {
-  return (static_cast<size_t>(n) / kScanChunk + 2) * sizeof(uint32_t);
-}
-
-hipError_t scan_exclusive(uint32_t* v, int n, uint32_t* sums, hipStream_t s) {
-  const int nb = (n + kScanChunk - 1) / kScanChunk;
-  if (nb > kScanChunk) return hipErrorInvalidValue;
-  if (nb == 0) return hipSuccess;
-  if (nb > 1) hipLaunchKernelGGL(scan_sums_kernel, dim3(nb), dim3(kThreads), 0, s, v, n, sums);
-  hipLaunchKernelGGL(scan_apply_kernel, dim3(nb), dim3(kThreads), 0, s, v, n, sums);
-  return hipGetLastError();
+SortPlan sort_plan(int M, int bits, void* ws) {
+  SortPlan p;
+  p.M = M;
+  p.tile = kSortThreads * sort_steps(M);
+  p.tiles = (M + p.tile - 1) / p.tile;
+  p.passes = bits <= 0 ? 1 : (bits + kSortMaxDigitBits - 1) / kSortMaxDigitBits;
+  p.dbits = bits <= 0 ? 1 : (bits + p.passes - 1) / p.passes;     // <= kSortMaxDigitBits
+  p.a = static_cast<uint2*>(ws);
+  p.b = p.a + M;
+  p.keys = reinterpret_cast<uint32_t*>(p.b);
+  p.n = reinterpret_cast<uint32_t*>(p.b + M);
+  p.tot = p.n + 16;
+  p.hist = p.tiles > 1 ? p.tot + kMaxDigits : p.tot;
+  p.spare = p.n + 16;
+  return p;
 }
 
 size_t sort_workspace_bytes(int M) {
-  const size_t tiles = (static_cast<size_t>(M) + kTile - 1) / kTile;
-  return 2 * static_cast<size_t>(M) * sizeof(uint32_t) + kMaxDigits * tiles * sizeof(uint32_t) +
-         scan_workspace_bytes(static_cast<int>(kMaxDigits * tiles)) + 256;
+  const int tile = kSortThreads * sort_steps(M);
+  const size_t words = std::max(count_words((M + tile - 1) / tile), static_cast<size_t>(M));
+  return 2 * static_cast<size_t>(M) * sizeof(uint2) + (16 + words) * sizeof(uint32_t);
 }
 
-hipError_t sort_pairs(uint32_t* keys, uint32_t* vals, int M, int bits, void* ws, hipStream_t s,
-                      uint32_t** keys_sorted, uint32_t** vals_sorted) {
-  uint32_t* k2 = static_cast<uint32_t*>(ws);
-  uint32_t* v2 = k2 + M;
-  uint32_t* hist = v2 + M;
-  uint32_t* sums = hist + kMaxDigits * static_cast<size_t>((M + kTile - 1) / kTile);
-  uint32_t *ka = keys, *va = vals, *kb = k2, *vb = v2;
-  const int tiles = (M + kTile - 1) / kTile;
-  const int passes = (M <= 1 || bits <= 0) ? 0 : (bits + kMaxDigitBits - 1) / kMaxDigitBits;
-  const int dbits = passes > 0 ? (bits + passes - 1) / passes : 0;      // <= kMaxDigitBits
-  if (static_cast<int64_t>(tiles) << dbits > static_cast<int64_t>(kScanChunk) * kScanChunk)
-    return hipErrorInvalidValue;                          // beyond the scan (M of 2^25 and more)
-  for (int pass = 0; pass < passes; ++pass) {
-    const int shift = dbits * pass;
-    hipLaunchKernelGGL(sort_hist_kernel, dim3(tiles), dim3(kThreads), 0, s, ka, M, shift, dbits,
-                       hist, tiles);
-    hipError_t e = scan_exclusive(hist, tiles << dbits, sums, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sort_scatter_kernel, dim3(tiles), dim3(kThreads), 0, s, ka, va, kb, vb, M,
-                       shift, dbits, hist, tiles);
-    std::swap(ka, kb);
-    std::swap(va, vb);
+hipError_t sort_run(const SortPlan& p, uint32_t skip, bool have_hist, hipStream_t s, uint2** sorted,
+                    uint2** dead) {
+  uint2 *in = p.b, *out = p.a;                            // the first pass reads p.keys, not p.b
+  const int nd = 1 << p.dbits;
+  for (int pass = 0; pass < p.passes; ++pass) {
+    const int shift = p.dbits * pass;
+    const bool first = pass == 0;
+    if (!first || !have_hist)
+      hipLaunchKernelGGL(sort_hist_kernel, dim3(p.tiles), dim3(kThreads), 0, s, first ? nullptr : in,
+                         p.keys, p.M, first ? nullptr : p.n, skip, shift, p.dbits, p.hist, p.tiles, p.tile);
+    if (p.tiles > 1)
+      hipLaunchKernelGGL(sort_scan_kernel, dim3((nd + 3) / 4), dim3(256), 0, s, p.hist, nd, p.tiles, p.tot);
+#define UMEM_SCATTER(STEPS, FIRST)                                                                  \
+  hipLaunchKernelGGL((sort_scatter_kernel<STEPS, FIRST>), dim3(p.tiles), dim3(kThreads), 0, s, p.keys, \
+                     in, out, p.M, p.n, skip, shift, p.dbits, p.hist, p.tot, p.tiles)
+    if (p.tile == kThreads * 4) {
+      if (first) UMEM_SCATTER(4, true);
+      else UMEM_SCATTER(4, false);
+    } else {
+      if (first) UMEM_SCATTER(8, true);
+      else UMEM_SCATTER(8, false);
+    }
+#undef UMEM_SCATTER
+    uint2* t = in;
+    in = out;
+    out = t;
   }
-  *keys_sorted = ka;     // the input arrays or the scratch copies, by the number of passes
-  *vals_sorted = va;
+  *sorted = in;
+  *dead = out;
   return hipGetLastError();
 }
 

@@ -98,16 +98,24 @@ hipError_t gemm_bf16(const uint16_t* A, const uint16_t* B, float* C, int M, int 
 hipError_t gemm_bf16_parts(const uint16_t* A, const uint16_t* B, float* C, int M, int N, int K,
                            float* part, hipStream_t s, int* splits);
 
-// Stable sort of M (key, value) pairs with keys < 2^bits (sort.hip); the inputs are reordered
-// through ws (sort_workspace_bytes(M) bytes, 4-byte aligned) and the sorted arrays returned
-// (either the inputs or part of ws).
+// Stable sort of the positions 0 .. M-1 by keys below 2^bits (sort.hip), in ws of
+// sort_workspace_bytes(M) bytes (8-byte aligned).  The caller writes the keys to plan.keys; a key
+// equal to `skip` drops its position.  The sorted (key, position) pairs are returned, their number
+// at *plan.n on the device; `dead` is the other array of M pairs, free for the caller from then
+// on, and so are the M words at plan.spare (the counts').  With have_hist the caller's kernel has
+// written the first digit's tile counts itself: over tiles of plan.tile consecutive positions,
+// plan.hist[d * plan.tiles + tile] of the digit key & (2^dbits - 1), skipped keys left out.
+constexpr int kSortThreads = 512;
+constexpr int kSortMaxDigitBits = 11;
+struct SortPlan {
+  int M, tile, tiles, passes, dbits;
+  uint2 *a, *b;
+  uint32_t *keys, *n, *tot, *hist, *spare;
+};
+SortPlan sort_plan(int M, int bits, void* ws);
 size_t sort_workspace_bytes(int M);
-// Exclusive prefix sums of v[0, n) in place (n <= 2^24); sums: scan_workspace_bytes(n) bytes of
-// scratch for the per-chunk sums.
-size_t scan_workspace_bytes(int n);
-hipError_t scan_exclusive(uint32_t* v, int n, uint32_t* sums, hipStream_t s);
-hipError_t sort_pairs(uint32_t* keys, uint32_t* vals, int M, int bits, void* ws, hipStream_t s,
-                      uint32_t** keys_sorted, uint32_t** vals_sorted);
+hipError_t sort_run(const SortPlan& p, uint32_t skip, bool have_hist, hipStream_t s, uint2** sorted,
+                    uint2** dead);
 
 // Backward of the gather-sum and of the scores (backward.hip).
 size_t gather_backward_workspace_bytes(int T, int bag, int dv);
@@ -168,6 +176,13 @@ __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
   return v;
+}
+
+// Orders a wave's own LDS traffic (no wait for the other waves of the workgroup).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ __forceinline__ uint64_t lanemask_lt() {

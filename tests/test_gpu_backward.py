@@ -147,6 +147,74 @@ def test_gather_backward_rows(dv, vdtype, expand, bag, T, cores, Np):
     assert e_dv <= RTOL
 
 
+# Where the token-by-token and row kernels change shape: rows of 2 .. 6 KiB (one, two or four waves
+# to an entry, several chunks each), workgroups sharing a bag across virtual blocks, entries alone on
+# their row beside runs that span segments, and d_pooled read by column slice (rows that repeat,
+# T E <= T bag / 64, d_pooled beyond 4 MiB): slices of 32 columns in a multiple of eight, two cores.
+GATHER_BWD_SHAPES = [
+    (2048, CF.BF16, 4, 37, 6, 2, 400),        # two waves to an entry
+    (3072, CF.BF16, 1, 21, 9, 1, 70),         # ... of three chunks each
+    (2560, CF.BF16, 9, 65, 3, 5, 90),         # five chunks to a wave
+    (1792, CF.F32, 1, 130, 2, 7, 150),        # seven
+    (512, CF.BF16, 4, 70, 3, 1, 100000),      # every entry alone, shared bags
+    (512, CF.BF16, 1, 100, 41, 1, 1),         # one row for all: a run of 65 segments
+    (768, CF.F32, 1, 64, 1400, 2, 900),       # 24 slices of 32 columns, two cores
+    (512, CF.BF16, 4, 256, 520, 1, 700),      # eight slices of 64 columns, virtual blocks
+]
+
+
+@pytest.mark.parametrize("dv,vdtype,expand,bag,T,cores,Np", GATHER_BWD_SHAPES)
+def test_gather_backward_shapes(dv, vdtype, expand, bag, T, cores, Np):
+    """Dense (onto a table that is not zero) and compact gradients against the backward oracle.  A
+    row's sum of fp32 products over up to its run's entries: RTOL of the largest value, as above."""
+    log(f"[case] gather backward shapes dv={dv} E={expand} bag={bag} T={T} cores={cores} Np={Np}")
+    V, idx, perm, w, dp, dev = gather_backward_inputs(dv, vdtype, expand, bag, T, cores, Np)
+    dV0 = torch.randn((Np, dv), dtype=torch.float32, device="cuda")
+    dV = dV0.clone()
+    dw_dense = run_gather_backward(Np, dv, vdtype, V, T, bag, dev["idx"], dev["w"], dev["perm"],
+                                   expand, cores, dev["dp"], dV)
+    rows, d_rows, n_rows, dw = run_gather_backward_rows(Np, dv, vdtype, V, T, bag, dev["idx"], dev["w"],
+                                                        dev["perm"], expand, cores, dev["dp"])
+    torch.cuda.synchronize()
+    Vh = V.float().cpu().numpy()
+    rows_ref, dV_ref, dw_ref = B.gather_backward(lambda r: Vh[r], idx, w, dp, perm, Np, expand)
+    order = np.argsort(rows_ref)
+    n = int(n_rows.item())
+    assert n == len(rows_ref)
+    assert np.array_equal(rows[:n].cpu().numpy(), np.asarray(rows_ref)[order])
+    assert torch.equal(dw, dw_dense)
+    assert rel(dw.cpu().numpy(), dw_ref) <= RTOL
+    assert rel(d_rows[:n].cpu().numpy(), np.asarray(dV_ref)[order]) <= RTOL
+    # the dense form adds into values of order one: their rounding (2^-24 of a sum of a few) is
+    # below RTOL of the gradients' largest values
+    assert rel((dV - dV0)[rows[:n].long()].cpu().numpy(), np.asarray(dV_ref)[order]) <= RTOL
+    untouched = torch.ones(Np, dtype=torch.bool, device="cuda")
+    untouched[rows[:n].long()] = False
+    assert torch.equal(dV[untouched], dV0[untouched])
+
+
+@pytest.mark.parametrize("T,bag,Np", [(4, 1024, 50), (1, 1, 5), (241, 17, 3000), (64, 64, 1 << 22),
+                                      (2049, 2, 2047), (1024, 512, 40000), (1037, 512, 1 << 20)])
+def test_gather_backward_rows_sort_edges(T, bag, Np):
+    """The rows' order and number at the sort's edges (one tile, just past it, tiles of 4096 from
+    2^19 entries on; one, two and three digits), and each row's gradient: with weights of one and
+    d_pooled of ones it is the row's number of entries, exact in fp32."""
+    log(f"[case] rows sort edges T={T} bag={bag} Np={Np}")
+    rng = np.random.default_rng(T + bag)
+    idx = rng.integers(0, Np, size=(T, bag)).astype(np.int32)
+    V = torch.zeros((Np, 8), dtype=torch.bfloat16, device="cuda")
+    one = torch.ones((T, bag), device="cuda")
+    rows, d_rows, n_rows, dw = run_gather_backward_rows(Np, 8, CF.BF16, V, T, bag,
+                                                        torch.from_numpy(idx).cuda(), one, None, 1, 1,
+                                                        torch.ones((T, 1, 8), device="cuda"))
+    torch.cuda.synchronize()
+    uniq, count = np.unique(idx, return_counts=True)
+    n = int(n_rows.item())
+    assert n == len(uniq) and np.array_equal(rows[:n].cpu().numpy(), uniq)
+    assert np.array_equal(d_rows[:n].cpu().numpy(), np.repeat(count[:, None], 8, 1).astype(np.float32))
+    assert not dw.any()
+
+
 def test_gather_backward_rows_tucker_ive():
     """The compact form at the 4M-slot Tucker + IVE layer's 4096-token batch (clustered queries:
     runs of hundreds of entries spanning many segments), against the dense form bit for bit."""
