@@ -830,6 +830,766 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
   }
 }
 
+// ---------------------------------------------------------------- a wave per (token, head)
+//
+// Many (token, head) pairs: one wave takes a pair from its scores to its slots.  With a workgroup to
+// a pair the vector ALUs' issue was the bound (1,230 instructions in each of eight waves at 2,048
+// keys, k = m = 64: every phase's counts, scans and thresholds are repeated by waves that each hold
+// a part), and six barriers stand in its chain.  A wave alone needs none of either: thresholds and
+// ranks run once, on 64 lanes, and its arrays are its own part of LDS, ordered by wave_lds_order.
+//  * Axis scores sit in registers (NV 16-byte pieces a lane).  The threshold of step 1 is the k-th
+//    largest of 64 G lane maxima (G = 2 for k <= 32, else 4); survivors go to LDS by ballot.
+//  * The Tucker grid needs the top-k only as a set: the k-th key of the survivors is found by a
+//    ballot per key bit.  The additive grid needs it in order: every lane counts the keys above its
+//    own (32-bit compares; equal keys are found by two lanes claiming one rank, and ranked again
+//    with their indices).
+//  * Tucker: exact per-slice scores as in the workgroup kernel (the same lanes per row and the same
+//    order of additions); a lane then takes a column and walks the rows, whose scores it reads from
+//    LDS as doubles; the threshold is the m-th largest of the 512 maxima over eight rows of a column,
+//    and only the columns' sets of eight rows that reach it are looked into.
+//  * The final rank compares fp64 scores; NaNs and equal scores (claims, as above) take the ordered
+//    compare by (key, slot).
+// Whatever the fast steps cannot hold (more than kWaveCap survivors, fewer than k or m numbers) goes
+// to exact searches over all elements, as in the workgroup kernel.
+constexpr int kWaveCap = 256;            // survivors of an axis or of the grid
+constexpr int kWavePieces = 128;         // 16-byte pieces of an axis (sets of the grid) that hold them
+// Pairs (waves) per workgroup: alone where a pair's rare slow steps would hold its neighbours' LDS
+// (16,384 Tucker pairs 161 us, 166 with two, 162 - 173 with four), four where they share a table.
+constexpr int wave_items(bool tucker) { return tucker ? 1 : 4; }
+constexpr int kWaveMaxK = 64, kWaveMaxM = 64;
+constexpr int kWaveMaxKeys = 18 * 256;
+
+// One pair's LDS: the survivors (8 bytes each: key and index of an axis, then fp64 scores of the
+// grid), claims of ranks, the grid survivors' (a << 8) | b, the axes' indices, the additive grid's
+// sorted scores or the Tucker per-slice scores, and the two query rows.
+struct WaveLds {
+  uint32_t* skey;        // [kWaveCap]
+  uint32_t* sidx;        // [kWaveCap]
+  double* cg;            // [kWaveCap], in their place
+  uint32_t* code;        // [kWaveCap]: claims; the exponentials
+  uint16_t* ab;          // [8 kWavePieces]: the grid survivors
+  f32x4* piece;          // [kWavePieces], with piece_at: before the Tucker scores, in their place
+  uint32_t* piece_at;    // [kWavePieces]
+  int32_t* ax_idx;       // [2][64]
+  float* ax_sc;          // [2][64] (additive)
+  float* s_ex;           // [2][rank][64] (Tucker)
+  double* srow;          // [64][2]: row scores (the second 0 with rank 1)
+  double* pcol;          // [2][64]: column factors
+  f32x4* q;              // [2][dk / 4]
+};
+
+constexpr int kWaveRank = 2;             // the largest Tucker rank here
+
+__host__ __device__ inline size_t wave_lds_bytes(bool tucker, int rank, int dk) {
+  const size_t base = kWaveCap * 8 + kWaveCap * 4 + 8 * kWavePieces * 2 + 2 * 64 * 4, pieces = kWavePieces * 20;
+  const size_t scores = tucker ? 2 * rank * 64 * 4 + 2 * 64 * kWaveRank * 8 : 2 * 64 * 4;
+  return base + (scores > 2 * 64 * 4 + pieces ? scores : 2 * 64 * 4 + pieces) +
+         (tucker ? static_cast<size_t>(2) * dk * 4 : 0);
+}
+
+__device__ __forceinline__ WaveLds wave_lds(unsigned char* p, bool tucker, int rank) {
+  WaveLds s;
+  s.cg = reinterpret_cast<double*>(p);
+  s.skey = reinterpret_cast<uint32_t*>(p);
+  s.sidx = s.skey + kWaveCap;
+  s.code = s.sidx + kWaveCap;
+  s.ab = reinterpret_cast<uint16_t*>(s.code + kWaveCap);
+  s.ax_idx = reinterpret_cast<int32_t*>(s.ab + 8 * kWavePieces);
+  s.ax_sc = reinterpret_cast<float*>(s.ax_idx + 2 * 64);
+  s.piece = reinterpret_cast<f32x4*>(s.ax_sc + 2 * 64);
+  s.piece_at = reinterpret_cast<uint32_t*>(s.piece + kWavePieces);
+  s.srow = reinterpret_cast<double*>(s.ax_sc);
+  s.pcol = s.srow + 64 * kWaveRank;
+  s.s_ex = reinterpret_cast<float*>(s.pcol + 64 * kWaveRank);
+  s.q = reinterpret_cast<f32x4*>(p + wave_lds_bytes(tucker, rank, 0));
+  return s;
+}
+
+// Lanes before this one among those of the mask.
+__device__ __forceinline__ int mask_rank(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+}
+
+// Largest L with zero low 16 bits such that at least k of the wave's 64 G values are >= L, one bit
+// and G ballots a step (fewer vector instructions than radix-4 steps; other waves fill the chain).
+template <int G>
+__device__ __forceinline__ uint32_t wave_kth16(const uint32_t (&v)[G], int k) {
+  uint32_t p = 0u;
+#pragma unroll 1
+  for (int b = 31; b >= 16; --b) {
+    const uint32_t c = p | (1u << b);
+    int cnt = 0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) cnt += __popcll(__ballot(v[g] >= c));
+    p = cnt >= k ? c : p;
+    if (cnt == k) break;
+  }
+  return p;
+}
+
+// A key that exactly k of the wave's 64 R keys reach, or, where equal keys allow none, the k-th
+// largest.
+template <int R>
+__device__ __forceinline__ uint32_t wave_kth32(const uint32_t (&v)[R], int k) {
+  uint32_t p = 0u;
+#pragma unroll 1
+  for (int b = 31; b >= 0; --b) {
+    const uint32_t c = p | (1u << b);
+    int cnt = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) cnt += __popcll(__ballot(v[r] >= c));
+    p = cnt >= k ? c : p;
+    if (cnt == k) break;
+  }
+  return p;
+}
+
+// The set of the k largest of the S survivors (key desc, index asc) to ax[0, k), in survivor order.
+template <int R>
+__device__ __forceinline__ void wave_top_set(const WaveLds& s, int S, int k, int32_t* ax) {
+  const int lane = threadIdx.x & (kWave - 1);
+  uint32_t key[R], idx[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int e = lane + kWave * r;
+    key[r] = e < S ? s.skey[e] : 0u;
+    idx[r] = e < S ? s.sidx[e] : 0xFFFFFFFFu;
+  }
+  uint32_t theta = 0u, ylim = 0xFFFFFFFEu;               // (index of no survivor: above ylim)
+  if (S > k) {
+    theta = wave_kth32<R>(key, k);
+    int gt = 0, ge = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      gt += __popcll(__ballot(key[r] > theta));
+      ge += __popcll(__ballot(key[r] >= theta && idx[r] <= ylim));
+    }
+    if (ge > k) {                                         // ties: the lowest indices among them
+      const int need = k - gt;
+      ylim = 0u;
+      for (int b = 15; b >= 0; --b) {                     // largest y with fewer than need below it
+        const uint32_t c = ylim | (1u << b);
+        int below = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) below += __popcll(__ballot(key[r] == theta && idx[r] < c));
+        if (below < need) ylim = c;
+      }
+    }
+  }
+  int pos = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool take = idx[r] != 0xFFFFFFFFu && (key[r] > theta || (key[r] == theta && idx[r] <= ylim));
+    const uint64_t m = __ballot(take);
+    if (take) ax[pos + mask_rank(m)] = static_cast<int32_t>(idx[r]);
+    pos += __popcll(m);
+  }
+}
+
+// The S survivors ranked (key desc, index asc): ranks < k to ax / sc.
+template <int R>
+__device__ __forceinline__ void wave_top_sorted(const WaveLds& s, int S, int k, int32_t* ax, float* sc) {
+  const int lane = threadIdx.x & (kWave - 1);
+  uint32_t key[R], idx[R];
+  int rank[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int e = lane + kWave * r;
+    key[r] = e < S ? s.skey[e] : 0u;
+    idx[r] = e < S ? s.sidx[e] : 0u;
+    rank[r] = 0;
+  }
+  if (lane < 4 && S + lane < kWaveCap) s.skey[S + lane] = 0u;   // the last group of four compares
+  wave_lds_order();
+#pragma unroll 4
+  for (int u = 0; u < S; u += 4) {
+    const uint4 o = *reinterpret_cast<const uint4*>(s.skey + u);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      rank[r] += static_cast<int>(o.x > key[r]) + static_cast<int>(o.y > key[r]) +
+                 static_cast<int>(o.z > key[r]) + static_cast<int>(o.w > key[r]);
+  }
+  // equal keys claim one rank: the claim's last writer is one of them, the others see it
+  bool tie = false;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (lane + kWave * r < S) s.code[rank[r]] = lane + kWave * r;
+  wave_lds_order();
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (lane + kWave * r < S) tie |= s.code[rank[r]] != static_cast<uint32_t>(lane + kWave * r);
+  if (__ballot(tie) != 0ull) {
+    for (int u = 0; u < S; ++u) {
+      const uint32_t ok = s.skey[u], oi = s.sidx[u];
+#pragma unroll
+      for (int r = 0; r < R; ++r) rank[r] += static_cast<int>((ok == key[r]) & (oi < idx[r]));
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (lane + kWave * r < S && rank[r] < k) {
+      ax[rank[r]] = static_cast<int32_t>(idx[r]);
+      sc[rank[r]] = key32_value(key[r]);
+    }
+}
+
+// One axis: the top-k of src[0, n), which is in v, to ax (a set, or in order with their scores to sc).
+// Once the survivors' pieces are in LDS v takes the next axis's scores, which land under the rest.
+template <int NV>
+__device__ __forceinline__ void wave_load(const float* __restrict__ src, int n, f32x4 (&v)[NV]) {
+  const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+    v[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + min(256 * j + 4 * lane, n - 4)));
+}
+template <int NV, bool TUCKER>
+__device__ __forceinline__ void wave_axis(f32x4 (&v)[NV], const float* __restrict__ src,
+                                          const float* __restrict__ next, int n, int k, bool sorted,
+                                          const WaveLds& s, int32_t* ax, float* sc) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const float nan = __builtin_nanf("");
+  float mx[4] = {nan, nan, nan, nan};                     // fmaxf takes the number
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    if (256 * (j + 1) > n && 256 * j + 4 * lane >= n) v[j] = f32x4{nan, nan, nan, nan};
+    mx[j & 3] = fmaxf(mx[j & 3], fmaxf(fmaxf(v[j].x, v[j].y), fmaxf(v[j].z, v[j].w)));
+  }
+  uint32_t L;
+  if (k <= kWave / 2 || NV < 4) {
+    const uint32_t g[2] = {order_key(fmaxf(mx[0], mx[2])), order_key(fmaxf(mx[1], mx[3]))};
+    L = wave_kth16<2>(g, k);
+  } else {
+    const uint32_t g[4] = {order_key(mx[0]), order_key(mx[1]), order_key(mx[2]), order_key(mx[3])};
+    L = wave_kth16<4>(g, k);
+  }
+  int S = 0, Q = 0;
+  if (L != 0u) {
+    // first the 16-byte pieces that hold a survivor, then, a piece to a lane, the survivors
+    const float lim = key32_value(L);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const bool hit = fmaxf(fmaxf(v[j].x, v[j].y), fmaxf(v[j].z, v[j].w)) >= lim;
+      const uint64_t m = __ballot(hit);
+      if (m != 0ull) {                                    // (wave-uniform)
+        const int at = Q + mask_rank(m);
+        if (hit && at < kWavePieces) {
+          s.piece[at] = v[j];
+          s.piece_at[at] = static_cast<uint32_t>(256 * j + 4 * lane);
+        }
+        Q += __popcll(m);
+      }
+    }
+  }
+  if (next != nullptr) wave_load<NV>(next, n, v);
+  if (L != 0u) {
+    const float lim = key32_value(L);
+    wave_lds_order();
+    if (Q <= kWavePieces) {
+      for (int q0 = 0; q0 < Q; q0 += kWave) {             // (wave-uniform)
+        const int q = q0 + lane;
+        const f32x4 x = q < Q ? s.piece[q] : f32x4{nan, nan, nan, nan};
+        const uint32_t i = q < Q ? s.piece_at[q] : 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool hit = x[e] >= lim;
+          const uint64_t m = __ballot(hit);
+          const int at = S + mask_rank(m);
+          if (hit && at < kWaveCap) {
+            s.skey[at] = order_key(x[e]);
+            s.sidx[at] = i + e;
+          }
+          S += __popcll(m);
+        }
+      }
+    }
+  }
+  if (L == 0u || Q > kWavePieces || S > kWaveCap) {
+    // too many survivors (massive ties) or too few numbers: the exact k-th key over all elements,
+    // then the elements above it and the lowest-indexed ones equal to it.  The scores are read again
+    // for every step: kept in registers, the code of a path that hardly ever runs would set the
+    // kernel's registers.  The search starts at the highest bit in which any two keys differ.
+    const int steps = (n + kWave - 1) / kWave;
+    auto key_of = [&](int i) { return order_key(src[min(i, n - 1)]); };
+    uint32_t hi = 0u, lo = 0xFFFFFFFFu;
+#pragma unroll 1
+    for (int j = 0; j < steps; ++j) {                     // (the clamped tail repeats the last element)
+      const uint32_t key = key_of(kWave * j + lane);
+      hi = max(hi, key);
+      lo = min(lo, key);
+    }
+#pragma unroll 1
+    for (int off = 1; off < kWave; off <<= 1) {
+      hi = max(hi, static_cast<uint32_t>(__shfl_xor(static_cast<int>(hi), off, kWave)));
+      lo = min(lo, static_cast<uint32_t>(__shfl_xor(static_cast<int>(lo), off, kWave)));
+    }
+    const int top = hi == lo ? -1 : 31 - __builtin_clz(hi ^ lo);
+    uint32_t theta = top < 0 ? hi : (top == 31 ? 0u : hi >> (top + 1) << (top + 1));
+    int gt = 0;                                           // keys above theta
+#pragma unroll 1
+    for (int b = top; b >= -1; --b) {
+      const uint32_t c = b < 0 ? theta : theta | (1u << b);
+      int cnt = 0;
+#pragma unroll 1
+      for (int j = 0; j < steps; ++j) {
+        const int i = kWave * j + lane;
+        const uint32_t key = key_of(i);
+        cnt += __popcll(__ballot(i < n && (b < 0 ? key > c : key >= c)));
+      }
+      if (b < 0) gt = cnt;
+      else if (cnt >= k) theta = c;
+    }
+    int need = k - gt, pos = 0;
+#pragma unroll 1
+    for (int j = 0; j < steps; ++j) {                     // in index order
+      const int i = kWave * j + lane;
+      const uint32_t key = key_of(i);
+      const uint64_t eq = __ballot(i < n && key == theta);
+      const bool take = i < n && (key > theta || (key == theta && mask_rank(eq) < need));
+      need -= min(need, __popcll(eq));
+      const uint64_t m = __ballot(take);
+      if (take) {
+        const int at = pos + mask_rank(m);
+        s.skey[at] = key;
+        s.sidx[at] = static_cast<uint32_t>(i);
+      }
+      pos += __popcll(m);
+    }
+    S = k;
+  }
+  S = __builtin_amdgcn_readfirstlane(S);
+  wave_lds_order();
+  if (TUCKER && !sorted) {
+    if (S <= 2 * kWave) wave_top_set<2>(s, S, k, ax);
+    else wave_top_set<4>(s, S, k, ax);
+  } else {
+    if (!TUCKER && S <= kWave) wave_top_sorted<1>(s, S, k, ax, sc);
+    else wave_top_sorted<4>(s, S, k, ax, sc);
+  }
+  wave_lds_order();
+}
+
+// The S grid survivors (fp64 scores in s.cg, lane + 64 r's slot in id[r]) ranked (score desc, slot
+// asc).
+template <int R>
+__device__ __forceinline__ void wave_rank_grid(const WaveLds& s, int S, const double (&g)[R],
+                                               const int32_t (&id)[R], int (&rank)[R]) {
+  const int lane = threadIdx.x & (kWave - 1);
+  bool odd = false;                                       // a NaN, or a rank claimed twice
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    rank[r] = 0;
+    odd |= lane + kWave * r < S && g[r] != g[r];
+  }
+  if (lane == 0 && (S & 1) != 0) s.cg[S] = __builtin_nan("");    // (S < kWaveCap: the second of a pair)
+  wave_lds_order();
+#pragma unroll 4
+  for (int u = 0; u < S; u += 2) {
+    const double2 o = *reinterpret_cast<const double2*>(s.cg + u);
+#pragma unroll
+    for (int r = 0; r < R; ++r) rank[r] += static_cast<int>(o.x > g[r]) + static_cast<int>(o.y > g[r]);
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (lane + kWave * r < S) s.code[rank[r]] = lane + kWave * r;
+  wave_lds_order();
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (lane + kWave * r < S) odd |= s.code[rank[r]] != static_cast<uint32_t>(lane + kWave * r);
+  if (__ballot(odd) != 0ull) {
+    wave_lds_order();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      rank[r] = 0;
+      if (lane + kWave * r < S) s.code[lane + kWave * r] = static_cast<uint32_t>(id[r]);
+    }
+    wave_lds_order();
+    for (int u = 0; u < S; ++u) {
+      const uint64_t ok = order_key64(s.cg[u]);
+      const int32_t oi = static_cast<int32_t>(s.code[u]);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint64_t me = order_key64(g[r]);
+        rank[r] += static_cast<int>(ok > me) + static_cast<int>((ok == me) & (oi < id[r]));
+      }
+    }
+  }
+}
+
+struct WaveArgs {
+  const float *sel, *q_row, *q_col, *k_row, *k_col, *core;
+  int32_t* idx_out;
+  float* w_out;
+  int32_t* axis_out;
+  int T, H, n, dk, rank, k, m, softmax, cores;
+};
+
+// Ranks the S grid survivors, whose codes are in s.ab, and writes the m best.
+template <int R, bool TUCKER>
+__device__ __forceinline__ void wave_finish(const WaveArgs& A, const WaveLds& s, int S, size_t pair, int h) {
+  const int lane = threadIdx.x & (kWave - 1);
+  double g[R];
+  int32_t id[R];
+  int rank[R], a[R], b[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int e = lane + kWave * r;
+    const uint32_t c = e < S ? s.ab[e] : 0u;
+    a[r] = static_cast<int>(c >> 8);
+    b[r] = static_cast<int>(c & 0xFFu);
+    if (TUCKER) {
+      g[r] = 0.0;
+      g[r] += s.srow[2 * a[r]] * s.pcol[b[r]];
+      g[r] += s.srow[2 * a[r] + 1] * s.pcol[64 + b[r]];
+    } else {
+      g[r] = static_cast<double>(s.ax_sc[a[r]]) + static_cast<double>(s.ax_sc[64 + b[r]]);
+    }
+    id[r] = s.ax_idx[a[r]] * A.n + s.ax_idx[64 + b[r]];
+  }
+  wave_lds_order();
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (lane + kWave * r < S) s.cg[lane + kWave * r] = g[r];
+  wave_lds_order();
+  wave_rank_grid<R>(s, S, g, id, rank);
+  const size_t o = pair * A.m;
+  float e_of[R];
+  float inv_of = 1.0f;
+  if (A.softmax) {
+    // the exponentials by rank (a lane each, as they are summed), then their sum
+    wave_lds_order();
+    float* ex = reinterpret_cast<float*>(s.code);
+    double* best = s.cg;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (lane + kWave * r < S && rank[r] == 0) best[0] = g[r];
+    wave_lds_order();
+    const double g0 = best[0];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      e_of[r] = __expf(static_cast<float>(g[r] - g0));
+      if (lane + kWave * r < S && rank[r] < A.m) ex[rank[r]] = e_of[r];
+    }
+    wave_lds_order();
+    inv_of = wave_sum(lane < A.m ? ex[lane] : 0.0f);
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    if (!(lane + kWave * r < S && rank[r] < A.m)) continue;
+    A.idx_out[o + rank[r]] = id[r];
+    if (!TUCKER || A.cores == 1) {
+      A.w_out[o + rank[r]] = A.softmax ? e_of[r] / inv_of : static_cast<float>(g[r]);
+    } else {
+      // multi-core scoring (eq. (16)): each core's exact score of the slot, in fp64
+      const float* parts = A.core + static_cast<size_t>(h) * A.cores * A.rank * A.rank;
+      for (int i = 0; i < A.cores; ++i) {
+        double gi = 0.0;
+        for (int rho = 0; rho < A.rank; ++rho) {
+          double p = 0.0;
+          for (int sg = 0; sg < A.rank; ++sg)
+            p += static_cast<double>(parts[(i * A.rank + rho) * A.rank + sg]) *
+                 static_cast<double>(s.s_ex[(A.rank + sg) * 64 + b[r]]);
+          gi += s.srow[2 * a[r] + rho] * p;
+        }
+        A.w_out[(o + rank[r]) * A.cores + i] = static_cast<float>(gi);
+      }
+    }
+  }
+}
+
+template <int NV, bool TUCKER>
+__global__ __launch_bounds__(wave_items(TUCKER) * kWave, NV <= 12 ? 4 : 3) void select_wave_kernel(WaveArgs A) {
+  constexpr int kItems = wave_items(TUCKER);
+  extern __shared__ __align__(16) unsigned char dyn[];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = kItems == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  // pairs in head-major order, dealt to the eight XCDs in contiguous runs (workgroups go to XCDs
+  // round-robin): an XCD's waves re-read the key rows of few heads, from its own L2
+  const int64_t pairs = static_cast<int64_t>(A.T) * A.H;
+  const int64_t nwg = gridDim.x, per = nwg >> 3, extra = nwg & 7, xcd = blockIdx.x & 7;
+  const int64_t wg = xcd * per + (xcd < extra ? xcd : extra) + (blockIdx.x >> 3);
+  const int64_t item = wg * kItems + wave;
+  const int k = A.k, m = A.m;
+  const size_t part = wave_lds_bytes(TUCKER, A.rank, A.dk);
+  const WaveLds s = wave_lds(dyn + wave * part, TUCKER, A.rank);
+  if (!TUCKER) {
+    // the workgroup's table of the additive grid's candidates (a+1)(b+1) <= m, row by row, and
+    // ceil(m / r) for the corner bound of r rows, after the waves' parts
+    uint16_t* ab = reinterpret_cast<uint16_t*>(dyn + kItems * part);
+    if (wave == 0) {
+      const int rows = min(k, m);
+      const int len = lane < rows ? min(k, m / (lane + 1)) : 0;
+      const int first = wave_scan_dpp(len) - len;
+      for (int b = 0; b < len; ++b) ab[first + b] = static_cast<uint16_t>((lane << 8) | b);
+    }
+    __syncthreads();
+  }
+  if (item >= pairs) return;                              // (no barrier beyond)
+  const int h = static_cast<int>(item / A.T);
+  const size_t pair = static_cast<size_t>(item % A.T) * A.H + h;
+  if (TUCKER) {                                           // the two query rows to LDS
+    const int n4 = A.dk >> 2;
+    for (int x = lane; x < 2 * n4; x += kWave)
+      s.q[x] = reinterpret_cast<const f32x4*>((x >= n4 ? A.q_col : A.q_row) + pair * A.dk)[x - (x >= n4 ? n4 : 0)];
+  }
+  const bool sorted = !TUCKER || A.axis_out != nullptr;
+  const float* const src0 = A.sel + pair * A.n;
+  const float* const src1 = src0 + static_cast<size_t>(A.T) * A.H * A.n;
+  f32x4 v[NV];
+  wave_load<NV>(src0, A.n, v);
+#pragma unroll 1
+  for (int axis = 0; axis < 2; ++axis) {
+    // (the Tucker per-slice scores come later: their place takes the axis scores nobody reads)
+    wave_axis<NV, TUCKER>(v, axis ? src1 : src0, axis ? nullptr : src1, A.n, k, sorted, s,
+                          s.ax_idx + axis * 64, s.ax_sc + axis * 64);
+    if (A.axis_out != nullptr && lane < k)
+      A.axis_out[(static_cast<size_t>(axis) * A.T * A.H + pair) * k + lane] = s.ax_idx[axis * 64 + lane];
+  }
+  int S = 0;
+  if (!TUCKER) {
+    const uint16_t* ab = reinterpret_cast<const uint16_t*>(dyn + kItems * part);
+    // theta: the best lower bound on the m-th score that a corner of r x ceil(m / r) pairs gives
+    // (a NaN corner bounds nothing; none at all keeps every candidate)
+    const int rows = min(k, m);
+    uint64_t th = 0ull;
+    if (lane < rows) {
+      const int c = (m + lane) / (lane + 1);
+      if (c <= k) th = order_key64(static_cast<double>(s.ax_sc[lane]) + static_cast<double>(s.ax_sc[64 + c - 1]));
+    }
+    th = wave_max_u64(th);
+    const int len = lane < rows ? min(k, m / (lane + 1)) : 0;
+    const int C = __shfl(wave_scan_dpp(len), kWave - 1, kWave);
+    for (int c0 = 0; c0 < C; c0 += kWave) {
+      const int c = c0 + lane;
+      bool keep = false;
+      uint32_t code = 0u;
+      if (c < C) {
+        code = ab[c];
+        keep = order_key64(static_cast<double>(s.ax_sc[code >> 8]) + static_cast<double>(s.ax_sc[64 + (code & 0xFFu)])) >= th;
+      }
+      const uint64_t mk = __ballot(keep);
+      if (keep) s.ab[S + mask_rank(mk)] = static_cast<uint16_t>(code);
+      S += __popcll(mk);
+    }
+    wave_lds_order();
+  } else {
+    // ---- exact per-slice scores of the selected keys (eq. (4)), fp32: G = 4, 8 or 16 lanes to an
+    // (axis, key) row, L of them to a slice, each striding its slice's 16-byte pieces by L, eight
+    // loads in flight; the partial sums meet through DPP
+    const int rank = A.rank;
+    {
+      constexpr int kPieces = 8;
+      const int n4 = A.dk >> 2, wp = n4 / rank;
+      const int lg = 2 * k <= 32 ? 4 : (2 * k <= 64 ? 3 : 2);
+      const int ls = rank == 1 ? lg : lg - 1;
+      const int part_of = lane & ((1 << lg) - 1);
+      const int rho = part_of >> ls, sub = part_of & ((1 << ls) - 1);
+      const int cnt = (wp - sub + (1 << ls) - 1) >> ls;
+      const int first = rho * wp + sub;
+      const int most = (wp + (1 << ls) - 1) >> ls, least = wp >> ls;    // of cnt
+      for (int row0 = 0; row0 < 2 * k; row0 += kWave >> lg) {
+        const int row = row0 + (lane >> lg);
+        const bool on = row < 2 * k;
+        const int axis = row >= k && on, a = on ? row - (axis ? k : 0) : 0;
+        const f32x4* kr = reinterpret_cast<const f32x4*>(
+            (axis ? A.k_col : A.k_row) + (static_cast<size_t>(h) * A.n + s.ax_idx[axis * 64 + a]) * A.dk) + first;
+        const f32x4* qr = s.q + axis * n4 + first;
+        float acc = 0.0f;
+        int i0 = 0;
+        for (; i0 + kPieces <= least; i0 += kPieces) {    // whole batches in every lane
+          f32x4 kv[kPieces];
+#pragma unroll
+          for (int i = 0; i < kPieces; ++i) kv[i] = kr[(i0 + i) << ls];
+#pragma unroll
+          for (int i = 0; i < kPieces; ++i) {
+            const f32x4 qv = qr[(i0 + i) << ls];
+            acc = fmaf(kv[i].x, qv.x, acc);
+            acc = fmaf(kv[i].y, qv.y, acc);
+            acc = fmaf(kv[i].z, qv.z, acc);
+            acc = fmaf(kv[i].w, qv.w, acc);
+          }
+        }
+        for (; i0 < most; i0 += kPieces) {
+          f32x4 kv[kPieces];
+#pragma unroll
+          for (int i = 0; i < kPieces; ++i)
+            if (i0 + i < cnt) kv[i] = kr[(i0 + i) << ls];
+#pragma unroll
+          for (int i = 0; i < kPieces; ++i)
+            if (i0 + i < cnt) {
+              const f32x4 qv = qr[(i0 + i) << ls];
+              acc = fmaf(kv[i].x, qv.x, acc);
+              acc = fmaf(kv[i].y, qv.y, acc);
+              acc = fmaf(kv[i].z, qv.z, acc);
+              acc = fmaf(kv[i].w, qv.w, acc);
+            }
+        }
+        acc = group_sum_f(acc, ls);
+        if (on && sub == 0) {
+          s.s_ex[(axis * rank + rho) * 64 + a] = acc;
+          if (axis == 0) {
+            s.srow[2 * a + rho] = static_cast<double>(acc);
+            if (rank == 1) s.srow[2 * a + 1] = 0.0;
+          }
+        }
+      }
+    }
+    // rows up to the next eight score NaN: never above a threshold
+    const double nan64 = __builtin_nan("");
+    if (lane >= k && lane < ((k + 7) & ~7))
+      s.srow[2 * lane] = s.srow[2 * lane + 1] = nan64;
+    wave_lds_order();
+    // column factors p = C S_col[:, b], lane b's own and in LDS
+    double pc[kWaveRank];
+    {
+      const float* ch = A.core + static_cast<size_t>(h) * A.cores * rank * rank;
+#pragma unroll
+      for (int rho = 0; rho < kWaveRank; ++rho) {
+        double p = 0.0;
+        for (int sg = 0; sg < rank; ++sg) {
+          double c = 0.0;
+          if (rho < rank)
+            for (int i = 0; i < A.cores; ++i) c += static_cast<double>(ch[(i * rank + rho) * rank + sg]);
+          p += c * static_cast<double>(s.s_ex[(rank + sg) * 64 + min(lane, k - 1)]);
+        }
+        if (rho >= rank) p = 0.0;
+        s.pcol[rho * 64 + lane] = p;
+        pc[rho] = lane < k ? p : nan64;
+      }
+    }
+    wave_lds_order();
+    // row a's score in the column of factors p0, p1, exact in fp64; this lane's column
+    auto score_at = [&](int a, double p0, double p1) {
+      const double2 sr = *reinterpret_cast<const double2*>(s.srow + 2 * a);
+      double g = 0.0;
+      g += sr.x * p0;
+      g += sr.y * p1;
+      return g;
+    };
+    auto score = [&](int a) { return score_at(a, pc[0], pc[1]); };
+    // sets of eight rows of a column: their maxima (fp32 roundings: rounding is monotone)
+    uint32_t mxk[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      double mx = nan64;
+      if (8 * c < k) {                                    // (wave-uniform)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) mx = fmax(mx, score(8 * c + i));
+      }
+      mxk[c] = order_key(static_cast<float>(mx));
+    }
+    const uint32_t L = wave_kth16<8>(mxk, m);
+    int Q = 0;
+    if (L != 0u) {
+      // first the sets that hold a survivor, then, a set to a lane, the survivors
+      const float lim = key32_value(L);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const bool hit = mxk[c] >= L;
+        const uint64_t mk = __ballot(hit);
+        const int at = Q + mask_rank(mk);
+        if (hit && at < kWavePieces) s.sidx[at] = static_cast<uint32_t>((c << 11) | lane);
+        Q += __popcll(mk);
+      }
+      wave_lds_order();
+      if (Q <= kWavePieces) {
+        for (int q0 = 0; q0 < Q; q0 += kWave) {           // (wave-uniform)
+          const bool on = q0 + lane < Q;
+          const uint32_t set = on ? s.sidx[q0 + lane] : 0u;
+          const int a0 = static_cast<int>(set >> 8), b = static_cast<int>(set & 0xFFu);
+          const double p0 = on ? s.pcol[b] : nan64, p1 = s.pcol[64 + b];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const bool hit = static_cast<float>(score_at(a0 + i, p0, p1)) >= lim;
+            const uint64_t mk = __ballot(hit);
+            const int at = S + mask_rank(mk);
+            if (hit) s.ab[at] = static_cast<uint16_t>(set + (i << 8));
+            S += __popcll(mk);
+          }
+        }
+      }
+    }
+    if (L != 0u && Q <= kWavePieces && S > kWaveCap && S <= 2 * kWaveCap) {
+      // sets of a few columns that hold most of the grid's best (a core close to rank one): the m-th
+      // largest rounding of all survivors takes the threshold's place (skey and sidx hold the keys)
+      wave_lds_order();
+      for (int e = lane; e < S; e += kWave) {
+        const int c = s.ab[e];
+        s.skey[e] = order_key(static_cast<float>(score_at(c >> 8, s.pcol[c & 0xFF], s.pcol[64 + (c & 0xFF)])));
+      }
+      wave_lds_order();
+      uint32_t theta = 0u;
+      for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t c = theta | (1u << bit);
+        int cnt = 0;
+        for (int e0 = 0; e0 < S; e0 += kWave) cnt += __popcll(__ballot(e0 + lane < S && s.skey[e0 + lane] >= c));
+        if (cnt >= m) theta = c;
+        if (cnt == m) break;
+      }
+      // (a step of 64 is read before it is written, and written no further than it was read)
+      int kept = 0;
+      for (int e0 = 0; e0 < S; e0 += kWave) {
+        const bool hit = e0 + lane < S && s.skey[e0 + lane] >= theta;
+        const uint16_t c = hit ? s.ab[e0 + lane] : static_cast<uint16_t>(0);
+        const uint64_t mk = __ballot(hit);
+        wave_lds_order();
+        if (hit) s.ab[kept + mask_rank(mk)] = c;
+        wave_lds_order();
+        kept += __popcll(mk);
+      }
+      S = kept;
+    }
+    if (L == 0u || Q > kWavePieces || S > kWaveCap) {
+      // massive ties, or fewer than m numbers: the exact m-th largest fp64 key, then the lowest
+      // slots among the candidates equal to it.  The searches start at the highest bit in which any
+      // two keys (any slot) can differ.
+      const bool on = lane < k;
+      uint64_t hi = 0ull, lo = ~0ull;
+      for (int a = 0; a < k; ++a) {
+        const uint64_t key = order_key64(score(a));
+        hi = on && key > hi ? key : hi;
+        lo = on && key < lo ? key : lo;
+      }
+      hi = wave_max_u64(hi);
+      lo = ~wave_max_u64(~lo);
+      const int top = hi == lo ? -1 : 63 - __builtin_clzll(hi ^ lo);
+      uint64_t theta = top < 0 ? hi : (top == 63 ? 0ull : hi >> (top + 1) << (top + 1));
+      for (int bit = top; bit >= 0; --bit) {
+        const uint64_t c = theta | (1ull << bit);
+        int cnt = 0;
+        for (int a = 0; a < k; ++a) cnt += __popcll(__ballot(on && order_key64(score(a)) >= c));
+        if (cnt >= m) theta = c;
+      }
+      int gt = 0;
+      for (int a = 0; a < k; ++a) gt += __popcll(__ballot(on && order_key64(score(a)) > theta));
+      const int need = m - gt;
+      const uint32_t col = static_cast<uint32_t>(s.ax_idx[64 + min(lane, k - 1)]);
+      uint32_t ylim = 0u;
+      for (int bit = 31 - __builtin_clz(static_cast<uint32_t>(A.n) * static_cast<uint32_t>(A.n)); bit >= 0; --bit) {
+        const uint32_t c = ylim | (1u << bit);
+        int below = 0;
+        for (int a = 0; a < k; ++a)
+          below += __popcll(__ballot(on && order_key64(score(a)) == theta &&
+                                     static_cast<uint32_t>(s.ax_idx[a]) * A.n + col < c));
+        if (below < need) ylim = c;
+      }
+      S = 0;
+      for (int a = 0; a < k; ++a) {
+        const uint64_t key = order_key64(score(a));
+        const bool take = on && (key > theta || (key == theta && static_cast<uint32_t>(s.ax_idx[a]) * A.n + col <= ylim));
+        const uint64_t mk = __ballot(take);
+        if (take) s.ab[S + mask_rank(mk)] = static_cast<uint16_t>((a << 8) | lane);
+        S += __popcll(mk);
+      }
+    }
+    wave_lds_order();
+  }
+  S = __builtin_amdgcn_readfirstlane(S);
+  constexpr int kUsual = TUCKER ? 2 : 1;                  // (about 100 and 60 survivors)
+  if (S <= kUsual * kWave) wave_finish<kUsual, TUCKER>(A, s, S, pair, h);
+  else wave_finish<4, TUCKER>(A, s, S, pair, h);
+}
+
 }  // namespace
 
 int additive_candidates(int k, int m) {
@@ -862,6 +1622,39 @@ hipError_t launch_select(const umem_desc& d, int T, const float* sel, const floa
   const int n_cand = tucker ? d.topk * d.topk : additive_candidates(d.topk, d.topm);
   if (tucker && n_cand > KK_MAX) return hipErrorInvalidValue;
   const size_t lds = select_lds_bytes(n_cand, tucker, pooled ? d.dv : 0);
+  const int64_t pairs = static_cast<int64_t>(T) * d.heads;
+  // A wave per pair from two waves per SIMD on: fewer leave its chain of steps (about 12 us, 25 with
+  // the Tucker grid) longer than the workgroup kernel's, which spreads a pair over eight waves.
+  // Measured (us, wave / workgroup kernel): additive, k = m = 32, 1,024 keys, 1,024 / 2,048 / 4,096
+  // pairs 11.7 / 10.8, 17.4 / 18.1, 22.4 / 32.5; 4,480 keys 20.5 / 16.1, 22.2 / 26.3, 44.6 / 46.9;
+  // Tucker, k = m = 64, 2,048 keys 26.6 / 33.9, 31.3 / 52.6, 43.8 / 95.5; k = m = 42, 448 dims
+  // 39.8 / 36.2, 49.4 / 58.8, 94.5 / 109.2.  Beyond 2,048 keys the scores take 48 to 72 registers (two
+  // or three waves per SIMD) and too few loads are in flight where the scores come from HBM: 3,000
+  // keys 28.3 / 23.5 at 2,048 pairs, 43.5 / 79.1 at 8,192; 4,480 keys 68.0 / 88.7 at 8,192, but the
+  // 1,024-token decode forward (2,048 pairs) 76.0 against 71.6.
+  const int64_t wave_pairs = d.n_keys > 2048 ? 8192 : 2048;
+  if (pooled == nullptr && pairs >= wave_pairs && d.n_keys % 4 == 0 && d.n_keys <= kWaveMaxKeys &&
+      d.topk <= kWaveMaxK && d.rank <= kWaveRank && d.n_keys >= 8 * d.topk && d.topm <= kWaveMaxM &&
+      (tucker || n_cand <= kWaveCap)) {
+    const WaveArgs A{sel, q_row, q_col, k_row, k_col, core, idx, w, axis_idx, T, d.heads, d.n_keys, d.dk,
+                     d.rank, d.topk, d.topm, d.weight == UMEM_W_SOFTMAX, n_cores(d)};
+    const int items = wave_items(tucker);
+    const size_t bytes = items * wave_lds_bytes(tucker, d.rank, d.dk) + (tucker ? 0 : 2 * static_cast<size_t>(kWaveCap));
+    const dim3 wgrid(static_cast<unsigned>((pairs + items - 1) / items)), wblock(items * kWave);
+#define UMEM_SELECT_WAVE(NV)                                                                        \
+  do {                                                                                            \
+    if (tucker) hipLaunchKernelGGL((select_wave_kernel<NV, true>), wgrid, wblock, bytes, s, A);   \
+    else hipLaunchKernelGGL((select_wave_kernel<NV, false>), wgrid, wblock, bytes, s, A);         \
+  } while (0)
+    const int nv = (d.n_keys + 255) / 256;
+    if (nv <= 2) UMEM_SELECT_WAVE(2);
+    else if (nv <= 4) UMEM_SELECT_WAVE(4);
+    else if (nv <= 8) UMEM_SELECT_WAVE(8);
+    else if (nv <= 12) UMEM_SELECT_WAVE(12);
+    else UMEM_SELECT_WAVE(18);
+#undef UMEM_SELECT_WAVE
+    return hipGetLastError();
+  }
   const dim3 grid(static_cast<unsigned>(T) * d.heads), block(THREADS);
 #define UMEM_SELECT_P(NV, VEC, MODE)                                                              \
   hipLaunchKernelGGL((select_kernel<NV, VEC, MODE>), grid, block, lds, s, sel, q_row, q_col,     \
