@@ -6,7 +6,7 @@
 // Trick 6 is a second GEMM of y by w_out [d_out, D'v].  Both operands are then rows of K.
 //
 // Tiles of 128 x 128 per workgroup, four waves of 64 x 64 (4 x 4 v_mfma_f32_16x16x32_bf16
-// tiles), K in steps of 64.  A (fp32, or bf16 when the producer already rounded it) and B (bf16)
+// tiles), or of 64 x 64, four waves of 32 x 32 (gemm_shape), K in steps of 64.  A (fp32, or bf16 when the producer already rounded it) and B (bf16)
 // are read with 16-byte buffer loads, whose range check returns zeros past the rows of the
 // matrix, so edge tiles need no branches; fp32 A is rounded to bf16 (nearest even) as it is
 // staged into LDS, bf16 A and B are copied.  The operand tiles are
@@ -31,14 +31,20 @@
 namespace umem {
 namespace {
 
-constexpr int BM = 128, BN = 128, BK = 64;
+constexpr int BK = 64;
 constexpr int THREADS = 256;
 constexpr int LDA = BK + 8;   // LDS pitch of A's and B's rows in bf16 (144 B: fragment reads conflict-free)
-constexpr int LDC = 64 + 4;   // LDS pitch of a wave's output rows in fp32 (epilogue)
-constexpr int kTileElems = (BM + BN) * LDA;      // one buffer of both operand tiles, bf16
 constexpr int kXcds = 8;
 constexpr uint32_t kOutOfRange = 0x80000000u;     // a buffer offset past any valid record
-static_assert(4 * 32 * LDC * 4 <= 2 * kTileElems * 2, "epilogue staging fits the tiles' LDS");
+
+// A tile is 32 MT x 32 MT, a wave's block of it 16 MT x 16 MT; MT = 4 or 2.
+template <int MT>
+struct Tile {
+  static constexpr int kRows = 32 * MT;
+  static constexpr int kElems = 2 * kRows * LDA;        // one buffer of both operand tiles, bf16
+  static constexpr int LDC = 16 * MT + 4;               // LDS pitch of a wave's output rows in fp32
+  static_assert(4 * 32 * LDC * 4 <= 2 * kElems * 2, "epilogue staging fits the tiles' LDS");
+};
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -46,14 +52,14 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// One K-slice of the operands in registers: of fp32 A eight 16-byte pieces (thread t, piece i:
-// row (t + 256 i) / 16, k ((t + 256 i) % 16) * 4), of bf16 A and of B four (row (t + 256 i) / 8,
+// One K-slice of the operands in registers: of fp32 A 2 MT 16-byte pieces (thread t, piece i:
+// row (t + 256 i) / 16, k ((t + 256 i) % 16) * 4), of bf16 A and of B MT (row (t + 256 i) / 8,
 // k ((t + 256 i) % 8) * 8).
-template <typename AT>
+template <typename AT, int MT>
 struct Slice {
-  static constexpr int kA = sizeof(AT) == 4 ? 8 : 4;
+  static constexpr int kA = sizeof(AT) == 4 ? 2 * MT : MT;
   u32x4 a[kA];
-  u32x4 b[4];
+  u32x4 b[MT];
 };
 
 // Buffer resource of a raw byte range (stride 0; 32-bit data format, as buffer loads need).
@@ -64,19 +70,19 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* p, uint32_t b
 
 // K-range [.., k_end) of this split; rows of K elements.  Rows past the matrix read as zeros by
 // the buffer range check; k past k_end is sent out of range explicitly.
-template <typename AT>
+template <typename AT, int MT>
 __device__ __forceinline__ void fetch(__amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb, int K,
-                                      int k_end, int m0, int n0, int k0, int tid, Slice<AT>& sl) {
+                                      int k_end, int m0, int n0, int k0, int tid, Slice<AT, MT>& sl) {
   constexpr int kPer = 16 / sizeof(AT);            // A elements per 16-byte piece
 #pragma unroll
-  for (int i = 0; i < Slice<AT>::kA; ++i) {
+  for (int i = 0; i < Slice<AT, MT>::kA; ++i) {
     const int f = tid + THREADS * i;
     const int gk = k0 + (f % (BK / kPer)) * kPer;
     const uint32_t off = static_cast<uint32_t>((m0 + f / (BK / kPer)) * K + gk) * sizeof(AT);
     sl.a[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, gk < k_end ? off : kOutOfRange, 0, 0);
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < MT; ++i) {
     const int f = tid + THREADS * i;
     const int gk = k0 + (f & 7) * 8;
     const uint32_t off = static_cast<uint32_t>((n0 + (f >> 3)) * K + gk) * 2u;
@@ -90,10 +96,10 @@ __device__ __forceinline__ uint32_t pack_bf16(uint32_t lo, uint32_t hi) {
                                               static_cast<__bf16>(__uint_as_float(hi))});
 }
 
-template <typename AT>
-__device__ __forceinline__ void stage(const Slice<AT>& sl, uint16_t* As, uint16_t* Bs, int tid) {
+template <typename AT, int MT>
+__device__ __forceinline__ void stage(const Slice<AT, MT>& sl, uint16_t* As, uint16_t* Bs, int tid) {
 #pragma unroll
-  for (int i = 0; i < Slice<AT>::kA; ++i) {
+  for (int i = 0; i < Slice<AT, MT>::kA; ++i) {
     const int f = tid + THREADS * i;
     if constexpr (sizeof(AT) == 4)
       *reinterpret_cast<u32x2*>(As + (f >> 4) * LDA + (f & 15) * 4) =
@@ -102,7 +108,7 @@ __device__ __forceinline__ void stage(const Slice<AT>& sl, uint16_t* As, uint16_
       *reinterpret_cast<u32x4*>(As + (f >> 3) * LDA + (f & 7) * 8) = sl.a[i];
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < MT; ++i) {
     const int f = tid + THREADS * i;
     *reinterpret_cast<u32x4*>(Bs + (f >> 3) * LDA + (f & 7) * 8) = sl.b[i];
   }
@@ -110,10 +116,11 @@ __device__ __forceinline__ void stage(const Slice<AT>& sl, uint16_t* As, uint16_
 
 // A fp32 or bf16 [M, K], B bf16 [N, K] (both rows of K, 16-byte aligned), C fp32 [M, N]; the
 // bytes of A and of B below 2^31.
-template <typename AT>
-__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_kernel(
+template <typename AT, int MT>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(MT == 4 ? 2 : 4, MT == 4 ? 2 : 4))) void gemm_bf16_kernel(
     const AT* __restrict__ A, const uint16_t* __restrict__ B, float* __restrict__ C, int M,
     int N, int K, int n_tiles_n, int per_xcd, int n_tiles, int n_items, int k_chunk) {
+  constexpr int BM = Tile<MT>::kRows, BN = BM, kTileElems = Tile<MT>::kElems, LDC = Tile<MT>::LDC;
   __shared__ __align__(16) uint16_t smem[2 * kTileElems];
   // item = split * n_tiles + tile; XCD x takes items [x per, (x + 1) per)
   const int item = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
@@ -126,17 +133,17 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;         // this wave's 64 x 64 block of the tile
+  const int wm = wave >> 1, wn = wave & 1;         // this wave's 16 MT x 16 MT block of the tile
   const __amdgpu_buffer_rsrc_t ra = rsrc(A, static_cast<uint32_t>(M) * K * static_cast<uint32_t>(sizeof(AT)));
   const __amdgpu_buffer_rsrc_t rb = rsrc(B, static_cast<uint32_t>(N) * K * 2u);
 
-  f32x4 acc[4][4];
+  f32x4 acc[MT][MT];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < MT; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < MT; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  Slice<AT> sl;
+  Slice<AT, MT> sl;
   fetch(ra, rb, K, k_end, m0, n0, k_begin, tid, sl);
   stage(sl, smem, smem + BM * LDA, tid);
   __syncthreads();
@@ -148,17 +155,17 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
     for (int ks = 0; ks < BK; ks += 32) {
       // lane: row (or column) lane % 16 of a 16-block, k = ks + 8 (lane / 16) ... + 7
-      bf16x8 af[4], bfr[4];
+      bf16x8 af[MT], bfr[MT];
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
-        af[a] = *reinterpret_cast<const bf16x8*>(As + (wm * 64 + a * 16 + (lane & 15)) * LDA + ks + 8 * (lane >> 4));
+      for (int a = 0; a < MT; ++a)
+        af[a] = *reinterpret_cast<const bf16x8*>(As + (wm * 16 * MT + a * 16 + (lane & 15)) * LDA + ks + 8 * (lane >> 4));
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
-        bfr[b] = *reinterpret_cast<const bf16x8*>(Bs + (wn * 64 + b * 16 + (lane & 15)) * LDA + ks + 8 * (lane >> 4));
+      for (int b = 0; b < MT; ++b)
+        bfr[b] = *reinterpret_cast<const bf16x8*>(Bs + (wn * 16 * MT + b * 16 + (lane & 15)) * LDA + ks + 8 * (lane >> 4));
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < MT; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < MT; ++b)
           acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
     }
     if (k0 + BK < k_end) {
@@ -169,32 +176,29 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if (k0 + 2 * BK < k_end) fetch(ra, rb, K, k_end, m0, n0, k0 + 2 * BK, tid, sl);
     buf ^= 1;
   }
-  // D layout: lane holds rows 4 (lane / 16) + r of column lane % 16.  Each wave's 64 x 64 block
-  // goes out in two halves of 32 rows through LDS (the operand tiles' space, free after the last
-  // barrier), read back as 16-byte pieces so that every row is written as whole 128-byte lines.
+  // D layout: lane holds rows 4 (lane / 16) + r of column lane % 16.  Each wave's block goes out 32
+  // rows at a time through LDS (the operand tiles' space, free after the last barrier), read back as
+  // 16-byte pieces so that every row is written in contiguous runs of 16 MT values.
+  constexpr int kPer = 4 * MT;                     // 16-byte pieces of a block's row
   float* Cs = reinterpret_cast<float*>(smem) + wave * 32 * LDC;
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
+  for (int half = 0; half < MT / 2; ++half) {
 #pragma unroll
     for (int a2 = 0; a2 < 2; ++a2)
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
+      for (int b = 0; b < MT; ++b)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           Cs[(a2 * 16 + 4 * (lane >> 4) + r) * LDC + b * 16 + (lane & 15)] = acc[half * 2 + a2][b][r];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_order();
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = (lane >> 4) + 4 * i, c4 = (lane & 15) * 4;
-      const int gm = m0 + wm * 64 + half * 32 + row, gn = n0 + wn * 64 + c4;
+    for (int i = 0; i < 32 * kPer / kWave; ++i) {
+      const int row = (lane + kWave * i) / kPer, c4 = (lane % kPer) * 4;
+      const int gm = m0 + wm * 16 * MT + half * 32 + row, gn = n0 + wn * 16 * MT + c4;
       const f32x4 v = *reinterpret_cast<const f32x4*>(Cs + row * LDC + c4);
       if (gm < M && gn < N) *reinterpret_cast<f32x4*>(C + static_cast<size_t>(gm) * N + gn) = v;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_order();
   }
 }
 
@@ -210,25 +214,40 @@ __global__ __launch_bounds__(THREADS) void sum_splits_kernel(const f32x4* __rest
   }
 }
 
-int n_tiles(int M, int N) { return ((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
-
-int split_count(int M, int N, int K) {
-  int S = 1;
-  while (static_cast<int64_t>(n_tiles(M, N)) * S < 512 && K / (2 * S) >= 4 * BK) S *= 2;
-  return S;
+// Tiles, tile size and K splits of a product.  128 x 128 tiles where there are enough of them to fill
+// the chip (two workgroups per CU) or K is long; else 64 x 64 tiles, which give four times the
+// workgroups before K has to be split and a quarter of the partial sums where it is: 4,096 x 512 x
+// 2,048 in 24.2 us unsplit against 19.6 and 7.5 us for four partial products and their sum; 2,036 x
+// 512 x 2,048 12.8 us either way, its partial sums then 33 -> 8 MB (the LayerNorm that adds them 9.1
+// -> 5.5 us).  Over a long K their operand traffic costs more: 512 x 1,024 x 16,384 43.2 against
+// 33.9 us with the sum.  (Two to six slices in flight instead of one: no faster at either tile.)
+constexpr int kFullTiles = 512, kLongK = 2048;
+struct Shape {
+  int mt, tm, tn, splits;
+  int tiles() const { return tm * tn; }
+};
+Shape gemm_shape(int M, int N, int K) {
+  Shape g;
+  g.mt = K > kLongK || static_cast<int64_t>((M + 127) / 128) * ((N + 127) / 128) >= kFullTiles ? 4 : 2;
+  const int rows = 32 * g.mt;
+  g.tm = (M + rows - 1) / rows;
+  g.tn = (N + rows - 1) / rows;
+  g.splits = 1;
+  while (static_cast<int64_t>(g.tm) * g.tn * g.splits < 512 && K / (2 * g.splits) >= 4 * BK) g.splits *= 2;
+  return g;
 }
 
 size_t round_up256(size_t x) { return (x + 255) / 256 * 256; }
 
 // A's buffer range is 32-bit: a GEMM is launched in bands of at most this many rows of A, whose
-// bytes stay below 2^31 (a multiple of BM).
+// bytes stay below 2^31 (a multiple of 128).
 int64_t band_rows(int K) {
-  return std::max<int64_t>(BM, (((INT64_C(1) << 31) - 1) / (static_cast<int64_t>(K) * 4)) / BM * BM);
+  return std::max<int64_t>(128, (((INT64_C(1) << 31) - 1) / (static_cast<int64_t>(K) * 4)) / 128 * 128);
 }
 
 // Partial-sum bytes of one launch (one band) of `rows` rows.
 size_t band_partial_bytes(int rows, int N, int K) {
-  const int S = split_count(rows, N, K);
+  const int S = gemm_shape(rows, N, K).splits;
   return S > 1 ? round_up256(static_cast<size_t>(S) * rows * N * sizeof(float)) : 0;
 }
 
@@ -247,6 +266,20 @@ size_t gemm_partial_bytes(int M, int N, int K) {
 
 namespace {
 
+// The product's tiles into C, or, split, the partial products into C [splits][M][N].
+template <typename AT>
+void launch_tiles(const AT* A, const uint16_t* B, float* C, int M, int N, int K, const Shape& g,
+                  hipStream_t s) {
+  const int items = g.tiles() * g.splits, per = (items + kXcds - 1) / kXcds;
+  const int k_chunk = g.splits > 1 ? ((K + g.splits - 1) / g.splits + BK - 1) / BK * BK : K;
+  if (g.mt == 4)
+    hipLaunchKernelGGL((gemm_bf16_kernel<AT, 4>), dim3(per * kXcds), dim3(THREADS), 0, s, A, B, C, M, N,
+                       K, g.tn, per, g.tiles(), items, k_chunk);
+  else
+    hipLaunchKernelGGL((gemm_bf16_kernel<AT, 2>), dim3(per * kXcds), dim3(THREADS), 0, s, A, B, C, M, N,
+                       K, g.tn, per, g.tiles(), items, k_chunk);
+}
+
 // The bands are sized for fp32 A whatever A's type, so that the scratch of the split-K partials
 // (gemm_partial_bytes) is the same for both.
 template <typename AT>
@@ -261,13 +294,9 @@ hipError_t gemm_any(const AT* A, const uint16_t* B, float* C, int M, int N, int 
     }
     return hipSuccess;
   }
-  const int tn = (N + BN - 1) / BN;
-  const int tiles = n_tiles(M, N);
-  const int S = split_count(M, N, K);
-  const int per = (tiles * S + kXcds - 1) / kXcds;
-  const int k_chunk = S > 1 ? ((K + S - 1) / S + BK - 1) / BK * BK : K;
-  hipLaunchKernelGGL(gemm_bf16_kernel<AT>, dim3(per * kXcds), dim3(THREADS), 0, s, A, B,
-                     S > 1 ? part : C, M, N, K, tn, per, tiles, tiles * S, k_chunk);
+  const Shape g = gemm_shape(M, N, K);
+  const int S = g.splits;
+  launch_tiles(A, B, S > 1 ? part : C, M, N, K, g, s);
   if (S > 1) {
     const size_t n4 = static_cast<size_t>(M) * N / 4;     // N % 8 == 0
     const unsigned blocks = static_cast<unsigned>(std::min<size_t>((n4 + THREADS - 1) / THREADS, 2048));
@@ -291,17 +320,13 @@ hipError_t gemm_bf16(const uint16_t* A, const uint16_t* B, float* C, int M, int 
 
 hipError_t gemm_bf16_parts(const uint16_t* A, const uint16_t* B, float* C, int M, int N, int K,
                            float* part, hipStream_t s, int* splits) {
-  const int S = split_count(M, N, K);
-  if (M > band_rows(K) || S == 1) {
+  const Shape g = gemm_shape(M, N, K);
+  if (M > band_rows(K) || g.splits == 1) {
     *splits = 1;
     return gemm_any(A, B, C, M, N, K, part, s);
   }
-  *splits = S;
-  const int tiles = n_tiles(M, N);
-  const int per = (tiles * S + kXcds - 1) / kXcds;
-  const int k_chunk = ((K + S - 1) / S + BK - 1) / BK * BK;
-  hipLaunchKernelGGL(gemm_bf16_kernel<uint16_t>, dim3(per * kXcds), dim3(THREADS), 0, s, A, B, part,
-                     M, N, K, (N + BN - 1) / BN, per, tiles, tiles * S, k_chunk);
+  *splits = g.splits;
+  launch_tiles(A, B, part, M, N, K, g, s);
   return hipGetLastError();
 }
 

@@ -5,8 +5,8 @@
 // -> LayerNorm of each (axis, head) query over its D_k elements -> q_row (and q_col unless the
 // query is shared).
 //
-// * conv_kernel: one thread per 4 consecutive channels of a token, the K_c source rows read as
-//   16-byte pieces (neighbouring tokens' rows are L2 hits), fp32 accumulation.  The convolved
+// * conv_kernel: one thread per 4 consecutive channels of a run of tokens, the source rows read as
+//   16-byte pieces and kept for the run's window, fp32 accumulation.  The convolved
 //   rows feed only the query linear, whose GEMM takes its operands in bf16, so they are stored
 //   rounded to bf16 (nearest even, the rounding the GEMM would apply to fp32 rows).
 // * the query linear is the projection's GEMM (split over K where few tiles would leave CUs
@@ -29,37 +29,97 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-// y: the convolved rows as bf16 bits [T, d]
+// y: the convolved rows as bf16 bits [T, d].  A thread takes four channels of R consecutive tokens
+// and holds the KC rows of its window, reading each source row once for the run (again after a
+// sequence's end); the row loads of a run that stays in one sequence are all issued before the first
+// is used.  Bound by HBM (rows read, bf16 rows written): 2,036 tokens of 2,048 channels in four
+// sequences 8.1 us, against 13.6 for a thread per token that read all KC rows behind two 64-bit
+// divisions.
+template <int KC, int R>
 __global__ __launch_bounds__(THREADS) void conv_kernel(const float* __restrict__ x,
                                                        const float* __restrict__ hist,
                                                        const float* __restrict__ w,
-                                                       uint16_t* __restrict__ y, int L, int d, int kc,
-                                                       size_t n4) {
-  const int d4 = d >> 2;
-  for (size_t i = static_cast<size_t>(blockIdx.x) * THREADS + threadIdx.x; i < n4;
-       i += static_cast<size_t>(gridDim.x) * THREADS) {
-    const size_t t = i / d4;
-    const int c = static_cast<int>(i - t * d4) * 4;
-    const size_t b = t / L;
-    const int l = static_cast<int>(t - b * L);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int j = 0; j < kc; ++j) {
-      const int src = l - j;
-      f32x4 v = {0.f, 0.f, 0.f, 0.f};
-      if (src >= 0)
-        v = *reinterpret_cast<const f32x4*>(x + (t - j) * d + c);
-      else if (hist != nullptr)
-        v = *reinterpret_cast<const f32x4*>(hist + (b * (kc - 1) + (kc - 1 + src)) * d + c);
-      const f32x4 wj = *reinterpret_cast<const f32x4*>(w + static_cast<size_t>(j) * d + c);
-      acc.x = fmaf(wj.x, v.x, acc.x);
-      acc.y = fmaf(wj.y, v.y, acc.y);
-      acc.z = fmaf(wj.z, v.z, acc.z);
-      acc.w = fmaf(wj.w, v.w, acc.w);
+                                                       uint16_t* __restrict__ y, int T, int L, int d,
+                                                       int cols) {
+  const int run = blockIdx.x / cols;                     // (uniform over the workgroup)
+  const int c = ((blockIdx.x - run * cols) * THREADS + threadIdx.x) * 4;
+  if (c >= d) return;                                    // (no barrier in this kernel)
+  const int t0 = run * R, end = min(T, t0 + R);
+  f32x4 wj[KC];
+#pragma unroll
+  for (int j = 0; j < KC; ++j) wj[j] = *reinterpret_cast<const f32x4*>(w + static_cast<size_t>(j) * d + c);
+  int b = t0 / L, l = t0 - b * L;
+  // the source row at place `at` of sequence `seq` (before its first token: the history, or zeros)
+  auto row = [&](int seq, int at) {
+    if (at >= 0) return *reinterpret_cast<const f32x4*>(x + (static_cast<size_t>(seq) * L + at) * d + c);
+    if (hist != nullptr)
+      return *reinterpret_cast<const f32x4*>(hist + (static_cast<size_t>(seq) * (KC - 1) + (KC - 1 + at)) * d + c);
+    return f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  f32x4 win[KC];                                         // win[j]: the row j tokens back
+  f32x4 ahead[R];
+  const bool one = l + R <= L && t0 + R <= T;
+#pragma unroll
+  for (int j = 1; j < KC; ++j) win[j - 1] = row(b, l - j);
+  if (one) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) ahead[r] = row(b, l + r);
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int t = t0 + r;
+    if (t >= end) break;
+    if (l == L) {                                        // the next sequence
+      l = 0;
+      ++b;
+#pragma unroll
+      for (int j = 1; j < KC; ++j) win[j - 1] = row(b, -j);
     }
-    *reinterpret_cast<u32x2*>(y + t * d + c) =
+#pragma unroll
+    for (int j = KC - 1; j > 0; --j) win[j] = win[j - 1];
+    win[0] = one ? ahead[r] : row(b, l);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < KC; ++j) {
+      acc.x = fmaf(wj[j].x, win[j].x, acc.x);
+      acc.y = fmaf(wj[j].y, win[j].y, acc.y);
+      acc.z = fmaf(wj[j].z, win[j].z, acc.z);
+      acc.w = fmaf(wj[j].w, win[j].w, acc.w);
+    }
+    *reinterpret_cast<u32x2*>(y + static_cast<size_t>(t) * d + c) =
         u32x2{__builtin_bit_cast(uint32_t, bf16x2{static_cast<__bf16>(acc.x), static_cast<__bf16>(acc.y)}),
               __builtin_bit_cast(uint32_t, bf16x2{static_cast<__bf16>(acc.z), static_cast<__bf16>(acc.w)})};
+    ++l;
   }
+}
+
+// Runs of four tokens where sequences are that long and the launch has waves to spare, else of one.
+hipError_t launch_conv(const float* x, const float* hist, const float* w, uint16_t* y, int T, int L, int d,
+                       int kc, hipStream_t s) {
+  const int cols = (d / 4 + THREADS - 1) / THREADS;
+  const bool run = L >= 4 && static_cast<int64_t>(T) * cols >= 2048;
+#define UMEM_CONV(KC)                                                                             \
+  do {                                                                                            \
+    if (run)                                                                                      \
+      hipLaunchKernelGGL((conv_kernel<KC, 4>), dim3(cols * ((T + 3) / 4)), dim3(THREADS), 0, s, x, hist, \
+                         w, y, T, L, d, cols);                                                    \
+    else                                                                                          \
+      hipLaunchKernelGGL((conv_kernel<KC, 1>), dim3(cols * T), dim3(THREADS), 0, s, x, hist, w, y, T, L, \
+                         d, cols);                                                                \
+  } while (0)
+  switch (kc) {
+    case 1: UMEM_CONV(1); break;
+    case 2: UMEM_CONV(2); break;
+    case 3: UMEM_CONV(3); break;
+    case 4: UMEM_CONV(4); break;
+    case 5: UMEM_CONV(5); break;
+    case 6: UMEM_CONV(6); break;
+    case 7: UMEM_CONV(7); break;
+    case 8: UMEM_CONV(8); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef UMEM_CONV
+  return hipGetLastError();
 }
 
 __device__ __forceinline__ float wave_sum_f(float v) {
@@ -183,11 +243,7 @@ hipError_t launch_query(const umem_query_desc& qd, int B, int L, const float* x,
   float* q_raw = reinterpret_cast<float*>(base + round_up256(static_cast<size_t>(T) * qd.d_model * sizeof(uint16_t)));
   float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(q_raw) +
                                          round_up256(static_cast<size_t>(T) * nq * sizeof(float)));
-  const size_t n4 = static_cast<size_t>(T) * qd.d_model / 4;
-  const unsigned blocks = static_cast<unsigned>(std::min<size_t>((n4 + THREADS - 1) / THREADS, 4096));
-  hipLaunchKernelGGL(conv_kernel, dim3(blocks), dim3(THREADS), 0, s, x,
-                     qd.conv_k > 1 ? x_hist : nullptr, conv_w, y, L, qd.d_model, qd.conv_k, n4);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_conv(x, qd.conv_k > 1 ? x_hist : nullptr, conv_w, y, T, L, qd.d_model, qd.conv_k, s);
   int splits = 1;
   if (e == hipSuccess) e = gemm_bf16_parts(y, w_q, q_raw, T, nq, qd.d_model, part, s, &splits);
   if (e == hipSuccess)

@@ -101,6 +101,43 @@ CASES = [
 ]
 
 
+@pytest.mark.parametrize("kc", range(1, 9))
+def test_convolution_runs(kc):
+    """Runs of four tokens to a thread (2,048 tokens and more): every tap count, runs that cross from
+    one sequence into the next and end past the last token, with and without a history.  Half a bf16
+    step (2^-8 of the value) and the fp32 sum's error (kc products of order one)."""
+    fe = CF.FrontEnd(f"conv-runs-{kc}", B=3, L=709, d_model=72, conv_k=kc, heads=1, dk=8, shared=True,
+                     seed=30 + kc, history=kc % 2 == 0)
+    inp, _, _, ws = run_query(fe)
+    y = torch.empty(fe.T * fe.d_model, dtype=torch.int16)
+    y.copy_(ws[: fe.T * fe.d_model * 2].view(torch.int16))
+    got = S.bf16_bits_to_f32(y.numpy().view(np.uint16)).reshape(fe.T, fe.d_model).astype(np.float64)
+    ref = Q.causal_conv(inp["x"], inp["conv_w"], inp["hist"]).reshape(fe.T, fe.d_model)
+    assert (np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + kc * 4 * 2.0 ** -23).all()
+
+
+@pytest.mark.parametrize("T,K,N", [(1, 8, 8), (63, 520, 72), (65, 2048, 64), (130, 1024, 200),
+                                   (2036, 2048, 512), (65, 2056, 72)])
+def test_small_tiles(T, K, N):
+    """The 64 x 64 tiles of short products (K <= 2048, too few 128 x 128 tiles for the chip) at their
+    edges, and just past the rule: against fp64 on the bf16-rounded operands, within the bound of an
+    fp32 sum of K products (K 2^-23 of the sum of their magnitudes)."""
+    log(f"[case] small tiles T={T} K={K} N={N}")
+    g = torch.Generator(device="cuda").manual_seed(T + K + N)
+    a = torch.randn((T, 1, K), device="cuda", generator=g)
+    b = torch.randn((N, K), device="cuda", generator=g).to(torch.bfloat16)
+    out = torch.empty((T, N), device="cuda")
+    st, nws = U.umem_project_workspace_size(T, 1, K, 0, N)
+    U.check(st)
+    ws = torch.empty(max(nws, 256), dtype=torch.uint8, device="cuda")
+    U.check(U.umem_project(T, 1, K, 0, N, a, None, b.view(torch.int16), out, ws, ws.numel()))
+    torch.cuda.synchronize()
+    A = a[:, 0].to(torch.bfloat16).double()
+    Bt = b.double().t().contiguous()
+    bound = K * 2.0 ** -23 * (A.abs() @ Bt.abs())
+    assert bool(((out.double() - A @ Bt).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("fe", CASES, ids=[c.name for c in CASES])
 def test_query_front_end(fe):
     inp, q_row, q_col, ws = run_query(fe)
