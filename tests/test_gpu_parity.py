@@ -269,6 +269,18 @@ def test_axis_scores_kernels(kw):
         assert err.max() <= 1e-5, (a, err.max())
 
 
+@pytest.mark.parametrize("kw", [
+    dict(dk=96, T=5, n_keys=1001, heads=3),                               # one 16-token block
+    dict(dk=96, T=30, n_keys=66, heads=2, rank=2, grid=CF.GRID_TUCKER),   # two, slices of 48 dims
+    dict(dk=96, T=333, n_keys=1001, heads=3),                             # four, the last ragged
+    dict(dk=96, T=70, n_keys=63, heads=1, rank=3, grid=CF.GRID_TUCKER),
+    dict(dk=448, T=70, n_keys=1793, heads=2),                             # fourteen loads a thread, in two batches
+])
+def test_axis_scores_mfma_widths(kw):
+    """Key widths of the fp32 matrix-core kernel: 96 dims, and its widest query tile."""
+    test_axis_scores_kernels(kw)
+
+
 def _special_cores(rank, rng):
     """Cores whose leading singular pair the fp64 Jacobi sweeps must find in edge conditions: a
     diagonal core (nothing to rotate), a zero column (rank-deficient), leading singular values
