@@ -103,10 +103,12 @@ struct Chunk<uint16_t> {   // bf16 bit patterns
 // each piece is one wave's work, so that a row chosen by thousands of tokens does not leave one
 // wave walking them all.  The piece starts are listed in order (counted per chunk, then written
 // from the sum of the earlier chunks' counts), and a fixed grid of waves walks the list.  A piece
-// that starts its run adds its sum into its row; one that continues it (the first piece of
-// segment g = positions [g kSeg, (g + 1) kSeg)) stores its partial row in slot g, and
-// seg_join_kernel adds, for each run spanning segments, the partial rows of its later segments, in
-// order.
+// that is a whole run adds its sum into its row; one that continues its run (the first piece of
+// segment g = positions [g kSeg, (g + 1) kSeg)) stores its partial row in slot g; one that starts a
+// run that goes on stores its partial row in the gradient row itself where that is written from
+// zero (compact form), else in slot g of its own (`heads_part`), so that what the row held takes one
+// rounding.  seg_join_kernel adds, for each run spanning segments, its head and the partial rows of
+// its later segments, in order, into the row.
 constexpr int kSeg = kWave;
 
 // Where sorted position i (< n) stands in its run.
@@ -561,8 +563,8 @@ __global__ __launch_bounds__(THREADS) void row_bwd_kernel(
     const uint2* __restrict__ sorted, const uint32_t* __restrict__ n_sorted,
     const uint2* __restrict__ rec, const uint32_t* __restrict__ info, const float* __restrict__ w,
     int cores, int dv, size_t pooled_rows, const float* __restrict__ d_pooled, float* __restrict__ out, int compact,
-    float* __restrict__ partial, const uint32_t* __restrict__ list, uint32_t* __restrict__ counts,
-    uint32_t* __restrict__ heads) {
+    float* __restrict__ partial, float* __restrict__ heads_part, const uint32_t* __restrict__ list,
+    uint32_t* __restrict__ counts, uint32_t* __restrict__ heads) {
   constexpr int S = kWave / GL, kCols = 4 * GL;
   const int lane = threadIdx.x & (kWave - 1);
   const int sub = lane / GL;
@@ -614,7 +616,7 @@ __global__ __launch_bounds__(THREADS) void row_bwd_kernel(
         float* dst = out + static_cast<size_t>(run) * dv + col;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         f32x4 old = {0.f, 0.f, 0.f, 0.f};
-        if (starts && !compact && sub == 0) old = *reinterpret_cast<const f32x4*>(dst);
+        if (starts && ends && !compact && sub == 0) old = *reinterpret_cast<const f32x4*>(dst);
         for (int j0 = 0; j0 < n_e; j0 += S * kRowInFlight) {  // wave-uniform
           f32x4 v[kRowInFlight];
           float wt[kRowInFlight];
@@ -647,20 +649,21 @@ __global__ __launch_bounds__(THREADS) void row_bwd_kernel(
           acc.w += __shfl_xor(acc.w, off, kWave);
         }
         if (sub == 0) {
-          if (starts) *reinterpret_cast<f32x4*>(dst) = old + acc;
-          else *reinterpret_cast<f32x4*>(partial + static_cast<size_t>(ps / kSeg) * dv + col) = acc;
+          if (starts && (ends || compact)) *reinterpret_cast<f32x4*>(dst) = old + acc;
+          else *reinterpret_cast<f32x4*>((starts ? heads_part : partial) + static_cast<size_t>(ps / kSeg) * dv + col) = acc;
         }
       }
     }
   }
 }
 
-// One wave per run that spans segments: the partial rows of its later segments, in order, added
-// into the row, which holds the sum of its first piece.
+// One wave per run that spans segments: its head (heads_part, or what the row holds: compact form)
+// and the partial rows of its later segments, in order, added into the row.
 // heads: the places in list of those runs' first pieces.
 __global__ __launch_bounds__(THREADS) void seg_join_kernel(const uint2* __restrict__ sorted,
                                                            const uint32_t* __restrict__ n_sorted,
                                                            int width, const float* __restrict__ partial,
+                                                           const float* __restrict__ heads_part,
                                                            float* __restrict__ out,
                                                            const uint32_t* __restrict__ list,
                                                            const uint32_t* __restrict__ heads,
@@ -688,11 +691,11 @@ __global__ __launch_bounds__(THREADS) void seg_join_kernel(const uint2* __restri
     }
     for (int c = lane * 4; c < width; c += kWave * 4) {
       f32x4* d = reinterpret_cast<f32x4*>(dst + c);
-      const f32x4 head = *d;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      const f32x4 held = *d;
+      f32x4 acc = info != nullptr ? held : *reinterpret_cast<const f32x4*>(heads_part + static_cast<size_t>(g0) * width + c);
       for (int g = g0 + 1; g <= g1; ++g)
         acc += *reinterpret_cast<const f32x4*>(partial + static_cast<size_t>(g) * width + c);
-      *d = head + acc;
+      *d = info != nullptr ? acc : held + acc;
     }
   }
 }
@@ -1036,7 +1039,7 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
     const uint2* __restrict__ sorted, const uint32_t* __restrict__ n_sorted,
     const float* __restrict__ edS, const float* __restrict__ q_row, const float* __restrict__ q_col,
     float* __restrict__ dk_row, float* __restrict__ dk_col, int H, int n, int dk, int rank, int m,
-    float* __restrict__ partial, const uint32_t* __restrict__ list,
+    float* __restrict__ partial, float* __restrict__ heads_part, const uint32_t* __restrict__ list,
     uint32_t* __restrict__ counts, uint32_t* __restrict__ heads) {
   const int lane = threadIdx.x & (kWave - 1);
   const uint32_t n_pieces = counts[0];
@@ -1064,7 +1067,8 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
   const int width = dk / rank;
   const int n_e = pe - ps;
   const uint32_t my_slot = lane < n_e ? sorted[ps + lane].y : 0u;   // one entry per lane
-  float* const part_row = partial + static_cast<size_t>(ps / kSeg) * dk;
+  const bool whole = run_start && run_end;
+  float* const part_row = (run_start ? heads_part : partial) + static_cast<size_t>(ps / kSeg) * dk;
   if (dk <= 2 * kWave && (dk & (dk - 1)) == 0) {
     // Rows of at most 128 dims fill a fraction of the wave: G = dk / 4 lanes take one entry, and
     // the wave's S = 64 / G lane groups take entries s, s + S, s + 2 S, ... of the piece, each
@@ -1073,7 +1077,7 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
     const int sub = lane / G, d = (lane % G) * 4;
     const int r = d / width;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    const f32x4 old = (run_start && sub == 0) ? *reinterpret_cast<const f32x4*>(dK + d) : f32x4{0.f, 0.f, 0.f, 0.f};
+    const f32x4 old = (whole && sub == 0) ? *reinterpret_cast<const f32x4*>(dK + d) : f32x4{0.f, 0.f, 0.f, 0.f};
     for (int j0 = 0; j0 < n_e; j0 += S * kInFlight) {   // wave-uniform
       f32x4 qv[kInFlight];
       float ds[kInFlight];
@@ -1104,7 +1108,7 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
       acc.w += __shfl_xor(acc.w, off, kWave);
     }
     if (sub == 0) {
-      if (run_start) *reinterpret_cast<f32x4*>(dK + d) = old + acc;
+      if (whole) *reinterpret_cast<f32x4*>(dK + d) = old + acc;
       else *reinterpret_cast<f32x4*>(part_row + d) = acc;
     }
     continue;
@@ -1114,8 +1118,8 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
     const bool active = d < dk;
     const int r = active ? d / width : 0;             // four consecutive dims lie in one slice
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    // a piece that starts its run adds into its key's gradient row: read it now, under the entries' loads
-    const f32x4 old = (active && run_start) ? *reinterpret_cast<const f32x4*>(dK + d) : f32x4{0.f, 0.f, 0.f, 0.f};
+    // a whole run adds into its key's gradient row: read it now, under the entries' loads
+    const f32x4 old = (active && whole) ? *reinterpret_cast<const f32x4*>(dK + d) : f32x4{0.f, 0.f, 0.f, 0.f};
     for (int j0 = 0; j0 < n_e; j0 += 2 * kInFlight) {  // wave-uniform
       f32x4 qv[2 * kInFlight];
       float ds[2 * kInFlight];
@@ -1141,7 +1145,7 @@ __global__ __launch_bounds__(THREADS) void key_bwd_seg_kernel(
       }
     }
     if (!active) continue;
-    if (run_start) *reinterpret_cast<f32x4*>(dK + d) = old + acc;
+    if (whole) *reinterpret_cast<f32x4*>(dK + d) = old + acc;
     else *reinterpret_cast<f32x4*>(part_row + d) = acc;
   }
   }
@@ -1174,8 +1178,8 @@ int bits_for(int64_t n) {
 
 }  // namespace
 
-// [entry info: M words][segment heads][counts][chunk counts][partial rows][as many again, for
-// d_pooled by column slice][sort: its pairs, the dead half of which holds the entries' records, and
+// [entry info: M words][segment heads][counts][chunk counts][partial rows][as many again: the heads'
+// partial rows (dense form) or d_pooled by column slice (compact form)][sort: its pairs, the dead half of which holds the entries' records, and
 // M spare words, which hold the piece list: runs of several entries alone are cut into pieces, at
 // most M / 2 + nseg of them]
 size_t gather_backward_workspace_bytes(int T, int bag, int dv) {
@@ -1209,9 +1213,8 @@ hipError_t launch_tokens(const Elem* values, uint32_t n_values, int dv, int T, i
     while (T * NWAVES * split < kTokenWaves && bag * CW >= 4 * NWAVES * 2 * split) split *= 2;    \
     const dim3 grid(T, split);                                                                    \
     constexpr bool SL = LL == kWave;                                                              \
-    if (SL && sliced != nullptr && dense) UMEM_TOKENS_AS(LL, CC, CW, SL, true);                   \
+    if (dense) UMEM_TOKENS_AS(LL, CC, CW, false, true);                                           \
     else if (SL && sliced != nullptr) UMEM_TOKENS_AS(LL, CC, CW, SL, false);                      \
-    else if (dense) UMEM_TOKENS_AS(LL, CC, CW, false, true);                                      \
     else UMEM_TOKENS_AS(LL, CC, CW, false, false);                                                \
   } while (0)
   switch (chunks) {
@@ -1271,7 +1274,8 @@ hipError_t launch_gather_backward(int64_t n_values, int dv, int vdtype, const vo
   base += round_up256(list_chunks(M) * sizeof(uint2));
   float* partial = reinterpret_cast<float*>(base);
   base += round_up256(nseg * dv * sizeof(float));
-  float* sliced = reinterpret_cast<float*>(base);
+  float* const heads_part = reinterpret_cast<float*>(base);
+  float* sliced = heads_part;
   base += round_up256(nseg * dv * sizeof(float));
   const SortPlan sp = sort_plan(M, bits_for(n_values), base);
   const int32_t* pm = expand > 1 ? perm : nullptr;
@@ -1292,13 +1296,14 @@ hipError_t launch_gather_backward(int64_t n_values, int dv, int vdtype, const vo
                      chunk_cnt, list, counts, ri);
   // rows repeat from a quarter as many entries as rows on (the gather's rule for cached loads).  The
   // copy by column slice pays where rows repeat and d_pooled is beyond an L2; it needs rows of 64
-  // lanes (1 KiB) and room beside the partial rows
+  // lanes (1 KiB) and room beside the partial rows (which the dense form's heads take)
   const bool keep = 4 * static_cast<int64_t>(M) >= n_values;
   const int64_t pooled_rows = static_cast<int64_t>(T) * expand;
-  if (!(keep && dv * (vdtype == UMEM_F32 ? 4 : 2) >= 1024 && pooled_rows <= static_cast<int64_t>(nseg) &&
-        pooled_rows * dv * 4 > (INT64_C(4) << 20)))
-    sliced = nullptr;
-  const int cols = sliced != nullptr ? slice_columns(pooled_rows, dv) : std::min(dv, 256);
+  const bool slices = keep && dv * (vdtype == UMEM_F32 ? 4 : 2) >= 1024 && pooled_rows <= static_cast<int64_t>(nseg) &&
+                      pooled_rows * dv * 4 > (INT64_C(4) << 20);
+  if (!(slices && compact)) sliced = nullptr;
+  // (the dense form takes the compact form's columns at a time too: the same sums, bit for bit)
+  const int cols = slices ? slice_columns(pooled_rows, dv) : std::min(dv, 256);
   e = vdtype == UMEM_F32
           ? launch_tokens(static_cast<const float*>(values), nv, dv, T, bag, idx, w, pm, expand, c,
                           d_pooled, info, d_values, !compact, dw, sliced, cols, s)
@@ -1308,7 +1313,8 @@ hipError_t launch_gather_backward(int64_t n_values, int dv, int vdtype, const vo
 #define UMEM_ROWS(GL, SLICED)                                                                      \
   hipLaunchKernelGGL((row_bwd_kernel<GL, SLICED>), dim3(kRowWaves / NWAVES), dim3(THREADS), 0, s,  \
                      sorted, sp.n, rec, info, w, c, dv, static_cast<size_t>(pooled_rows),           \
-                     SLICED ? sliced : d_pooled, d_values, compact ? 1 : 0, partial, list, counts, heads)
+                     SLICED ? sliced : d_pooled, d_values, compact ? 1 : 0, partial, heads_part, \
+                     list, counts, heads)
   if (sliced != nullptr) {
     switch (cols) {
       case 32: UMEM_ROWS(8, true); break;
@@ -1330,7 +1336,7 @@ hipError_t launch_gather_backward(int64_t n_values, int dv, int vdtype, const vo
   }
 #undef UMEM_ROWS
   hipLaunchKernelGGL(seg_join_kernel, dim3(kJoinWaves / NWAVES), dim3(THREADS), 0, s, sorted, sp.n, dv,
-                     partial, d_values, list, heads, counts, 0, 0, nullptr, compact ? info : nullptr);
+                     partial, heads_part, d_values, list, heads, counts, 0, 0, nullptr, compact ? info : nullptr);
   return hipGetLastError();
 }
 
@@ -1343,7 +1349,7 @@ size_t score_backward_workspace_bytes(const umem_desc& d, int T) {
   const size_t nseg = (static_cast<size_t>(Mk) + kSeg - 1) / kSeg;
   return round_up256(nseg * sizeof(uint32_t)) + 256 + round_up256(list_chunks(Mk) * sizeof(uint2)) +
          round_up256(static_cast<size_t>(Mk) * d.rank * sizeof(float)) +
-         round_up256(nseg * d.dk * sizeof(float)) + round_up256(th * dc * sizeof(float)) +
+         2 * round_up256(nseg * d.dk * sizeof(float)) + round_up256(th * dc * sizeof(float)) +
          round_up256(sort_workspace_bytes(Mk));
 }
 
@@ -1365,6 +1371,8 @@ hipError_t launch_score_backward(const umem_desc& d, int T, const float* q_row, 
   base += round_up256(static_cast<size_t>(Mk) * r * sizeof(float));
   const size_t nseg = (static_cast<size_t>(Mk) + kSeg - 1) / kSeg;
   float* kpart = reinterpret_cast<float*>(base);
+  base += round_up256(nseg * d.dk * sizeof(float));
+  float* kheads = reinterpret_cast<float*>(base);
   base += round_up256(nseg * d.dk * sizeof(float));
   uint32_t* heads = reinterpret_cast<uint32_t*>(base);
   base += round_up256(nseg * sizeof(uint32_t));
@@ -1399,10 +1407,10 @@ hipError_t launch_score_backward(const umem_desc& d, int T, const float* q_row, 
   hipLaunchKernelGGL(piece_write_kernel<false>, dim3(list_chunks(Mk)), dim3(THREADS), 0, s, sorted,
                      sp.n, chunk_cnt, list, counts, RowInfo{});
   hipLaunchKernelGGL(key_bwd_seg_kernel, dim3(kListWaves / NWAVES), dim3(THREADS), 0, s, sorted, sp.n,
-                     edS, q_row, q_col, dk_row, dk_col, H, d.n_keys, d.dk, r, m, kpart, list, counts,
+                     edS, q_row, q_col, dk_row, dk_col, H, d.n_keys, d.dk, r, m, kpart, kheads, list, counts,
                      heads);
   hipLaunchKernelGGL(seg_join_kernel, dim3(kJoinWaves / NWAVES), dim3(THREADS), 0, s, sorted, sp.n,
-                     d.dk, kpart, dk_row, list, heads, counts, H, d.n_keys, dk_col, nullptr);
+                     d.dk, kpart, kheads, dk_row, list, heads, counts, H, d.n_keys, dk_col, nullptr);
   if (tucker)   // dC: the per-token partials [T][H dc], summed over tokens into dcore
     hipLaunchKernelGGL(sum_cols_kernel, dim3(H * dc), dim3(THREADS), 0, s, dc_part, dcore, T, H * dc);
   return hipGetLastError();
