@@ -89,10 +89,6 @@ __device__ __forceinline__ double key64_value(uint64_t k) {
   return __longlong_as_double(static_cast<long long>(raw));
 }
 
-__device__ __forceinline__ float key32_value(uint32_t k) {
-  return __uint_as_float((k >> 31) ? (k & 0x7FFFFFFFu) : ~k);
-}
-
 // Composite key of an axis element: larger = earlier in (score desc, index asc).
 __device__ __forceinline__ uint64_t axis_comp(uint32_t key, int idx) {
   return (static_cast<uint64_t>(key) << 32) |
@@ -1063,8 +1059,10 @@ __device__ __forceinline__ void wave_axis(f32x4 (&v)[NV], const float* __restric
     const uint32_t g[4] = {order_key(mx[0]), order_key(mx[1]), order_key(mx[2]), order_key(mx[3])};
     L = wave_kth16<4>(g, k);
   }
+  // (an L up to -inf's key, where that many groups hold no number above it, bounds nothing: exact search)
+  const bool limit = key32_is_limit(L);
   int S = 0, Q = 0;
-  if (L != 0u) {
+  if (limit) {
     // first the 16-byte pieces that hold a survivor, then, a piece to a lane, the survivors
     const float lim = key32_value(L);
 #pragma unroll
@@ -1082,7 +1080,7 @@ __device__ __forceinline__ void wave_axis(f32x4 (&v)[NV], const float* __restric
     }
   }
   if (next != nullptr) wave_load<NV>(next, n, v);
-  if (L != 0u) {
+  if (limit) {
     const float lim = key32_value(L);
     wave_lds_order();
     if (Q <= kWavePieces) {
@@ -1104,8 +1102,8 @@ __device__ __forceinline__ void wave_axis(f32x4 (&v)[NV], const float* __restric
       }
     }
   }
-  if (L == 0u || Q > kWavePieces || S > kWaveCap) {
-    // too many survivors (massive ties) or too few numbers: the exact k-th key over all elements,
+  if (S < k || Q > kWavePieces || S > kWaveCap) {
+    // too many survivors (massive ties) or too few (S stays 0 without a limit): the exact k-th key over all elements,
     // then the elements above it and the lowest-indexed ones equal to it.  The scores are read again
     // for every step: kept in registers, the code of a path that hardly ever runs would set the
     // kernel's registers.  The search starts at the highest bit in which any two keys differ.

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "order_keys.h"
 #include "umem.h"
 
 namespace umem {
@@ -152,15 +153,6 @@ hipError_t launch_project(int T, int expand, int dv, int dv_virt, int d_out, con
                           hipStream_t s);
 
 // ---------------------------------------------------------------- device helpers
-
-// Monotone map of a float to an unsigned key: larger float -> larger key.  -0.0 maps like +0.0
-// and NaN maps to 0, below every number including -inf.
-__device__ __forceinline__ uint32_t order_key(float x) {
-  if (x != x) return 0u;
-  uint32_t u = __float_as_uint(x);
-  if ((u << 1) == 0u) u = 0u;
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
 
 __device__ __forceinline__ int wave_inclusive_scan(int v) {
   const int lane = threadIdx.x & (kWave - 1);

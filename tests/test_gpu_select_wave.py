@@ -65,6 +65,12 @@ def scores(kind, cfg, g):
         sel[..., ::3] = float("-inf")
         sel[:, ::5, :, 7] = float("inf")
         sel[:, ::7, :, 11] = float("nan")
+    elif kind == "masked":                            # -inf but for a few keys: fewer than the top-k, then
+        sel[:, ::2, :, max(1, cfg.topk // 2):] = float("-inf")             # more, on few lanes
+        sel[:, 1::2, :, 100:] = float("-inf")
+    elif kind == "all masked":
+        sel[..., :] = float("-inf")
+        sel[:, ::3, :, 5:9] = float("nan")
     elif kind == "lowest":                            # a mask of the type's lowest value
         sel[..., 3:] = torch.finfo(torch.float32).min
     return sel
@@ -75,7 +81,7 @@ ADDITIVE = [(2048, 1, 512, 32, 32), (1030, 2, 1024, 33, 64), (700, 3, 772, 1, 1)
             (4097, 2, 4480, 32, 32), (2049, 1, 2044, 60, 40)]
 
 
-@pytest.mark.parametrize("kind", ["normal", "ties", "equal", "few", "inf", "lowest"])
+@pytest.mark.parametrize("kind", ["normal", "ties", "equal", "few", "inf", "lowest", "masked", "all masked"])
 @pytest.mark.parametrize("T,heads,n,k,m", ADDITIVE)
 def test_additive(T, heads, n, k, m, kind):
     print(f"[case] wave additive T={T} H={heads} n={n} k={k} m={m} {kind}", flush=True)
@@ -90,7 +96,7 @@ TUCKER = [(512, 4, 2048, 64, 64, 2, 1, 128), (1024, 2, 1792, 42, 42, 2, 2, 448),
           (700, 3, 1020, 16, 1, 1, 1, 20), (1024, 2, 2048, 64, 64, 1, 1, 64), (4097, 2, 4480, 30, 50, 2, 4, 40)]
 
 
-@pytest.mark.parametrize("kind", ["normal", "ties", "zero", "near-rank-1", "nan"])
+@pytest.mark.parametrize("kind", ["normal", "ties", "zero", "near-rank-1", "nan", "masked", "all masked"])
 @pytest.mark.parametrize("T,heads,n,k,m,rank,cores,dk", TUCKER)
 def test_tucker(T, heads, n, k, m, rank, cores, dk, kind):
     print(f"[case] wave Tucker T={T} H={heads} n={n} k={k} m={m} r={rank} h={cores} dk={dk} {kind}", flush=True)
@@ -117,4 +123,6 @@ def test_tucker(T, heads, n, k, m, rank, cores, dk, kind):
     sel = torch.stack([sum(torch.einsum("thd,hnd->thn", x[..., r * width:(r + 1) * width].double(),
                                         y[..., r * width:(r + 1) * width].double()) for r in range(rank)).float()
                        for x, y in zip(q, K)])
+    if kind.endswith("masked"):                       # as "masked" and "all masked" above
+        sel = torch.minimum(sel, scores(kind, cfg, g))
     check(cfg, sel.contiguous(), q, K, core, axis=(k % 2 == 1))
