@@ -1477,8 +1477,9 @@ __global__ __launch_bounds__(wave_items(TUCKER) * kWave, NV <= 12 ? 4 : 3) void 
       mxk[c] = order_key(static_cast<float>(mx));
     }
     const uint32_t L = wave_kth16<8>(mxk, m);
+    const bool limit = key32_is_limit(L);                 // (else the exact search, as for an axis)
     int Q = 0;
-    if (L != 0u) {
+    if (limit) {
       // first the sets that hold a survivor, then, a set to a lane, the survivors
       const float lim = key32_value(L);
 #pragma unroll
@@ -1507,7 +1508,7 @@ __global__ __launch_bounds__(wave_items(TUCKER) * kWave, NV <= 12 ? 4 : 3) void 
         }
       }
     }
-    if (L != 0u && Q <= kWavePieces && S > kWaveCap && S <= 2 * kWaveCap) {
+    if (limit && Q <= kWavePieces && S > kWaveCap && S <= 2 * kWaveCap) {
       // sets of a few columns that hold most of the grid's best (a core close to rank one): the m-th
       // largest rounding of all survivors takes the threshold's place (skey and sidx hold the keys)
       wave_lds_order();
@@ -1537,10 +1538,10 @@ __global__ __launch_bounds__(wave_items(TUCKER) * kWave, NV <= 12 ? 4 : 3) void 
       }
       S = kept;
     }
-    if (L == 0u || Q > kWavePieces || S > kWaveCap) {
-      // massive ties, or fewer than m numbers: the exact m-th largest fp64 key, then the lowest
-      // slots among the candidates equal to it.  The searches start at the highest bit in which any
-      // two keys (any slot) can differ.
+    if (S < m || Q > kWavePieces || S > kWaveCap) {
+      // massive ties, or fewer than m sets with a number above fp32's -inf: the exact m-th largest fp64
+      // key, then the lowest slots among the candidates equal to it.  The searches start at the highest
+      // bit in which any two keys (any slot) can differ.
       const bool on = lane < k;
       uint64_t hi = 0ull, lo = ~0ull;
       for (int a = 0; a < k; ++a) {

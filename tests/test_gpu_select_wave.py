@@ -96,7 +96,8 @@ TUCKER = [(512, 4, 2048, 64, 64, 2, 1, 128), (1024, 2, 1792, 42, 42, 2, 2, 448),
           (700, 3, 1020, 16, 1, 1, 1, 20), (1024, 2, 2048, 64, 64, 1, 1, 64), (4097, 2, 4480, 30, 50, 2, 4, 40)]
 
 
-@pytest.mark.parametrize("kind", ["normal", "ties", "zero", "near-rank-1", "nan", "masked", "all masked"])
+@pytest.mark.parametrize("kind", ["normal", "ties", "zero", "near-rank-1", "nan", "masked", "all masked", "huge",
+                                  "overflow"])
 @pytest.mark.parametrize("T,heads,n,k,m,rank,cores,dk", TUCKER)
 def test_tucker(T, heads, n, k, m, rank, cores, dk, kind):
     print(f"[case] wave Tucker T={T} H={heads} n={n} k={k} m={m} r={rank} h={cores} dk={dk} {kind}", flush=True)
@@ -119,10 +120,20 @@ def test_tucker(T, heads, n, k, m, rank, cores, dk, kind):
     elif kind == "nan":
         q[0][::3] = float("nan")
         K[1][:, ::2] = float("nan")
+    elif kind == "huge":                              # grid scores beyond fp32: all below, or all but one
+        q = [x.abs() * 1e18 for x in q]               # column's
+        K = [x.abs() * 1e18 for x in K]
+        K[1][1:, 5] *= -1.5
+        core.fill_(-1.0)
+    elif kind == "overflow":                          # per-slice scores beyond fp32
+        q = [x * 1e20 for x in q]
+        K = [x * 1e20 for x in K]
     width = dk // rank
     sel = torch.stack([sum(torch.einsum("thd,hnd->thn", x[..., r * width:(r + 1) * width].double(),
                                         y[..., r * width:(r + 1) * width].double()) for r in range(rank)).float()
                        for x, y in zip(q, K)])
+    if kind == "huge":
+        sel.abs_()
     if kind.endswith("masked"):                       # as "masked" and "all masked" above
         sel = torch.minimum(sel, scores(kind, cfg, g))
     check(cfg, sel.contiguous(), q, K, core, axis=(k % 2 == 1))

@@ -80,6 +80,20 @@ int main() {
           for (float v : x) survivors += v >= key32_value(L);
           if (survivors < k) return bad("survivors", L, survivors);
         }
+  // a Tucker grid of 64 x 64 fp64 scores, 512 maxima over eight rows of a column, rounded to fp32
+  for (double rest : {-1e300, -1e39, -static_cast<double>(INFINITY), static_cast<double>(NAN)})
+    for (double best : {1e300, 1.0, -1e38, -1e300})
+      for (int cols : {0, 1, 7, 8, 9, 64})
+        for (int m : {1, 8, 64}) {
+          std::vector<uint32_t> mx(512);
+          for (int i = 0; i < 512; ++i) mx[i] = order_key(static_cast<float>(i % 64 < cols ? best : rest));
+          const uint32_t L = kth16(mx, m);
+          if (!key32_is_limit(L)) continue;
+          int survivors = 0;
+          for (int i = 0; i < 4096; ++i)
+            survivors += static_cast<float>(i % 64 < cols ? best : rest) >= key32_value(L);
+          if (survivors < m) return bad("grid survivors", L, survivors);
+        }
   puts("ok");
   return 0;
 }
