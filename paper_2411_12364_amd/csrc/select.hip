@@ -1030,6 +1030,111 @@ __device__ __forceinline__ void wave_top_sorted(const WaveLds& s, int S, int k, 
     }
 }
 
+// The k largest of src[0, n) (score desc, index asc) to s.skey / s.sidx[0, k), in no order: the k-th key
+// by histograms of its four bytes in LDS, then the elements above it and the lowest-indexed ones equal
+// to it.  Bound by latency: five passes over scores that the caches hold, four 16-byte loads in flight
+// a lane (in registers they would set the whole kernel's).  2,048 Tucker pairs of 2,048 keys with all but
+// 100 masked: 52 us (37 with no key masked; 81 in the workgroup kernel), 508 when the search took a pass
+// of single loads a bit; 8,192 additive pairs of 4,480 keys 263 us (299), before 5,914.
+__device__ __forceinline__ void wave_axis_exact(const float* __restrict__ src, int n, int k, const WaveLds& s) {
+  constexpr int kLoads = 4;
+  int lane = threadIdx.x & (kWave - 1);
+  asm("" : "+v"(lane));                                   // (no address of the caller's kept for this)
+  const int steps = (n + 255) / 256;
+  uint32_t* const bins = s.skey;                          // [256]
+  uint32_t theta = 0u;                                    // the k-th key's bytes so far
+  int want = k, above = 0;                                // rank among the keys of these bytes, keys above
+  auto load = [&](int j0, f32x4 (&x)[kLoads]) {
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u)
+      x[u] = *reinterpret_cast<const f32x4*>(src + min(256 * (j0 + u) + 4 * lane, n - 4));
+  };
+  bool all = false;                                       // exactly k keys reach theta
+#pragma unroll 1
+  for (int shift = 24; shift >= 0 && !all; shift -= 8) {
+    const uint32_t known = shift == 24 ? 0u : ~0u << (shift + 8);
+    *reinterpret_cast<uint4*>(bins + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
+    wave_lds_order();
+#pragma unroll 1
+    for (int j0 = 0; j0 < steps; j0 += kLoads) {
+      f32x4 x[kLoads];
+      load(j0, x);
+#pragma unroll
+      for (int u = 0; u < kLoads; ++u) {
+        const bool in = 256 * (j0 + u) + 4 * lane < n;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t key = order_key(x[u][e]), digit = (key >> shift) & 255u;
+          const uint64_t m = __ballot(in && ((key ^ theta) & known) == 0u);
+          if (m == 0ull) continue;                        // (wave-uniform)
+          // equal digits (ties, a mask) add once
+          const int lead = __builtin_ctzll(m);
+          const uint32_t d0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(digit), lead));
+          if ((__ballot(digit != d0) & m) == 0ull) {
+            if (lane == lead) atomicAdd(bins + d0, static_cast<uint32_t>(__popcll(m)));
+          } else if ((m >> lane) & 1ull) {
+            atomicAdd(bins + digit, 1u);
+          }
+        }
+      }
+    }
+    wave_lds_order();
+    const uint4 c = *reinterpret_cast<const uint4*>(bins + 4 * lane);
+    const int sum = static_cast<int>(c.x + c.y + c.z + c.w);
+    const int incl = wave_scan_dpp(sum), total = __builtin_amdgcn_readlane(incl, kWave - 1);
+    const int at = __builtin_ctzll(__ballot(total - incl < want && total - incl + sum >= want));
+    int over = total - __builtin_amdgcn_readlane(incl, at);       // keys of these bytes in higher bins
+    int bin = 3, held = __builtin_amdgcn_readlane(static_cast<int>(c.w), at);
+    if (over + held < want) over += held, bin = 2, held = __builtin_amdgcn_readlane(static_cast<int>(c.z), at);
+    if (over + held < want) over += held, bin = 1, held = __builtin_amdgcn_readlane(static_cast<int>(c.y), at);
+    if (over + held < want) over += held, bin = 0, held = __builtin_amdgcn_readlane(static_cast<int>(c.x), at);
+    theta |= static_cast<uint32_t>(4 * at + bin) << shift;
+    want -= over;
+    above += over;
+    all = held == want;
+    wave_lds_order();                                     // before the next pass clears the bins
+  }
+  // greater keys from the front, equal ones from the back (their ranks in index order)
+  const int need = all ? k : want;
+  int pos = 0, seen = 0;
+#pragma unroll 1
+  for (int j0 = 0; j0 < steps; j0 += kLoads) {
+    f32x4 x[kLoads];
+    load(j0, x);
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int i = 256 * (j0 + u) + 4 * lane;
+      uint32_t key[4];
+      uint64_t eq[4];
+      int rank = seen;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        key[e] = order_key(x[u][e]);
+        const bool hit = i < n && key[e] > theta;
+        const uint64_t m = __ballot(hit);
+        if (hit) {
+          const int at = pos + mask_rank(m);
+          s.skey[at] = key[e];
+          s.sidx[at] = static_cast<uint32_t>(i + e);
+        }
+        pos += __popcll(m);
+        eq[e] = __ballot(i < n && key[e] == theta);
+        rank += mask_rank(eq[e]);
+        seen += __popcll(eq[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool mine = (eq[e] >> lane) & 1ull;
+        if (mine && rank < need) {
+          s.skey[k - 1 - rank] = theta;
+          s.sidx[k - 1 - rank] = static_cast<uint32_t>(i + e);
+        }
+        rank += mine;
+      }
+    }
+  }
+}
+
 // One axis: the top-k of src[0, n), which is in v, to ax (a set, or in order with their scores to sc).
 // Once the survivors' pieces are in LDS v takes the next axis's scores, which land under the rest.
 template <int NV>
@@ -1103,56 +1208,8 @@ __device__ __forceinline__ void wave_axis(f32x4 (&v)[NV], const float* __restric
     }
   }
   if (S < k || Q > kWavePieces || S > kWaveCap) {
-    // too many survivors (massive ties) or too few (S stays 0 without a limit): the exact k-th key over all elements,
-    // then the elements above it and the lowest-indexed ones equal to it.  The scores are read again
-    // for every step: kept in registers, the code of a path that hardly ever runs would set the
-    // kernel's registers.  The search starts at the highest bit in which any two keys differ.
-    const int steps = (n + kWave - 1) / kWave;
-    auto key_of = [&](int i) { return order_key(src[min(i, n - 1)]); };
-    uint32_t hi = 0u, lo = 0xFFFFFFFFu;
-#pragma unroll 1
-    for (int j = 0; j < steps; ++j) {                     // (the clamped tail repeats the last element)
-      const uint32_t key = key_of(kWave * j + lane);
-      hi = max(hi, key);
-      lo = min(lo, key);
-    }
-#pragma unroll 1
-    for (int off = 1; off < kWave; off <<= 1) {
-      hi = max(hi, static_cast<uint32_t>(__shfl_xor(static_cast<int>(hi), off, kWave)));
-      lo = min(lo, static_cast<uint32_t>(__shfl_xor(static_cast<int>(lo), off, kWave)));
-    }
-    const int top = hi == lo ? -1 : 31 - __builtin_clz(hi ^ lo);
-    uint32_t theta = top < 0 ? hi : (top == 31 ? 0u : hi >> (top + 1) << (top + 1));
-    int gt = 0;                                           // keys above theta
-#pragma unroll 1
-    for (int b = top; b >= -1; --b) {
-      const uint32_t c = b < 0 ? theta : theta | (1u << b);
-      int cnt = 0;
-#pragma unroll 1
-      for (int j = 0; j < steps; ++j) {
-        const int i = kWave * j + lane;
-        const uint32_t key = key_of(i);
-        cnt += __popcll(__ballot(i < n && (b < 0 ? key > c : key >= c)));
-      }
-      if (b < 0) gt = cnt;
-      else if (cnt >= k) theta = c;
-    }
-    int need = k - gt, pos = 0;
-#pragma unroll 1
-    for (int j = 0; j < steps; ++j) {                     // in index order
-      const int i = kWave * j + lane;
-      const uint32_t key = key_of(i);
-      const uint64_t eq = __ballot(i < n && key == theta);
-      const bool take = i < n && (key > theta || (key == theta && mask_rank(eq) < need));
-      need -= min(need, __popcll(eq));
-      const uint64_t m = __ballot(take);
-      if (take) {
-        const int at = pos + mask_rank(m);
-        s.skey[at] = key;
-        s.sidx[at] = static_cast<uint32_t>(i);
-      }
-      pos += __popcll(m);
-    }
+    // too many survivors (massive ties) or too few (S stays 0 without a limit)
+    wave_axis_exact(src, n, k, s);
     S = k;
   }
   S = __builtin_amdgcn_readfirstlane(S);
