@@ -837,14 +837,14 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
 //    largest of 64 G lane maxima (G = 2 for k <= 32, else 4); survivors go to LDS by ballot.
 //  * The Tucker grid needs the top-k only as a set: the k-th key of the survivors is found by a
 //    ballot per key bit.  The additive grid needs it in order: every lane counts the keys above its
-//    own (32-bit compares; equal keys are found by two lanes claiming one rank, and ranked again
-//    with their indices).
+//    own (32-bit compares; equal keys are found by two lanes claiming one rank, and the lower indices
+//    among them counted too).  More than 128 survivors are first cut to the top-k as a set.
 //  * Tucker: exact per-slice scores as in the workgroup kernel (the same lanes per row and the same
 //    order of additions); a lane then takes a column and walks the rows, whose scores it reads from
 //    LDS as doubles; the threshold is the m-th largest of the 512 maxima over eight rows of a column,
 //    and only the columns' sets of eight rows that reach it are looked into.
-//  * The final rank compares fp64 scores; NaNs and equal scores (claims, as above) take the ordered
-//    compare by (key, slot).
+//  * The final rank compares fp64 scores, and counts the lower slots among equal scores where claims
+//    (as above) show any; with NaNs it takes the ordered compare by (key, slot).
 // Whatever the fast steps cannot hold (more than kWaveCap survivors, fewer than k or m numbers) goes
 // to exact searches over all elements, as in the workgroup kernel.
 constexpr int kWaveCap = 256;            // survivors of an axis or of the grid
@@ -941,7 +941,8 @@ __device__ __forceinline__ uint32_t wave_kth32(const uint32_t (&v)[R], int k) {
   return p;
 }
 
-// The set of the k largest of the S survivors (key desc, index asc) to ax[0, k), in survivor order.
+// The set of the k largest of the S survivors (key desc, index asc), in survivor order: their indices to
+// ax[0, k), or, without ax, they become the survivors [0, k).
 template <int R>
 __device__ __forceinline__ void wave_top_set(const WaveLds& s, int S, int k, int32_t* ax) {
   const int lane = threadIdx.x & (kWave - 1);
@@ -978,7 +979,11 @@ __device__ __forceinline__ void wave_top_set(const WaveLds& s, int S, int k, int
   for (int r = 0; r < R; ++r) {
     const bool take = idx[r] != 0xFFFFFFFFu && (key[r] > theta || (key[r] == theta && idx[r] <= ylim));
     const uint64_t m = __ballot(take);
-    if (take) ax[pos + mask_rank(m)] = static_cast<int32_t>(idx[r]);
+    if (take && ax != nullptr) ax[pos + mask_rank(m)] = static_cast<int32_t>(idx[r]);
+    if (take && ax == nullptr) {
+      s.skey[pos + mask_rank(m)] = key[r];
+      s.sidx[pos + mask_rank(m)] = idx[r];
+    }
     pos += __popcll(m);
   }
 }
@@ -996,7 +1001,10 @@ __device__ __forceinline__ void wave_top_sorted(const WaveLds& s, int S, int k, 
     idx[r] = e < S ? s.sidx[e] : 0u;
     rank[r] = 0;
   }
-  if (lane < 4 && S + lane < kWaveCap) s.skey[S + lane] = 0u;   // the last group of four compares
+  if (lane < 4 && S + lane < kWaveCap) {                  // the last group of four compares
+    s.skey[S + lane] = 0u;
+    s.sidx[S + lane] = 0xFFFFFFFFu;
+  }
   wave_lds_order();
 #pragma unroll 4
   for (int u = 0; u < S; u += 4) {
@@ -1006,7 +1014,10 @@ __device__ __forceinline__ void wave_top_sorted(const WaveLds& s, int S, int k, 
       rank[r] += static_cast<int>(o.x > key[r]) + static_cast<int>(o.y > key[r]) +
                  static_cast<int>(o.z > key[r]) + static_cast<int>(o.w > key[r]);
   }
-  // equal keys claim one rank: the claim's last writer is one of them, the others see it
+  // equal keys claim one rank: the claim's last writer is one of them, the others see it.  (One pair with
+  // a tie holds up its launch: 2,048 additive pairs of 1,024 normal scores took 27.1 us where this and the
+  // grid's ranks below went entry by entry over up to 256 survivors in four registers a lane, 14.2 now, the
+  // workgroup kernel 18.3; scores in steps of 1/4 44 -> 22, 20 there.)
   bool tie = false;
 #pragma unroll
   for (int r = 0; r < R; ++r)
@@ -1016,10 +1027,13 @@ __device__ __forceinline__ void wave_top_sorted(const WaveLds& s, int S, int k, 
   for (int r = 0; r < R; ++r)
     if (lane + kWave * r < S) tie |= s.code[rank[r]] != static_cast<uint32_t>(lane + kWave * r);
   if (__ballot(tie) != 0ull) {
-    for (int u = 0; u < S; ++u) {
-      const uint32_t ok = s.skey[u], oi = s.sidx[u];
+#pragma unroll 2
+    for (int u = 0; u < S; u += 4) {
+      const uint4 ok = *reinterpret_cast<const uint4*>(s.skey + u), oi = *reinterpret_cast<const uint4*>(s.sidx + u);
 #pragma unroll
-      for (int r = 0; r < R; ++r) rank[r] += static_cast<int>((ok == key[r]) & (oi < idx[r]));
+      for (int r = 0; r < R; ++r)
+        rank[r] += static_cast<int>((ok.x == key[r]) & (oi.x < idx[r])) + static_cast<int>((ok.y == key[r]) & (oi.y < idx[r])) +
+                   static_cast<int>((ok.z == key[r]) & (oi.z < idx[r])) + static_cast<int>((ok.w == key[r]) & (oi.w < idx[r]));
     }
   }
 #pragma unroll
@@ -1043,7 +1057,7 @@ __device__ __forceinline__ void wave_axis_exact(const float* __restrict__ src, i
   const int steps = (n + 255) / 256;
   uint32_t* const bins = s.skey;                          // [256]
   uint32_t theta = 0u;                                    // the k-th key's bytes so far
-  int want = k, above = 0;                                // rank among the keys of these bytes, keys above
+  int want = k;                                           // its rank among the keys of these bytes
   auto load = [&](int j0, f32x4 (&x)[kLoads]) {
 #pragma unroll
     for (int u = 0; u < kLoads; ++u)
@@ -1090,7 +1104,6 @@ __device__ __forceinline__ void wave_axis_exact(const float* __restrict__ src, i
     if (over + held < want) over += held, bin = 0, held = __builtin_amdgcn_readlane(static_cast<int>(c.x), at);
     theta |= static_cast<uint32_t>(4 * at + bin) << shift;
     want -= over;
-    above += over;
     all = held == want;
     wave_lds_order();                                     // before the next pass clears the bins
   }
@@ -1218,8 +1231,13 @@ __device__ __forceinline__ void wave_axis(f32x4 (&v)[NV], const float* __restric
     if (S <= 2 * kWave) wave_top_set<2>(s, S, k, ax);
     else wave_top_set<4>(s, S, k, ax);
   } else {
-    if (!TUCKER && S <= kWave) wave_top_sorted<1>(s, S, k, ax, sc);
-    else wave_top_sorted<4>(s, S, k, ax, sc);
+    if (S > (TUCKER ? 1 : 2) * kWave) {                   // fewer first: a rank costs S compares
+      wave_top_set<4>(s, S, k, nullptr);
+      S = k;
+      wave_lds_order();
+    }
+    if (TUCKER || S <= kWave) wave_top_sorted<1>(s, S, k, ax, sc);
+    else wave_top_sorted<2>(s, S, k, ax, sc);
   }
   wave_lds_order();
 }
@@ -1230,11 +1248,11 @@ template <int R>
 __device__ __forceinline__ void wave_rank_grid(const WaveLds& s, int S, const double (&g)[R],
                                                const int32_t (&id)[R], int (&rank)[R]) {
   const int lane = threadIdx.x & (kWave - 1);
-  bool odd = false;                                       // a NaN, or a rank claimed twice
+  bool nan = false, tie = false;                          // (a tie: a rank claimed twice)
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     rank[r] = 0;
-    odd |= lane + kWave * r < S && g[r] != g[r];
+    nan |= lane + kWave * r < S && g[r] != g[r];
   }
   if (lane == 0 && (S & 1) != 0) s.cg[S] = __builtin_nan("");    // (S < kWaveCap: the second of a pair)
   wave_lds_order();
@@ -1250,23 +1268,35 @@ __device__ __forceinline__ void wave_rank_grid(const WaveLds& s, int S, const do
   wave_lds_order();
 #pragma unroll
   for (int r = 0; r < R; ++r)
-    if (lane + kWave * r < S) odd |= s.code[rank[r]] != static_cast<uint32_t>(lane + kWave * r);
-  if (__ballot(odd) != 0ull) {
-    wave_lds_order();
+    if (lane + kWave * r < S) tie |= s.code[rank[r]] != static_cast<uint32_t>(lane + kWave * r);
+  const bool nans = __ballot(nan) != 0ull;
+  if (!nans && __ballot(tie) == 0ull) return;
+  wave_lds_order();
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (lane + kWave * r < S) s.code[lane + kWave * r] = static_cast<uint32_t>(id[r]);
+  wave_lds_order();
+  if (!nans) {                                            // equal scores: the lower slots first
+#pragma unroll 4
+    for (int u = 0; u < S; u += 2) {                      // (the NaN past an odd S equals nothing)
+      const double2 o = *reinterpret_cast<const double2*>(s.cg + u);
+      const int2 oi = *reinterpret_cast<const int2*>(s.code + u);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        rank[r] += (static_cast<int>(o.x == g[r]) & static_cast<int>(oi.x < id[r])) +
+                   (static_cast<int>(o.y == g[r]) & static_cast<int>(oi.y < id[r]));
+    }
+    return;
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) rank[r] = 0;
+  for (int u = 0; u < S; ++u) {
+    const uint64_t ok = order_key64(s.cg[u]);
+    const int32_t oi = static_cast<int32_t>(s.code[u]);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      rank[r] = 0;
-      if (lane + kWave * r < S) s.code[lane + kWave * r] = static_cast<uint32_t>(id[r]);
-    }
-    wave_lds_order();
-    for (int u = 0; u < S; ++u) {
-      const uint64_t ok = order_key64(s.cg[u]);
-      const int32_t oi = static_cast<int32_t>(s.code[u]);
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const uint64_t me = order_key64(g[r]);
-        rank[r] += static_cast<int>(ok > me) + static_cast<int>((ok == me) & (oi < id[r]));
-      }
+      const uint64_t me = order_key64(g[r]);
+      rank[r] += static_cast<int>(ok > me) + static_cast<int>((ok == me) & (oi < id[r]));
     }
   }
 }
@@ -1641,8 +1671,9 @@ __global__ __launch_bounds__(wave_items(TUCKER) * kWave, NV <= 12 ? 4 : 3) void 
     wave_lds_order();
   }
   S = __builtin_amdgcn_readfirstlane(S);
-  constexpr int kUsual = TUCKER ? 2 : 1;                  // (about 100 and 60 survivors)
-  if (S <= kUsual * kWave) wave_finish<kUsual, TUCKER>(A, s, S, pair, h);
+  // (about 100 survivors of the Tucker grid, 60 of the additive one)
+  if (!TUCKER && S <= kWave) wave_finish<1, TUCKER>(A, s, S, pair, h);
+  else if (S <= 2 * kWave) wave_finish<2, TUCKER>(A, s, S, pair, h);
   else wave_finish<4, TUCKER>(A, s, S, pair, h);
 }
 
