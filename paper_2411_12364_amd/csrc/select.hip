@@ -1048,8 +1048,10 @@ __device__ __forceinline__ void wave_top_sorted(const WaveLds& s, int S, int k, 
 // by histograms of its four bytes in LDS, then the elements above it and the lowest-indexed ones equal
 // to it.  Bound by latency: five passes over scores that the caches hold, four 16-byte loads in flight
 // a lane (in registers they would set the whole kernel's).  2,048 Tucker pairs of 2,048 keys with all but
-// 100 masked: 52 us (37 with no key masked; 81 in the workgroup kernel), 508 when the search took a pass
-// of single loads a bit; 8,192 additive pairs of 4,480 keys 263 us (299), before 5,914.
+// 100 masked: 55 us (32 with no key masked; 81 in the workgroup kernel), 508 when the search took a pass
+// of single loads a bit; 8,192 additive pairs of 4,480 keys 277 us (299), before 5,914.  A pass that finds
+// one key among the candidates (all equal, few distinct scores) ends the search: those pairs with equal
+// scores 463 -> 243 us (312).
 __device__ __forceinline__ void wave_axis_exact(const float* __restrict__ src, int n, int k, const WaveLds& s) {
   constexpr int kLoads = 4;
   int lane = threadIdx.x & (kWave - 1);
@@ -1067,6 +1069,7 @@ __device__ __forceinline__ void wave_axis_exact(const float* __restrict__ src, i
 #pragma unroll 1
   for (int shift = 24; shift >= 0 && !all; shift -= 8) {
     const uint32_t known = shift == 24 ? 0u : ~0u << (shift + 8);
+    uint32_t hi = 0u, nlo = 0u;                           // the largest of these keys, ~ the smallest
     *reinterpret_cast<uint4*>(bins + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
     wave_lds_order();
 #pragma unroll 1
@@ -1079,18 +1082,26 @@ __device__ __forceinline__ void wave_axis_exact(const float* __restrict__ src, i
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const uint32_t key = order_key(x[u][e]), digit = (key >> shift) & 255u;
-          const uint64_t m = __ballot(in && ((key ^ theta) & known) == 0u);
+          const bool mine = in && ((key ^ theta) & known) == 0u;
+          const uint64_t m = __ballot(mine);
           if (m == 0ull) continue;                        // (wave-uniform)
+          hi = max(hi, mine ? key : 0u);
+          nlo = max(nlo, mine ? ~key : 0u);
           // equal digits (ties, a mask) add once
           const int lead = __builtin_ctzll(m);
           const uint32_t d0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(digit), lead));
           if ((__ballot(digit != d0) & m) == 0ull) {
             if (lane == lead) atomicAdd(bins + d0, static_cast<uint32_t>(__popcll(m)));
-          } else if ((m >> lane) & 1ull) {
+          } else if (mine) {
             atomicAdd(bins + digit, 1u);
           }
         }
       }
+    }
+    hi = static_cast<uint32_t>(wave_max_u64(hi));
+    if (hi == ~static_cast<uint32_t>(wave_max_u64(nlo))) {         // one key
+      theta = hi;
+      break;
     }
     wave_lds_order();
     const uint4 c = *reinterpret_cast<const uint4*>(bins + 4 * lane);
