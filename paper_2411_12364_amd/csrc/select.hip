@@ -1608,72 +1608,93 @@ __global__ __launch_bounds__(wave_items(TUCKER) * kWave, NV <= 12 ? 4 : 3) void 
     }
     if (limit && Q <= kWavePieces && S > kWaveCap && S <= 2 * kWaveCap) {
       // sets of a few columns that hold most of the grid's best (a core close to rank one): the m-th
-      // largest rounding of all survivors takes the threshold's place (skey and sidx hold the keys)
+      // largest rounding of all survivors takes the threshold's place
+      constexpr int kPer = 2 * kWaveCap / kWave;
       wave_lds_order();
-      for (int e = lane; e < S; e += kWave) {
-        const int c = s.ab[e];
-        s.skey[e] = order_key(static_cast<float>(score_at(c >> 8, s.pcol[c & 0xFF], s.pcol[64 + (c & 0xFF)])));
+      uint32_t key[kPer], code[kPer];
+#pragma unroll
+      for (int r = 0; r < kPer; ++r) {
+        const int e = lane + kWave * r;
+        code[r] = e < S ? s.ab[e] : 0u;
+        const uint32_t b = code[r] & 0xFFu;
+        key[r] = e < S ? order_key(static_cast<float>(score_at(code[r] >> 8, s.pcol[b], s.pcol[64 + b]))) : 0u;
       }
+      const uint32_t theta = wave_kth32<kPer>(key, m);    // (above 0: they are all numbers)
       wave_lds_order();
-      uint32_t theta = 0u;
-      for (int bit = 31; bit >= 0; --bit) {
-        const uint32_t c = theta | (1u << bit);
-        int cnt = 0;
-        for (int e0 = 0; e0 < S; e0 += kWave) cnt += __popcll(__ballot(e0 + lane < S && s.skey[e0 + lane] >= c));
-        if (cnt >= m) theta = c;
-        if (cnt == m) break;
-      }
-      // (a step of 64 is read before it is written, and written no further than it was read)
-      int kept = 0;
-      for (int e0 = 0; e0 < S; e0 += kWave) {
-        const bool hit = e0 + lane < S && s.skey[e0 + lane] >= theta;
-        const uint16_t c = hit ? s.ab[e0 + lane] : static_cast<uint16_t>(0);
+      S = 0;
+#pragma unroll
+      for (int r = 0; r < kPer; ++r) {
+        const bool hit = key[r] >= theta;
         const uint64_t mk = __ballot(hit);
-        wave_lds_order();
-        if (hit) s.ab[kept + mask_rank(mk)] = c;
-        wave_lds_order();
-        kept += __popcll(mk);
+        if (hit) s.ab[S + mask_rank(mk)] = static_cast<uint16_t>(code[r]);
+        S += __popcll(mk);
       }
-      S = kept;
     }
     if (S < m || Q > kWavePieces || S > kWaveCap) {
-      // massive ties, or fewer than m sets with a number above fp32's -inf: the exact m-th largest fp64
-      // key, then the lowest slots among the candidates equal to it.  The searches start at the highest
-      // bit in which any two keys (any slot) can differ.
+      // Massive ties, or fewer than m sets with a number above fp32's -inf: the exact m-th largest
+      // score, then the lowest slots among the candidates equal to it.  The search for its key starts at
+      // the highest bit in which any two keys differ, and compares the scores as numbers (of NaNs it
+      // knows only how many there are); slots go by row index, then column index.  2,048 Tucker pairs of
+      // k = m = 64 with keys of zeros 77 us (32 with scores all different, 184 in the workgroup kernel),
+      // 394 when every step made 64-bit keys anew and the slots were searched bit by bit.
       const bool on = lane < k;
-      uint64_t hi = 0ull, lo = ~0ull;
+      double hi = nan64, lo = nan64;
+      int numbers = 0;
+#pragma unroll 4
       for (int a = 0; a < k; ++a) {
-        const uint64_t key = order_key64(score(a));
-        hi = on && key > hi ? key : hi;
-        lo = on && key < lo ? key : lo;
+        const double g = score(a);
+        hi = fmax(hi, g);
+        lo = fmin(lo, g);
+        numbers += __popcll(__ballot(g == g));
       }
-      hi = wave_max_u64(hi);
-      lo = ~wave_max_u64(~lo);
-      const int top = hi == lo ? -1 : 63 - __builtin_clzll(hi ^ lo);
-      uint64_t theta = top < 0 ? hi : (top == 63 ? 0ull : hi >> (top + 1) << (top + 1));
-      for (int bit = top; bit >= 0; --bit) {
-        const uint64_t c = theta | (1ull << bit);
-        int cnt = 0;
-        for (int a = 0; a < k; ++a) cnt += __popcll(__ballot(on && order_key64(score(a)) >= c));
-        if (cnt >= m) theta = c;
+      const uint64_t hi_key = wave_max_u64(order_key64(hi)), lo_key = ~wave_max_u64(lo == lo ? ~order_key64(lo) : 0ull);
+      const bool nans = numbers < m;                      // NaNs among the top-m, after every number
+      double theta_at = nan64;
+      if (!nans) {
+        const int top = hi_key == lo_key ? -1 : 63 - __builtin_clzll(hi_key ^ lo_key);
+        uint64_t theta = top < 0 ? hi_key : (top == 63 ? 0ull : hi_key >> (top + 1) << (top + 1));
+#pragma unroll 1
+        for (int bit = top; bit >= 0; --bit) {
+          // (a key below the lowest score's is reached by all; one above the highest's, a number or
+          // not, by none)
+          const uint64_t c = theta | (1ull << bit);
+          const double at = key64_value(c < lo_key ? lo_key : c);
+          int cnt = 0;
+#pragma unroll 4
+          for (int a = 0; a < k; ++a) cnt += __popcll(__ballot(score(a) >= at));
+          theta = cnt >= m ? c : theta;
+          if (cnt == m) break;
+        }
+        theta_at = key64_value(theta < lo_key ? lo_key : theta);
       }
-      int gt = 0;
-      for (int a = 0; a < k; ++a) gt += __popcll(__ballot(on && order_key64(score(a)) > theta));
-      const int need = m - gt;
-      const uint32_t col = static_cast<uint32_t>(s.ax_idx[64 + min(lane, k - 1)]);
-      uint32_t ylim = 0u;
-      for (int bit = 31 - __builtin_clz(static_cast<uint32_t>(A.n) * static_cast<uint32_t>(A.n)); bit >= 0; --bit) {
-        const uint32_t c = ylim | (1u << bit);
-        int below = 0;
-        for (int a = 0; a < k; ++a)
-          below += __popcll(__ballot(on && order_key64(score(a)) == theta &&
-                                     static_cast<uint32_t>(s.ax_idx[a]) * A.n + col < c));
-        if (below < need) ylim = c;
+      int above = 0, ties = 0;                            // lane a: row a's candidates equal to theta
+#pragma unroll 4
+      for (int a = 0; a < k; ++a) {
+        const double g = score(a);
+        above += __popcll(__ballot(nans ? g == g : g > theta_at));
+        const int row_ties = __popcll(__ballot(on && (nans ? g != g : g == theta_at)));
+        ties = lane == a ? row_ties : ties;
       }
+      const int row = s.ax_idx[min(lane, k - 1)], col = s.ax_idx[64 + min(lane, k - 1)];
+      int before = 0;                                     // ties in rows of lower index
+      for (int a = 0; a < k; ++a)
+        before += __builtin_amdgcn_readlane(row, a) < row ? __builtin_amdgcn_readlane(ties, a) : 0;
+      const int quota = max(0, min(ties, m - above - before));
       S = 0;
       for (int a = 0; a < k; ++a) {
-        const uint64_t key = order_key64(score(a));
-        const bool take = on && (key > theta || (key == theta && static_cast<uint32_t>(s.ax_idx[a]) * A.n + col <= ylim));
+        const double g = score(a);
+        const bool tie = on && (nans ? g != g : g == theta_at);
+        const uint64_t mt = __ballot(tie);
+        const int n_take = __builtin_amdgcn_readlane(quota, a);
+        bool take = nans ? g == g : g > theta_at;
+        if (n_take == __popcll(mt)) {                     // (wave-uniform)
+          take = take || tie;
+        } else if (n_take > 0) {                          // the row with the last of them: by column
+          int rank = 0;
+          for (uint64_t x = mt; x != 0ull; x &= x - 1ull)
+            rank += static_cast<int>(__builtin_amdgcn_readlane(col, __builtin_ctzll(x)) < col);
+          take = take || (tie && rank < n_take);
+        }
         const uint64_t mk = __ballot(take);
         if (take) s.ab[S + mask_rank(mk)] = static_cast<uint16_t>((a << 8) | lane);
         S += __popcll(mk);
