@@ -6,12 +6,16 @@
 // The T * bag entries are keyed by physical row and stably sorted (sort.hip), so the entries of
 // one row form a run in their original order.  Most rows of a large table are chosen once, some
 // by thousands of tokens, and the two are separate work:
-//  * token_bwd_kernel walks the entries token by token with the token's d_pooled row in
-//    registers: it reads every entry's value row once for the weight gradient, and writes the
-//    gradient row of an entry that is alone on its row there and then (w_e d_pooled);
-//  * row_bwd_kernel sums the rows with several entries: their runs are cut into pieces of at most
-//    64 entries, and a piece adds its entries' w_e d_pooled in order into its row, or, where it
-//    continues a run, stores a partial row that seg_join_kernel adds in order.
+//  * token_bwd_kernel walks the entries that are alone on their row token by token, with the token's
+//    d_pooled row in registers: it reads the entry's value row for the weight gradient and writes its
+//    gradient row (w_e d_pooled) there and then;
+//  * the runs of several entries are cut into pieces of at most 64 entries; row_bwd_kernel reads a
+//    piece's value row once, and each entry's d_pooled row for the entry's weight gradient and for the
+//    row's sum.  A piece adds its sum into its row, or, where it continues a run, stores a partial row
+//    that seg_join_kernel adds in order.
+// Where a call touches so few rows that they stay in the L2s, and for narrow rows, token_bwd_kernel takes
+// the weight gradients of all entries, and the rows are summed by another walk, of column slices of
+// d_pooled that stay in the L2s.
 // Every row has one writer and a fixed summation order: the result does not depend on timing, and
 // no float atomics are needed.  The compact form writes one gradient row per run (distinct row)
 // from zero instead of adding into a dense table.
@@ -208,7 +212,8 @@ struct RowInfo {
 };
 
 // cnt: the counts of piece_count_kernel.  Writes the pieces' first sorted positions in order into
-// list, their number into counts[0], and clears counts[1] (the spanning runs, appended later).
+// list, their number into counts[0] and that of the runs into counts[2], and clears counts[1] (the
+// spanning runs, appended later).
 template <bool ROWS>
 __global__ __launch_bounds__(THREADS) void piece_write_kernel(
     const uint2* __restrict__ sorted, const uint32_t* __restrict__ n_sorted,
@@ -280,11 +285,27 @@ __global__ __launch_bounds__(THREADS) void piece_write_kernel(
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
     counts[0] = bp;
     counts[1] = 0u;
+    counts[2] = br;
     if (ROWS && info.n_runs != nullptr) *info.n_runs = static_cast<int32_t>(br);
   }
 }
 
 int list_chunks(int M) { return (M + kListChunk - 1) / kListChunk; }
+
+// Whether the runs of several entries are summed by slices.  Where a call touches few distinct rows (at
+// most `few`, kFewBytes of them) its entries find them in the L2s token by token, and their runs are long
+// enough to be walked once for every slice; otherwise a row is better read once for its run (row_dot)
+// than once for each of its entries.  Few pieces are walked by slices all the same: a wave each, which
+// goes through all columns of a wide row, they leave the chip short of waves.
+// Compact form, slices / row_dot (us): 4,096 tokens of 256 entries on rows of 1 KiB, 4,096 rows 351 / 395,
+// 7,600 in clusters 383 / 392, 16,384 561 / 446, 32,768 529 / 453, 65,536 588 / 453, 262,144 714 / 571; 2,048
+// tokens of 64 entries on rows of 2 KiB, 2,048 rows in clusters 115 / 153, 4,096 117 / 140, 16,384 (18,000
+// pieces) 148 / 126; 512 tokens of 84 on rows of 7 KiB, 2,688 rows in clusters (3,400 pieces) 161 / 252; of
+// 5 KiB, 4,096 rows (4,700) 140 / 146.
+constexpr uint32_t kFewBytes = 8u << 20, kFewPieces = 8192;
+__device__ __forceinline__ bool by_slices(const uint32_t* __restrict__ counts, uint32_t few) {
+  return few > 0 && (counts[2] <= few || counts[0] <= kFewPieces);
+}
 
 // ---------------------------------------------------------------- value rows, token by token
 
@@ -315,7 +336,7 @@ __device__ __forceinline__ float group_total(float x) {
 // where the block changes; narrower rows are read L lanes each, 64 / L entries at once, with their
 // d_pooled rows from cache.  Entry j of a group's current 64 leaves its partial weight gradients in
 // LDS ([group][wave][core][j]), which are added in wave order behind a barrier per 64 entries.
-// SLICED: the wave that takes a block's first entry also leaves its d_pooled columns in `sliced`, by
+// SLICED, where the others are summed by slices: the wave that takes a block's first entry also leaves its d_pooled columns in `sliced`, by
 // column slice (row_bwd_kernel).  Wide rows are split between waves (CW = 4 at 4096 bf16 columns) because the d_pooled row of a
 // whole one takes 64 registers beside the value row: three waves per SIMD, one row in flight each.
 // Bound by HBM: each value row is read once and each lone entry's gradient row written once.  At
@@ -330,7 +351,7 @@ __global__ __launch_bounds__(THREADS) void token_bwd_kernel(
     const float* __restrict__ w, const int32_t* __restrict__ perm, uint32_t n_values, int expand,
     int cores, const float* __restrict__ d_pooled, const uint32_t* __restrict__ info,
     float* __restrict__ d_rows, float* __restrict__ dw, float* __restrict__ sliced,
-    int slice_cols) {
+    int slice_cols, const uint32_t* __restrict__ counts, uint32_t few) {
   using TR = Chunk<Elem>;
   constexpr int EPC = TR::kElems;
   constexpr int SUB = kWave / L;                   // entries a wave reads at once
@@ -348,16 +369,20 @@ __global__ __launch_bounds__(THREADS) void token_bwd_kernel(
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   int32_t *rows = lds + NWAVES * cores * kWave, *blk = rows + bag, *order = blk + bag;
+  // which entries: all where the others' rows are summed without the value rows, else those alone on theirs
+  const bool all = L != kWave || (SLICED && by_slices(counts, few));
+  int n_mine = bag;
   if (expand > 1) {
-    __shared__ int bcount[kMaxExpand];
+    __shared__ int bcount[kMaxExpand], total;
     for (int p = tid; p < expand; p += THREADS) bcount[p] = 0;
     __syncthreads();
     for (int s = tid; s < bag; s += THREADS) {
       const uint32_t v = static_cast<uint32_t>(perm[idx_t[s]]);
       const uint32_t p = v / n_values;
+      const bool mine = all || (info_t[s] & kAlone) != 0u;
       rows[s] = static_cast<int32_t>(v - p * n_values);
-      blk[s] = static_cast<int32_t>(p);
-      atomicAdd(&bcount[p], 1);
+      blk[s] = mine ? static_cast<int32_t>(p) : -1;
+      if (mine) atomicAdd(&bcount[p], 1);
     }
     __syncthreads();
     // entries by block, stably (the workgroups that share a bag must agree on the order): wave 0
@@ -367,37 +392,40 @@ __global__ __launch_bounds__(THREADS) void token_bwd_kernel(
       const int incl = wave_inclusive_scan(c);
       wave_lds_order();
       if (lane < expand) bcount[lane] = incl - c;
+      if (lane == kWave - 1) total = incl;
       wave_lds_order();
       const uint64_t lt = lanemask_lt();
       for (int s0 = 0; s0 < bag; s0 += kWave) {
         const int s = s0 + lane;
-        const int p = s < bag ? blk[s] : 0;
-        uint64_t peers = __ballot(s < bag);
+        const int p = s < bag ? blk[s] : -1;
+        uint64_t peers = __ballot(p >= 0);
         for (int b = 0; (1 << b) < expand; ++b) {
           const bool one = (p >> b) & 1;
           const uint64_t ones = __ballot(one);
           peers &= one ? ones : ~ones;
         }
-        const int at = bcount[p];
+        const int at = bcount[max(p, 0)];
         const int rank = __popcll(peers & lt);
-        if (s < bag) order[at + rank] = s;
+        if (p >= 0) order[at + rank] = s;
         wave_lds_order();
-        if (s < bag && rank == 0) bcount[p] = at + __popcll(peers);
+        if (p >= 0 && rank == 0) bcount[p] = at + __popcll(peers);
         wave_lds_order();
       }
     }
-  } else {                                         // the bag as it is
+    __syncthreads();
+    n_mine = __builtin_amdgcn_readfirstlane(total);
+  } else {                                         // the bag as it is, others' entries passed over
     for (int s = tid; s < bag; s += THREADS) {
       rows[s] = idx_t[s];
-      blk[s] = 0;
+      blk[s] = all || (info_t[s] & kAlone) != 0u ? 0 : -1;
       order[s] = s;
     }
+    __syncthreads();
   }
-  __syncthreads();
   const int parts = NG * gridDim.y, group = wave / CW;
-  const int per = (bag + parts - 1) / parts;
+  const int per = (n_mine + parts - 1) / parts;
   const int part = blockIdx.y * NG + group;
-  const int beg = min(bag, part * per), end = min(bag, beg + per);
+  const int beg = min(n_mine, part * per), end = min(n_mine, beg + per);
   const int sub = lane / L, cl = lane % L;
   const int chunk0 = (wave % CW) * CPL * kWave + cl;    // the lane's first 16-byte chunk of the row
   const int per_core = dv / cores;
@@ -434,19 +462,22 @@ __global__ __launch_bounds__(THREADS) void token_bwd_kernel(
             r = __builtin_amdgcn_readfirstlane(r);
             p = __builtin_amdgcn_readfirstlane(p);
           }
-          ent[u] = s;
-          row[u] = r;
-          blk_of[u] = p;
-          inf[u] = info_t[s];
-          const Elem* src = values + static_cast<size_t>(r) * dv;
+          if (p >= 0) {                            // (wave-uniform where a wave takes one entry)
+            ent[u] = s;
+            row[u] = r;
+            blk_of[u] = p;
+            inf[u] = info_t[s];
+            const Elem* src = values + static_cast<size_t>(r) * dv;
 #pragma unroll
-          for (int c = 0; c < CPL; ++c)
-            raw[u][c] = *reinterpret_cast<const u32x4*>(src + (chunk0 + L * c) * EPC);
+            for (int c = 0; c < CPL; ++c)
+              raw[u][c] = *reinterpret_cast<const u32x4*>(src + (chunk0 + L * c) * EPC);
+          }
         }
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (L == kWave && j0 + u >= rend) break;   // (wave-uniform)
+        if (L == kWave && ent[u] < 0) continue;
         const bool on = ent[u] >= 0;
         const int p = blk_of[u];
         if (L != kWave || p != held) {
@@ -460,7 +491,7 @@ __global__ __launch_bounds__(THREADS) void token_bwd_kernel(
               dp[c][e + 1] = v.y;
               dp[c][e + 2] = v.z;
               dp[c][e + 3] = v.w;
-              if (SLICED && (j0 + u == 0 || blk[order[max(j0 + u - 1, 0)]] != p)) {
+              if (SLICED && all && (j0 + u == 0 || blk[order[max(j0 + u - 1, 0)]] != p)) {
                 const int col = (chunk0 + L * c) * EPC + e;       // slices are whole 16-byte pieces
                 const size_t at = (static_cast<size_t>(col / slice_cols) * gridDim.x + t) * expand + p;
                 *reinterpret_cast<f32x4*>(sliced + at * slice_cols + col % slice_cols) = v;
@@ -478,10 +509,9 @@ __global__ __launch_bounds__(THREADS) void token_bwd_kernel(
           for (int e = 0; e < EPC; ++e) dot[c] = fmaf(dp[c][e], x[e], dot[c]);
         }
         for (int k = core_lo; k <= core_hi; ++k) {
-          float v = 0.0f;
+          float v = 0.0f;                          // (chunk by chunk, as row_dot adds them)
 #pragma unroll
-          for (int c = 0; c < CPL; ++c) v += slice[c] == k ? dot[c] : 0.0f;
-          v = group_total<L>(v);
+          for (int c = 0; c < CPL; ++c) v += group_total<L>(slice[c] == k ? dot[c] : 0.0f);
           if (cl == L - 1 && on) sums[(wave * cores + k) * kWave + (j0 + SUB * u + sub - rbeg)] = v;
         }
         if (on && (inf[u] & kAlone) != 0u) {       // alone on its row: the gradient row is here
@@ -515,7 +545,7 @@ __global__ __launch_bounds__(THREADS) void token_bwd_kernel(
     // the group's waves share its entries' sums out: lane = entry, wave % CW, + CW, ... = core
     for (int k = wave % CW; k < cores; k += CW) {
       const int j = rbeg + lane;
-      if (j < rend) {
+      if (j < rend && blk[order[j]] >= 0) {
         float v = sums[(group * CW * cores + k) * kWave + lane];
 #pragma unroll
         for (int x = 1; x < CW; ++x) v += sums[((group * CW + x) * cores + k) * kWave + lane];
@@ -545,38 +575,20 @@ struct RowPiece {
   uint32_t prev, next;   // the rows at first - 1 and first + 64
 };
 
-// The pieces of the runs of several entries: their w_e d_pooled rows summed in order.  GL lanes
-// of 16 bytes take an entry, 64 / GL entries at once, each lane group every (64 / GL)-th entry in
-// order, the groups then meeting by a fixed butterfly.  The next piece's record is read two pieces
-// ahead and its entries one piece ahead, so that a piece waits for its d_pooled rows only.
-// Bound by the re-reads of d_pooled: a run's tokens are random, so its rows come from all over.
-// SLICED: d_pooled is read from the copy that token_bwd_kernel left by column slice, [slice]
-// [pooled row][4 GL columns], slice s by XCD s % 8 (workgroups go to XCDs round-robin): an XCD
-// then reads a few columns of every row, a contiguous block that its 4 MiB L2 holds.  (The same
-// slices read from d_pooled itself lie a row apart, on two of the L2's sixteen channels.)  Otherwise
-// a wave walks all columns of its piece.  At 4,096 tokens of 256 entries on 7,600 rows (2 KiB of
-// d_pooled an entry): 146 us beside the token kernel's 108, against 342 us for one kernel that did
-// both from d_pooled as it is.  8,192 waves 169 us, 32,768 146; two entries in flight a lane group
-// 252, eight 153; slices of half the columns (2 MiB of d_pooled an XCD) no faster.
-template <int GL, bool SLICED>
-__global__ __launch_bounds__(THREADS) void row_bwd_kernel(
-    const uint2* __restrict__ sorted, const uint32_t* __restrict__ n_sorted,
-    const uint2* __restrict__ rec, const uint32_t* __restrict__ info, const float* __restrict__ w,
-    int cores, int dv, size_t pooled_rows, const float* __restrict__ d_pooled, float* __restrict__ out, int compact,
-    float* __restrict__ partial, float* __restrict__ heads_part, const uint32_t* __restrict__ list,
-    uint32_t* __restrict__ counts, uint32_t* __restrict__ heads) {
-  constexpr int S = kWave / GL, kCols = 4 * GL;
+// A piece as the walks below take it: its entries n_e, whether it starts and ends its run.
+struct PieceEnds {
+  uint32_t row;
+  int n_e;
+  bool starts, ends;
+};
+
+// The pieces k = first, first + step, ... of the list in turn, to body(k, piece, ends).  The next piece's
+// record is read two pieces ahead and its entries one piece ahead.
+template <typename Body>
+__device__ __forceinline__ void walk_pieces(const uint2* __restrict__ sorted, int n, const uint2* __restrict__ rec,
+                                            const uint32_t* __restrict__ list, uint32_t n_pieces,
+                                            uint32_t first, uint32_t step, Body body) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int sub = lane / GL;
-  const int n = static_cast<int>(*n_sorted);
-  const uint32_t n_pieces = counts[0];
-  const int per_core = dv / cores;
-  // sliced: each XCD walks the whole list for its own slices
-  const uint32_t xcds = SLICED ? 8u : 1u;
-  const uint32_t first = (blockIdx.x / xcds) * NWAVES + threadIdx.x / kWave;
-  const uint32_t step = (gridDim.x / xcds) * NWAVES;
-  const int c_first = SLICED ? static_cast<int>(blockIdx.x & 7u) * kCols : 0;
-  if (first >= n_pieces) return;                     // (whole waves: no barrier in this kernel)
   auto fetch = [&](uint32_t at, RowPiece& p) {
     p.at = at;
     const int ps = static_cast<int>(at);
@@ -586,37 +598,93 @@ __global__ __launch_bounds__(THREADS) void row_bwd_kernel(
     p.prev = sorted[max(ps - 1, 0)].x;
     p.next = sorted[min(ps + kWave, n - 1)].x;
   };
+  if (first >= n_pieces) return;
+  RowPiece nxt;
+  fetch(list[first], nxt);
+  uint32_t after = first + step < n_pieces ? list[first + step] : 0u;
+  for (uint32_t k = first; k < n_pieces; k += step) {  // wave-uniform
+    const RowPiece cur = nxt;
+    if (k + step < n_pieces) fetch(after, nxt);
+    if (k + 2 * step < n_pieces) after = list[k + 2 * step];
+    const int ps = static_cast<int>(cur.at);
+    PieceEnds e;
+    e.row = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(cur.own.x)));
+    e.starts = ps == 0 || cur.prev != e.row;
+    const int seg_end = min(n, (ps / kSeg + 1) * kSeg);
+    const uint64_t other = __ballot(ps + lane < seg_end && cur.own.x != e.row);
+    e.n_e = other != 0ull ? __builtin_ctzll(other) : seg_end - ps;
+    // the row after the piece (a piece that stops before its segment's end stops at another row)
+    const uint32_t past = e.n_e == kWave ? cur.next : static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(cur.own.x), e.n_e & (kWave - 1)));
+    e.ends = ps + e.n_e >= n || past != e.row;
+    body(k, cur, e);
+  }
+}
+
+// What the walks read and write.
+struct RowArgs {
+  const uint2* sorted;
+  const uint32_t* n_sorted;
+  const uint2* rec;
+  const uint32_t *info, *list;
+  uint32_t *counts, *heads;
+  const float* w;
+  int cores, dv, compact;
+  size_t pooled_rows;
+  const float *d_pooled, *sliced;
+  float *out, *dw, *partial, *heads_part;
+
+  __device__ __forceinline__ float* row_of(const RowPiece& p, const PieceEnds& e) const {
+    const uint32_t r = compact ? info[__builtin_amdgcn_readfirstlane(static_cast<int>(p.own.y))] & ~kAlone : e.row;
+    return out + static_cast<size_t>(r) * dv;
+  }
+  // where a piece's sum goes: its row (after what that held, where the run is whole) or a partial row
+  __device__ __forceinline__ float* sum_at(const RowPiece& p, const PieceEnds& e, float* dst) const {
+    if (e.starts && (e.ends || compact)) return dst;
+    return (e.starts ? heads_part : partial) + static_cast<size_t>(p.at / kSeg) * dv;
+  }
+};
+
+// The pieces of the runs of several entries: their w_e d_pooled rows summed.  The entries j, j + S,
+// j + 2 S, ... of a piece are one group's, added in order; the S groups then meet by a fixed tree.  GL
+// lanes of 16 bytes take an entry, 64 / GL = S groups at once.
+// Bound by the re-reads of d_pooled: a run's tokens are random, so its rows come from all over.
+// SLICED: d_pooled is read from the copy that token_bwd_kernel left by column slice, [slice]
+// [pooled row][4 GL columns], slice s by XCD s % 8 (workgroups go to XCDs round-robin): an XCD
+// then reads a few columns of every row, a contiguous block that its 4 MiB L2 holds.  (The same
+// slices read from d_pooled itself lie a row apart, on two of the L2's sixteen channels.)  Otherwise
+// (rows below 1 KiB) a wave walks all columns of its piece.  At 4,096 tokens of 256 entries on 7,600 rows
+// (2 KiB of d_pooled an entry): 146 us beside the token kernel's 108, against 342 us for one kernel that
+// did both from d_pooled as it is.  8,192 waves 169 us, 32,768 146; two entries in flight a lane group
+// 252, eight 153; slices of half the columns (2 MiB of d_pooled an XCD) no faster.
+template <int GL, bool SLICED>
+__device__ __forceinline__ void row_walk(const RowArgs& A) {
+  constexpr int S = kWave / GL, kCols = 4 * GL;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int sub = lane / GL;
+  const int dv = A.dv, cores = A.cores, per_core = dv / cores;
+  // sliced: each XCD walks the whole list for its own slices
+  const uint32_t xcds = SLICED ? 8u : 1u;
+  const uint32_t first = (blockIdx.x / xcds) * NWAVES + threadIdx.x / kWave;
+  const uint32_t step = (gridDim.x / xcds) * NWAVES;
+  const int c_first = SLICED ? static_cast<int>(blockIdx.x & 7u) * kCols : 0;
+  const uint32_t n_pieces = A.counts[0];
   for (int c0 = c_first; c0 < (SLICED ? dv : 1); c0 += 8 * kCols) {
-    RowPiece nxt;
-    fetch(list[first], nxt);
-    uint32_t after = first + step < n_pieces ? list[first + step] : 0u;
-    for (uint32_t k = first; k < n_pieces; k += step) {  // wave-uniform
-      const RowPiece cur = nxt;
-      if (k + step < n_pieces) fetch(after, nxt);
-      if (k + 2 * step < n_pieces) after = list[k + 2 * step];
-      const int ps = static_cast<int>(cur.at);
-      const uint32_t row = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(cur.own.x)));
-      const bool starts = ps == 0 || cur.prev != row;
-      const int seg_end = min(n, (ps / kSeg + 1) * kSeg);
-      const uint64_t other = __ballot(ps + lane < seg_end && cur.own.x != row);
-      const int n_e = other != 0ull ? __builtin_ctzll(other) : seg_end - ps;
-      // the row after the piece (a piece that stops before its segment's end stops at another row)
-      const uint32_t past = n_e == kWave ? cur.next : static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(cur.own.x), n_e & (kWave - 1)));
-      const bool ends = ps + n_e >= n || past != row;
-      if (c0 == 0 && starts && !ends && lane == 0) heads[atomicAdd(counts + 1, 1u)] = k;
+    walk_pieces(A.sorted, static_cast<int>(*A.n_sorted), A.rec, A.list, n_pieces, first, step,
+                [&](uint32_t k, const RowPiece& cur, const PieceEnds& e) {
+      const int n_e = e.n_e;
+      if (c0 == 0 && e.starts && !e.ends && lane == 0) A.heads[atomicAdd(A.counts + 1, 1u)] = k;
       const int my_prow = static_cast<int>(cur.rec.x);
       const int my_we = static_cast<int>(cur.rec.y);
-      const uint32_t run = compact ? info[__builtin_amdgcn_readfirstlane(static_cast<int>(cur.own.y))] & ~kAlone : row;
+      float* row = A.row_of(cur, e);
       for (int c = c0; c < (SLICED ? c0 + 1 : dv); c += kCols) {
         const int col = c + (lane % GL) * 4;
         const int core = cores > 1 ? col / per_core : 0;   // four columns lie in one core's slice
-        const float* src = SLICED ? d_pooled + static_cast<size_t>(c0 / kCols) * pooled_rows * kCols + (col - c0)
-                                  : d_pooled + col;
+        const float* src = SLICED ? A.sliced + static_cast<size_t>(c0 / kCols) * A.pooled_rows * kCols + (col - c0)
+                                  : A.d_pooled + col;
         const int pitch = SLICED ? kCols : dv;
-        float* dst = out + static_cast<size_t>(run) * dv + col;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         f32x4 old = {0.f, 0.f, 0.f, 0.f};
-        if (starts && ends && !compact && sub == 0) old = *reinterpret_cast<const f32x4*>(dst);
+        if (e.starts && e.ends && !A.compact && sub == 0) old = *reinterpret_cast<const f32x4*>(row + col);
         for (int j0 = 0; j0 < n_e; j0 += S * kRowInFlight) {  // wave-uniform
           f32x4 v[kRowInFlight];
           float wt[kRowInFlight];
@@ -628,7 +696,7 @@ __global__ __launch_bounds__(THREADS) void row_bwd_kernel(
             const int we = __shfl(my_we, jj, kWave);
             v[u] = f32x4{0.f, 0.f, 0.f, 0.f};
             wt[u] = __int_as_float(we);
-            if (cores > 1) wt[u] = j < n_e ? w[static_cast<size_t>(we) * cores + core] : 0.0f;
+            if (cores > 1) wt[u] = j < n_e ? A.w[static_cast<size_t>(we) * cores + core] : 0.0f;
             if (j < n_e) v[u] = *reinterpret_cast<const f32x4*>(src + static_cast<size_t>(pr) * pitch);
           }
 #pragma unroll
@@ -648,13 +716,145 @@ __global__ __launch_bounds__(THREADS) void row_bwd_kernel(
           acc.z += __shfl_xor(acc.z, off, kWave);
           acc.w += __shfl_xor(acc.w, off, kWave);
         }
-        if (sub == 0) {
-          if (starts && (ends || compact)) *reinterpret_cast<f32x4*>(dst) = old + acc;
-          else *reinterpret_cast<f32x4*>((starts ? heads_part : partial) + static_cast<size_t>(ps / kSeg) * dv + col) = acc;
+        if (sub == 0) *reinterpret_cast<f32x4*>(A.sum_at(cur, e, row) + col) = old + acc;
+      }
+    });
+  }
+}
+
+// The same pieces with their weight gradients, rows of 1 KiB and more: a wave takes 64 16-byte chunks of
+// the piece's value row at a time and reads each entry's d_pooled columns once, for the dot and for the
+// sum.  S groups of entries as row_walk's (S of them in a lane's registers), and the dots added chunk
+// by chunk and, after every `cpl` chunks, between the waves' shares, as token_bwd_kernel adds them: dense
+// and compact form give the same bits whichever kernel a call takes.
+// Bound by the re-reads of d_pooled, one an entry.  With the weight gradients left to the token kernel,
+// which reads a value row for each entry, calls whose rows repeat a few times were slower than the
+// one-kernel form of old: dense, 4,096 tokens of 256 entries (rows of 1 KiB, 2 KiB of d_pooled an entry) on
+// 262,144 / 65,536 rows 781 / 609 us the whole call, 647 / 466 now, 687 / 503 then; compact 934 / 588, 636 / 453,
+// 665 / 492.  Four waves per SIMD for S = 4 (128 registers, two of them in scratch): 612 / 484.
+template <typename Elem, int S>
+__device__ __forceinline__ void row_dot(const RowArgs& A, const Elem* __restrict__ values, int cpl) {
+  constexpr int EPC = Chunk<Elem>::kElems, Q = EPC / 4;
+  constexpr int U = kRowInFlight, kTurns = S > U ? S / U : 1;  // entries in flight; batches until the groups recur
+  const int lane = threadIdx.x & (kWave - 1);
+  const int dv = A.dv, cores = A.cores, per_core = dv / cores;
+  const uint32_t first = blockIdx.x * NWAVES + threadIdx.x / kWave;
+  walk_pieces(A.sorted, static_cast<int>(*A.n_sorted), A.rec, A.list, A.counts[0], first, gridDim.x * NWAVES,
+              [&](uint32_t k, const RowPiece& cur, const PieceEnds& e) {
+    const int n_e = e.n_e;
+    if (e.starts && !e.ends && lane == 0) A.heads[atomicAdd(A.counts + 1, 1u)] = k;
+    const int my_prow = static_cast<int>(cur.rec.x);
+    const int my_we = static_cast<int>(cur.rec.y);
+    float* row = A.row_of(cur, e);
+    float my_dw[kMaxCores], share[kMaxCores];                // lane j: entry j's, by core
+#pragma unroll
+    for (int c = 0; c < kMaxCores; ++c) my_dw[c] = share[c] = 0.0f;
+    int chunk = 0;
+    for (int c0 = 0; c0 < dv; c0 += kWave * EPC) {
+      const int col = c0 + lane * EPC;
+      const int core = cores > 1 ? col / per_core : 0;       // a chunk lies in one core's slice
+      const u32x4 raw = *reinterpret_cast<const u32x4*>(values + static_cast<size_t>(e.row) * dv + col);
+      f32x4 acc[S][Q], old[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        old[q] = e.starts && e.ends && !A.compact ? *reinterpret_cast<const f32x4*>(row + col + 4 * q)
+                                                  : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < S; ++i) acc[i][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      float x[EPC];
+      Chunk<Elem>::widen(raw, x);
+      for (int jt = 0; jt < n_e; jt += U * kTurns) {         // wave-uniform
+#pragma unroll
+       for (int turn = 0; turn < kTurns; ++turn) {
+        const int j0 = jt + U * turn;
+        if (j0 >= n_e) break;
+        f32x4 v[U][Q];
+        float wt[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {                        // all loads first
+          const int j = min(j0 + u, n_e - 1);
+          const int pr = __builtin_amdgcn_readlane(my_prow, j);
+          const int we = __builtin_amdgcn_readlane(my_we, j);
+          wt[u] = cores > 1 ? A.w[static_cast<size_t>(we) * cores + core] : __int_as_float(we);
+#pragma unroll
+          for (int q = 0; q < Q; ++q) {
+            v[u][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (j0 + u < n_e) v[u][q] = *reinterpret_cast<const f32x4*>(A.d_pooled + static_cast<size_t>(pr) * dv + col + 4 * q);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {                        // then each group's entries in order
+          if (j0 + u >= n_e) break;
+          float dot = 0.0f;
+#pragma unroll
+          for (int q = 0; q < Q; ++q) {
+            f32x4& a = acc[(U * turn + u) % S][q];
+            dot = fmaf(v[u][q].x, x[4 * q], dot);
+            dot = fmaf(v[u][q].y, x[4 * q + 1], dot);
+            dot = fmaf(v[u][q].z, x[4 * q + 2], dot);
+            dot = fmaf(v[u][q].w, x[4 * q + 3], dot);
+            a.x = fmaf(wt[u], v[u][q].x, a.x);
+            a.y = fmaf(wt[u], v[u][q].y, a.y);
+            a.z = fmaf(wt[u], v[u][q].z, a.z);
+            a.w = fmaf(wt[u], v[u][q].w, a.w);
+          }
+          const int lo = __builtin_amdgcn_readfirstlane(core), hi = __builtin_amdgcn_readlane(core, kWave - 1);
+#pragma unroll
+          for (int c = 0; c < kMaxCores; ++c) {
+            if (c < lo || c > hi) continue;                  // (wave-uniform)
+            const float t = group_total<kWave>(core == c ? dot : 0.0f);
+            const float sum = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), kWave - 1));
+            if (lane == j0 + u) share[c] += sum;
+          }
+        }
+       }
+      }
+#pragma unroll
+      for (int off = 1; off < S; off <<= 1)
+#pragma unroll
+        for (int i = 0; i < S; i += 2 * off)
+#pragma unroll
+          for (int q = 0; q < Q; ++q) acc[i][q] += acc[i + off][q];
+      float* dst = A.sum_at(cur, e, row) + col;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) *reinterpret_cast<f32x4*>(dst + 4 * q) = old[q] + acc[0][q];
+      if (++chunk == cpl) {
+        chunk = 0;
+#pragma unroll
+        for (int c = 0; c < kMaxCores; ++c) {
+          my_dw[c] += share[c];
+          share[c] = 0.0f;
         }
       }
     }
-  }
+    if (lane < n_e) {                                        // this wave is the entries' only writer
+      float* dw = A.dw + static_cast<size_t>(cur.own.y) * cores;
+#pragma unroll
+      for (int c = 0; c < kMaxCores; ++c)
+        if (c < cores) dw[c] = my_dw[c];
+    }
+  });
+}
+
+// Rows of 1 KiB and more, with their weight gradients, unless the next kernel takes them (few: 0 where
+// it is not launched).  Kept apart: row_dot's registers would leave its walk three waves per SIMD of five.
+template <typename Elem, int S>
+__global__ __launch_bounds__(THREADS) void row_bwd_kernel(RowArgs A, const Elem* __restrict__ values, int cpl,
+                                                          uint32_t few) {
+  if (!by_slices(A.counts, few)) row_dot<Elem, S>(A, values, cpl);
+}
+
+// ... by slices of 4 GL columns; all weight gradients are the token kernel's then.
+template <int GL>
+__global__ __launch_bounds__(THREADS) void row_bwd_sliced_kernel(RowArgs A, uint32_t few) {
+  if (by_slices(A.counts, few)) row_walk<GL, true>(A);
+}
+
+// Narrower rows, GL lanes an entry.
+template <int GL>
+__global__ __launch_bounds__(THREADS) void row_bwd_narrow_kernel(RowArgs A) {
+  row_walk<GL, false>(A);
 }
 
 // One wave per run that spans segments: its head (heads_part, or what the row holds: compact form)
@@ -1197,7 +1397,8 @@ template <typename Elem>
 hipError_t launch_tokens(const Elem* values, uint32_t n_values, int dv, int T, int bag,
                          const int32_t* idx, const float* w, const int32_t* perm, int expand, int cores,
                          const float* d_pooled, const uint32_t* info, float* d_rows, bool dense,
-                         float* dw, float* sliced, int slice_cols, hipStream_t s) {
+                         float* dw, float* sliced, int slice_cols, const uint32_t* counts, uint32_t few,
+                         hipStream_t s) {
   const int chunks = dv * static_cast<int>(sizeof(Elem)) / 16;
   const size_t lds = static_cast<size_t>(NWAVES) * cores * kWave * 4 + static_cast<size_t>(bag) * 12;
   const dim3 block(THREADS);
@@ -1206,7 +1407,7 @@ hipError_t launch_tokens(const Elem* values, uint32_t n_values, int dv, int T, i
 #define UMEM_TOKENS_AS(LL, CC, CW, SLICED, DENSE)                                                  \
   hipLaunchKernelGGL((token_bwd_kernel<Elem, LL, CC, CW, SLICED, DENSE>), grid, block, lds, s, values, \
                      dv, bag, idx, w, perm, n_values, expand, cores, d_pooled, info, d_rows, dw,  \
-                     sliced, slice_cols)
+                     sliced, slice_cols, counts, few)
 #define UMEM_TOKENS(LL, CC, CW)                                                                   \
   do {                                                                                            \
     int split = 1;                                                                                \
@@ -1236,6 +1437,44 @@ hipError_t launch_tokens(const Elem* values, uint32_t n_values, int dv, int T, i
   }
 #undef UMEM_TOKENS
 #undef UMEM_TOKENS_AS
+  return hipGetLastError();
+}
+
+// The runs of several entries.  few: as by_slices takes it (0: there is no copy by slices); cols:
+// the slices' columns (256 without); a wave's share of a wide row's chunks as launch_tokens deals them.
+template <typename Elem>
+hipError_t launch_rows(const RowArgs& A, const Elem* values, int cols, uint32_t few, hipStream_t s) {
+  const dim3 grid(kRowWaves / NWAVES), block(THREADS);
+  const int chunks = A.dv * static_cast<int>(sizeof(Elem)) / 16;
+  const int cpl = chunks == 256 ? 2 : chunks == 384 ? 3 : chunks == 512 ? 2 : chunks / kWave;
+#define UMEM_NARROW(GL) hipLaunchKernelGGL(row_bwd_narrow_kernel<GL>, grid, block, 0, s, A)
+#define UMEM_ROWS(S, GL)                                                                           \
+  do {                                                                                            \
+    hipLaunchKernelGGL((row_bwd_kernel<Elem, S>), grid, block, 0, s, A, values, cpl, few);          \
+    if (few > 0) hipLaunchKernelGGL(row_bwd_sliced_kernel<GL>, grid, block, 0, s, A, few);          \
+  } while (0)
+  if (chunks >= kWave) {
+    switch (cols) {
+      case 32: UMEM_ROWS(8, 8); break;
+      case 64: UMEM_ROWS(4, 16); break;
+      case 128: UMEM_ROWS(2, 32); break;
+      case 256: UMEM_ROWS(1, 64); break;
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    switch (A.dv / 4) {                                     // dv a power of two
+      case 1: UMEM_NARROW(1); break;
+      case 2: UMEM_NARROW(2); break;
+      case 4: UMEM_NARROW(4); break;
+      case 8: UMEM_NARROW(8); break;
+      case 16: UMEM_NARROW(16); break;
+      case 32: UMEM_NARROW(32); break;
+      case 64: UMEM_NARROW(64); break;
+      default: return hipErrorInvalidValue;
+    }
+  }
+#undef UMEM_ROWS
+#undef UMEM_NARROW
   return hipGetLastError();
 }
 
@@ -1302,39 +1541,20 @@ hipError_t launch_gather_backward(int64_t n_values, int dv, int vdtype, const vo
   const bool slices = keep && dv * (vdtype == UMEM_F32 ? 4 : 2) >= 1024 && pooled_rows <= static_cast<int64_t>(nseg) &&
                       pooled_rows * dv * 4 > (INT64_C(4) << 20);
   if (!(slices && compact)) sliced = nullptr;
-  // (the dense form takes the compact form's columns at a time too: the same sums, bit for bit)
-  const int cols = slices ? slice_columns(pooled_rows, dv) : std::min(dv, 256);
+  // (the dense form adds in the compact form's groups: the same sums, bit for bit)
+  const int cols = slices ? slice_columns(pooled_rows, dv) : 256;
+  const uint32_t few = sliced == nullptr ? 0u : kFewBytes / (static_cast<uint32_t>(dv) * (vdtype == UMEM_F32 ? 4 : 2));
   e = vdtype == UMEM_F32
           ? launch_tokens(static_cast<const float*>(values), nv, dv, T, bag, idx, w, pm, expand, c,
-                          d_pooled, info, d_values, !compact, dw, sliced, cols, s)
+                          d_pooled, info, d_values, !compact, dw, sliced, cols, counts, few, s)
           : launch_tokens(static_cast<const uint16_t*>(values), nv, dv, T, bag, idx, w, pm, expand, c,
-                          d_pooled, info, d_values, !compact, dw, sliced, cols, s);
+                          d_pooled, info, d_values, !compact, dw, sliced, cols, counts, few, s);
   if (e != hipSuccess) return e;
-#define UMEM_ROWS(GL, SLICED)                                                                      \
-  hipLaunchKernelGGL((row_bwd_kernel<GL, SLICED>), dim3(kRowWaves / NWAVES), dim3(THREADS), 0, s,  \
-                     sorted, sp.n, rec, info, w, c, dv, static_cast<size_t>(pooled_rows),           \
-                     SLICED ? sliced : d_pooled, d_values, compact ? 1 : 0, partial, heads_part, \
-                     list, counts, heads)
-  if (sliced != nullptr) {
-    switch (cols) {
-      case 32: UMEM_ROWS(8, true); break;
-      case 64: UMEM_ROWS(16, true); break;
-      case 128: UMEM_ROWS(32, true); break;
-      default: UMEM_ROWS(64, true); break;
-    }
-  } else {
-    switch (cols / 4) {                                   // dv a power of two below 256, or 256 at a time
-      case 1: UMEM_ROWS(1, false); break;
-      case 2: UMEM_ROWS(2, false); break;
-      case 4: UMEM_ROWS(4, false); break;
-      case 8: UMEM_ROWS(8, false); break;
-      case 16: UMEM_ROWS(16, false); break;
-      case 32: UMEM_ROWS(32, false); break;
-      case 64: UMEM_ROWS(64, false); break;
-      default: return hipErrorInvalidValue;
-    }
-  }
-#undef UMEM_ROWS
+  const RowArgs ra{sorted, sp.n, rec, info, list, counts, heads, w, c, dv, compact ? 1 : 0,
+                   static_cast<size_t>(pooled_rows), d_pooled, sliced, d_values, dw, partial, heads_part};
+  e = vdtype == UMEM_F32 ? launch_rows(ra, static_cast<const float*>(values), cols, few, s)
+                         : launch_rows(ra, static_cast<const uint16_t*>(values), cols, few, s);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(seg_join_kernel, dim3(kJoinWaves / NWAVES), dim3(THREADS), 0, s, sorted, sp.n, dv,
                      partial, heads_part, d_values, list, heads, counts, 0, 0, nullptr, compact ? info : nullptr);
   return hipGetLastError();

@@ -160,6 +160,16 @@ GATHER_BWD_SHAPES = [
     (512, CF.BF16, 1, 100, 41, 1, 1),         # one row for all: a run of 65 segments
     (768, CF.F32, 1, 64, 1400, 2, 900),       # 24 slices of 32 columns, two cores
     (512, CF.BF16, 4, 256, 520, 1, 700),      # eight slices of 64 columns, virtual blocks
+    # ... where the distinct rows pass 8 MiB and the pieces 8,192: their weight gradients with the rows'
+    # sums, in the slices' groups of entries (eight, four, two), over several chunks and shares of a
+    # row, two to eight cores
+    (512, CF.BF16, 4, 256, 520, 1, 8192),
+    (512, CF.BF16, 4, 256, 520, 1, 20000),
+    (768, CF.F32, 1, 64, 1400, 2, 9000),
+    (1024, CF.BF16, 1, 70, 1100, 2, 14000),
+    (2560, CF.BF16, 1, 65, 470, 5, 9000),
+    (3072, CF.BF16, 4, 256, 90, 3, 8500),
+    (4096, CF.BF16, 4, 256, 80, 8, 8000),
 ]
 
 
