@@ -40,11 +40,11 @@ __global__ __launch_bounds__(THREADS) void conv_kernel(const float* __restrict__
                                                        const float* __restrict__ hist,
                                                        const float* __restrict__ w,
                                                        uint16_t* __restrict__ y, int T, int L, int d,
-                                                       int cols) {
-  const int run = blockIdx.x / cols;                     // (uniform over the workgroup)
-  const int c = ((blockIdx.x - run * cols) * THREADS + threadIdx.x) * 4;
+                                                       int cols, int run0) {
+  const int band_run = blockIdx.x / cols;                // (uniform over the workgroup)
+  const int c = ((blockIdx.x - band_run * cols) * THREADS + threadIdx.x) * 4;
   if (c >= d) return;                                    // (no barrier in this kernel)
-  const int t0 = run * R, end = min(T, t0 + R);
+  const int t0 = (run0 + band_run) * R, end = min(T, t0 + R);
   f32x4 wj[KC];
 #pragma unroll
   for (int j = 0; j < KC; ++j) wj[j] = *reinterpret_cast<const f32x4*>(w + static_cast<size_t>(j) * d + c);
@@ -93,29 +93,31 @@ __global__ __launch_bounds__(THREADS) void conv_kernel(const float* __restrict__
   }
 }
 
-// Runs of four tokens where sequences are that long and the launch has waves to spare, else of one.
+// Runs of four tokens where sequences are that long and the launch has waves to spare, else of one; in
+// bands of runs, as a launch takes fewer than 2^32 threads.
+constexpr int kConvGroups = 1 << 23;
 hipError_t launch_conv(const float* x, const float* hist, const float* w, uint16_t* y, int T, int L, int d,
                        int kc, hipStream_t s) {
   const int cols = (d / 4 + THREADS - 1) / THREADS;
-  const bool run = L >= 4 && static_cast<int64_t>(T) * cols >= 2048;
+  const bool four = L >= 4 && static_cast<int64_t>(T) * cols >= 2048;
+  const int runs = four ? (T + 3) / 4 : T, band = std::max(1, kConvGroups / cols);
 #define UMEM_CONV(KC)                                                                             \
-  do {                                                                                            \
-    if (run)                                                                                      \
-      hipLaunchKernelGGL((conv_kernel<KC, 4>), dim3(cols * ((T + 3) / 4)), dim3(THREADS), 0, s, x, hist, \
-                         w, y, T, L, d, cols);                                                    \
+  for (int r0 = 0; r0 < runs; r0 += band) {                                                       \
+    const dim3 grid(static_cast<unsigned>(cols) * std::min(band, runs - r0)), block(THREADS);     \
+    if (four)                                                                                     \
+      hipLaunchKernelGGL((conv_kernel<KC, 4>), grid, block, 0, s, x, hist, w, y, T, L, d, cols, r0); \
     else                                                                                          \
-      hipLaunchKernelGGL((conv_kernel<KC, 1>), dim3(cols * T), dim3(THREADS), 0, s, x, hist, w, y, T, L, \
-                         d, cols);                                                                \
-  } while (0)
+      hipLaunchKernelGGL((conv_kernel<KC, 1>), grid, block, 0, s, x, hist, w, y, T, L, d, cols, r0); \
+  }
   switch (kc) {
-    case 1: UMEM_CONV(1); break;
-    case 2: UMEM_CONV(2); break;
-    case 3: UMEM_CONV(3); break;
-    case 4: UMEM_CONV(4); break;
-    case 5: UMEM_CONV(5); break;
-    case 6: UMEM_CONV(6); break;
-    case 7: UMEM_CONV(7); break;
-    case 8: UMEM_CONV(8); break;
+    case 1: UMEM_CONV(1) break;
+    case 2: UMEM_CONV(2) break;
+    case 3: UMEM_CONV(3) break;
+    case 4: UMEM_CONV(4) break;
+    case 5: UMEM_CONV(5) break;
+    case 6: UMEM_CONV(6) break;
+    case 7: UMEM_CONV(7) break;
+    case 8: UMEM_CONV(8) break;
     default: return hipErrorInvalidValue;
   }
 #undef UMEM_CONV

@@ -116,6 +116,38 @@ def test_convolution_runs(kc):
     assert (np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + kc * 4 * 2.0 ** -23).all()
 
 
+def test_convolution_past_one_launch():
+    """2^20 sequences of one token over 16,384 channels: more threads than one launch of the convolution
+    takes.  Tokens at the ends and at the bands' edges (2^19 runs each) against fp64 (half a bf16 step
+    and the fp32 sum's error)."""
+    T, d = 1 << 20, 16384
+    if torch.cuda.mem_get_info()[0] < 120 << 30:
+        pytest.skip("needs 120 GiB of device memory")
+    log(f"[case] convolution past one launch: T={T} d={d}")
+    qd = U.umem_query_desc()
+    qd.d_model, qd.conv_k, qd.heads, qd.dk, qd.shared, qd.eps = d, 1, 1, 8, 1, 1e-5
+    st, nws = U.umem_query_workspace_size(qd, T, 1)
+    U.check(st)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    ws = torch.empty(nws, dtype=torch.uint8, device="cuda")
+    ws[: T * d * 2].view(torch.int16).fill_(0x7FC0)       # NaN where no token is written
+    x = torch.empty((T, 1, d), dtype=torch.float32, device="cuda").normal_(generator=g)
+    w = torch.randn((1, d), device="cuda", generator=g)
+    wq = torch.randn((8, d), device="cuda", generator=g).to(torch.bfloat16)
+    q = torch.empty((T, 1, 8), dtype=torch.float32, device="cuda")
+    U.check(U.umem_query(qd, T, 1, x, None, w, wq.view(torch.int16), torch.ones((1, 1, 8), device="cuda"),
+                         torch.zeros((1, 1, 8), device="cuda"), q, None, ws, ws.numel()), "umem_query")
+    torch.cuda.synchronize()
+    y = ws[: T * d * 2].view(torch.bfloat16).view(T, d)
+    for t in (0, 1, T // 2 - 1, T // 2, T // 2 + 1, T - 1):
+        ref = x[t, 0].double() * w[0].double()
+        assert bool(((y[t].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 4 * 2.0 ** -23).all()), t
+    assert not bool(y[:, ::4096].isnan().any())
+    assert not bool(q.isnan().any())
+    del x, ws, y
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("T,K,N", [(1, 8, 8), (63, 520, 72), (65, 2048, 64), (130, 1024, 200),
                                    (2036, 2048, 512), (65, 2056, 72)])
 def test_small_tiles(T, K, N):
