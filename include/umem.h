@@ -27,6 +27,8 @@
  *   - Ties: every selection orders by (score desc, index asc) -- the per-axis key index, or the
  *     logical flat index i*n + j on the grid; -0.0 equals +0.0; NaN ranks below -inf.
  *     Selections are returned sorted in that order.
+ *     (Additive grid: it is searched at the pairs of places a, b in its axes' orders with
+ *     (a+1)(b+1) <= topm, which hold its best scores unless +inf meets -inf.)
  *   - Indices are int32 (n*n < 2^31); byte offsets into the value table are 64-bit.
  *   - Alignment: q/k/core 16 bytes, values and fp32 outputs 16 bytes, other arrays 4 bytes.
  *   - T == 0 is a no-op once the descriptor is valid.

@@ -71,6 +71,9 @@ def scores(kind, cfg, g):
     elif kind == "all masked":
         sel[..., :] = float("-inf")
         sel[:, ::3, :, 5:9] = float("nan")
+    elif kind == "opposite":                          # rows of +inf, columns of -inf: the grid's pairs
+        sel[0, ..., : min(cfg.topk, cfg.topm) - 1] = float("inf")     # are NaN in all the candidates' rows but one
+        sel[1] = float("-inf")
     elif kind == "lowest":                            # a mask of the type's lowest value
         sel[..., 3:] = torch.finfo(torch.float32).min
     return sel
@@ -79,6 +82,7 @@ def scores(kind, cfg, g):
 # n: one 256-key step to eighteen, remainders of 4 and of 252; k, m: 1, the largest, m > k
 ADDITIVE = [(2048, 1, 512, 32, 32), (1030, 2, 1024, 33, 64), (700, 3, 772, 1, 1), (4100, 2, 2308, 20, 17),
             (4097, 2, 4480, 32, 32), (2049, 1, 2044, 60, 40)]
+OPPOSITE = [(2048, 1, 512, 2, 2), (2048, 1, 512, 32, 32), (1030, 2, 1024, 33, 64), (2049, 1, 2044, 60, 40)]
 
 
 @pytest.mark.parametrize("kind", ["normal", "ties", "equal", "few", "inf", "lowest", "masked", "all masked"])
@@ -88,6 +92,23 @@ def test_additive(T, heads, n, k, m, kind):
     cfg = layer(T, heads, n, k, m, softmax=(kind == "normal" and k % 2 == 0))
     g = torch.Generator(device="cuda").manual_seed(n + k)
     check(cfg, scores(kind, cfg, g), [torch.empty(0)] * 2, None, None, axis=(m != 17))
+
+
+@pytest.mark.parametrize("T,heads,n,k,m", OPPOSITE)
+def test_additive_opposite_infinities(T, heads, n, k, m):
+    """Every slot is written, with a candidate of its own, where most of the grid is +inf - inf: the best
+    is the finite row's first column, the others NaN or -inf."""
+    print(f"[case] wave additive opposite infinities T={T} H={heads} n={n} k={k} m={m}", flush=True)
+    cfg = layer(T, heads, n, k, m)
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    sel = scores("opposite", cfg, g)
+    check(cfg, sel, [torch.empty(0)] * 2, None, None, axis=True)
+    for ts in (slice(0, T), slice(0, 5)):             # either kernel
+        idx, w, ax = select(cfg, ts.stop, sel[:, ts].contiguous(), [torch.empty(0)] * 2, None, None, True)
+        assert torch.equal(idx[..., 0], ax[0, ..., min(k, m) - 1] * n + ax[1, ..., 0])
+        assert bool((w[..., 0] == float("-inf")).all()) and bool((w.isnan() | w.isneginf()).all())
+        assert bool(((idx >= 0) & (idx < n * n)).all())
+        assert all(x.unique().numel() == m for x in idx[:3].reshape(-1, m))
 
 
 # (T, heads, n, k, m, rank, cores, dk): whole and ragged batches of key pieces, k and m from one to
