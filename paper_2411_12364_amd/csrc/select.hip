@@ -1650,7 +1650,6 @@ __global__ __launch_bounds__(wave_items(TUCKER) * kWave, NV <= 12 ? 4 : 3) void 
       const bool on = lane < k;
       double hi = nan64, lo = nan64;
       int numbers = 0;
-#pragma unroll 4
       for (int a = 0; a < k; ++a) {
         const double g = score(a);
         hi = fmax(hi, g);
@@ -1670,7 +1669,6 @@ __global__ __launch_bounds__(wave_items(TUCKER) * kWave, NV <= 12 ? 4 : 3) void 
           const uint64_t c = theta | (1ull << bit);
           const double at = key64_value(c < lo_key ? lo_key : c);
           int cnt = 0;
-#pragma unroll 4
           for (int a = 0; a < k; ++a) cnt += __popcll(__ballot(score(a) >= at));
           theta = cnt >= m ? c : theta;
           if (cnt == m) break;
@@ -1678,7 +1676,6 @@ __global__ __launch_bounds__(wave_items(TUCKER) * kWave, NV <= 12 ? 4 : 3) void 
         theta_at = key64_value(theta < lo_key ? lo_key : theta);
       }
       int above = 0, ties = 0;                            // lane a: row a's candidates equal to theta
-#pragma unroll 4
       for (int a = 0; a < k; ++a) {
         const double g = score(a);
         above += __popcll(__ballot(nans ? g == g : g > theta_at));
@@ -1757,8 +1754,9 @@ hipError_t launch_select(const umem_desc& d, int T, const float* sel, const floa
   // Measured (us, wave / workgroup kernel): additive, k = m = 32, 1,024 keys, 1,024 / 2,048 / 4,096
   // pairs 11.7 / 10.8, 17.4 / 18.1, 22.4 / 32.5; 4,480 keys 20.5 / 16.1, 22.2 / 26.3, 44.6 / 46.9;
   // Tucker, k = m = 64, 2,048 keys 26.6 / 33.9, 31.3 / 52.6, 43.8 / 95.5; k = m = 42, 448 dims
-  // 39.8 / 36.2, 49.4 / 58.8, 94.5 / 109.2.  Beyond 2,048 keys the scores take 48 to 72 registers (two
-  // or three waves per SIMD) and too few loads are in flight where the scores come from HBM: 3,000
+  // 39.8 / 36.2, 49.4 / 58.8, 94.5 / 109.2.  Beyond 2,048 keys the scores take 48 to 72 registers (four
+  // waves per SIMD up to 3,072 keys, three beyond, and the additive forms keep two or three registers in
+  // scratch) and too few loads are in flight where the scores come from HBM: 3,000
   // keys 28.3 / 23.5 at 2,048 pairs, 43.5 / 79.1 at 8,192; 4,480 keys 68.0 / 88.7 at 8,192, but the
   // 1,024-token decode forward (2,048 pairs) 76.0 against 71.6.
   const int64_t wave_pairs = d.n_keys > 2048 ? 8192 : 2048;
