@@ -221,14 +221,20 @@ __global__ __launch_bounds__(THREADS) void sum_splits_kernel(const f32x4* __rest
 // 512 x 2,048 12.8 us either way, its partial sums then 33 -> 8 MB (the LayerNorm that adds them 9.1
 // -> 5.5 us).  Over a long K their operand traffic costs more: 512 x 1,024 x 16,384 43.2 against
 // 33.9 us with the sum.  (Two to six slices in flight instead of one: no faster at either tile.)
-constexpr int kFullTiles = 512, kLongK = 2048;
+// Long is K > 2,048, and from a 128 x 128 tile per CU on, where a CU's 64 x 64 tiles come in rounds, K >
+// 1,536.  The whole product, small / large tiles (us), by their number: 64 large tiles, K = 1,536 17.4 /
+// 21.4, 2,048 19.9 / 24.9, 4,096 26.3 / 25.8; 128 tiles 20.6 / 24.7, 24.7 / 27.1, 44.6 / 38.2; 224 tiles
+// 33.2 / 39.9, 40.6 / 44.3, 80.6 / 65.4; 256 tiles, K = 1,024 23.0 / 27.7, 1,536 32.9 / 32.7, 1,792 37.5 /
+// 35.2, 2,048 40.7 / 37.4; 448 tiles 35.5 / 45.2, 53.9 / 54.9, 61.6 / 60.1, 71.0 / 64.4.
+constexpr int kFullTiles = 512, kCuTiles = 256, kLongK = 2048, kLongKCu = 1536;
 struct Shape {
   int mt, tm, tn, splits;
   int tiles() const { return tm * tn; }
 };
 Shape gemm_shape(int M, int N, int K) {
   Shape g;
-  g.mt = K > kLongK || static_cast<int64_t>((M + 127) / 128) * ((N + 127) / 128) >= kFullTiles ? 4 : 2;
+  const int64_t large = static_cast<int64_t>((M + 127) / 128) * ((N + 127) / 128);
+  g.mt = large >= kFullTiles || K > (large >= kCuTiles ? kLongKCu : kLongK) ? 4 : 2;
   const int rows = 32 * g.mt;
   g.tm = (M + rows - 1) / rows;
   g.tn = (N + rows - 1) / rows;

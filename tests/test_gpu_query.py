@@ -149,10 +149,11 @@ def test_convolution_past_one_launch():
 
 
 @pytest.mark.parametrize("T,K,N", [(1, 8, 8), (63, 520, 72), (65, 2048, 64), (130, 1024, 200),
-                                   (2036, 2048, 512), (65, 2056, 72)])
+                                   (2036, 2048, 512), (65, 2056, 72), (2036, 1536, 2040),
+                                   (2036, 1544, 2040)])
 def test_small_tiles(T, K, N):
-    """The 64 x 64 tiles of short products (K <= 2048, too few 128 x 128 tiles for the chip) at their
-    edges, and just past the rule: against fp64 on the bf16-rounded operands, within the bound of an
+    """The 64 x 64 tiles of short products (K <= 2048, too few 128 x 128 tiles for the chip; K <= 1536 from
+    256 such tiles on) at their edges, and just past the rule: against fp64 on the bf16-rounded operands, within the bound of an
     fp32 sum of K products (K 2^-23 of the sum of their magnitudes)."""
     log(f"[case] small tiles T={T} K={K} N={N}")
     g = torch.Generator(device="cuda").manual_seed(T + K + N)
