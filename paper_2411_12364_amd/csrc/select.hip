@@ -260,13 +260,12 @@ __device__ __forceinline__ void rank_axis(const uint64_t* comp, int S, int axis,
   }
 }
 
-// Whether a candidate of the additive grid may be NaN: +inf on one axis with -inf on the other (or an axis
-// short of numbers).  Such a pair lies below the corners that it stands before, whose bound then may leave
-// fewer than m candidates: all are kept.  row, col: the sorted axes, of which candidates lie in the first
-// `far` rows and columns.
-__device__ __forceinline__ bool additive_unordered(const float* row, const float* col, int far) {
-  const float a = row[0] + col[far - 1], b = row[far - 1] + col[0];
-  return a != a || b != b;
+// The additive grid's corner bound as a limit of its candidates.  +inf on one axis with -inf on the other is
+// NaN, below the corners that it stands before; those are -inf then (or NaN), and as a bound -inf may leave fewer
+// than m candidates: all are kept.
+__device__ __forceinline__ uint64_t additive_limit(uint64_t th) {
+  constexpr uint64_t kNegInf = 0x000FFFFFFFFFFFFFull;     // order_key64(-inf)
+  return th > kNegInf ? th : 0ull;
 }
 
 // The additive grid's candidates (a+1)(b+1) <= m as a table, row by row, and ceil(m / r) for
@@ -595,8 +594,7 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
       if (c > 0)
         th = max(th, order_key64(static_cast<double>(sh.ax_sc[0][r - 1]) + static_cast<double>(sh.ax_sc[1][c - 1])));
     }
-    th = wave_max_u64(th);
-    if (additive_unordered(sh.ax_sc[0], sh.ax_sc[1], R)) th = 0ull;
+    th = additive_limit(wave_max_u64(th));
     const int C = sh.grid_total;
     for (int c0 = wave * kWave; c0 < C; c0 += THREADS) {
       const int c = c0 + lane;
@@ -1461,8 +1459,7 @@ __global__ __launch_bounds__(wave_items(TUCKER) * kWave, NV <= 12 ? 4 : 3) void 
       const int c = (m + lane) / (lane + 1);
       if (c <= k) th = order_key64(static_cast<double>(s.ax_sc[lane]) + static_cast<double>(s.ax_sc[64 + c - 1]));
     }
-    th = wave_max_u64(th);
-    if (additive_unordered(s.ax_sc, s.ax_sc + 64, rows)) th = 0ull;
+    th = additive_limit(wave_max_u64(th));
     const int len = lane < rows ? min(k, m / (lane + 1)) : 0;
     const int C = __shfl(wave_scan_dpp(len), kWave - 1, kWave);
     for (int c0 = 0; c0 < C; c0 += kWave) {
