@@ -995,6 +995,55 @@ __device__ __forceinline__ void wave_top_set(const WaveLds& s, int S, int k, int
   }
 }
 
+// Ranks among equal scores, by id: rank[] counts the greater scores, so that c equal ones have the places rank
+// .. rank + c - 1 to themselves.  Each round the lowest id that claims a place keeps it, the others go on to
+// the next.  Places from `limit` on are not told apart.  `lost`: the lanes that are not the only ones of their
+// score, but for one of each.  False where they are over three quarters of the S or some score has more than
+// kClaimRounds + 1 (many equal scores: a round is a trip to LDS and back, and comparing all is as fast); rank[]
+// is then as it was.  Scores rounded to bf16, 2,049 pairs of 2,044 keys, k = 60, m = 40: 24.6 us, 31.7 where all
+// were compared, the workgroup kernel 25.8; 2,048 of 1,024, k = m = 32: 15.3, 18.2, 19.1.
+constexpr int kClaimRounds = 12;
+template <int R, typename Id>
+__device__ __forceinline__ bool wave_claim_places(const WaveLds& s, int S, int limit, const uint64_t (&lost)[R],
+                                                  const Id (&id)[R], int (&rank)[R]) {
+  int n_lost = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) n_lost += __popcll(lost[r]);
+  if (4 * n_lost > 3 * S) return false;
+  const int lane = threadIdx.x & (kWave - 1);
+  int at[R];
+  bool open[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    at[r] = rank[r];
+    open[r] = lane + kWave * r < S && at[r] < limit;
+    s.code[lane + kWave * r] = ~0u;
+  }
+  wave_lds_order();
+#pragma unroll 1
+  for (int round = 0; round <= kClaimRounds; ++round) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (open[r]) atomicMin(s.code + at[r], static_cast<uint32_t>(id[r]));
+    wave_lds_order();
+    bool any = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (open[r] && s.code[at[r]] != static_cast<uint32_t>(id[r])) ++at[r];
+      else open[r] = false;
+      open[r] = open[r] && at[r] < limit;
+      any |= open[r];
+    }
+    if (__ballot(any) == 0ull) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) rank[r] = at[r];
+      return true;
+    }
+    wave_lds_order();
+  }
+  return false;
+}
+
 // The S survivors ranked (key desc, index asc): ranks < k to ax / sc.
 template <int R>
 __device__ __forceinline__ void wave_top_sorted(const WaveLds& s, int S, int k, int32_t* ax, float* sc) {
@@ -1025,15 +1074,17 @@ __device__ __forceinline__ void wave_top_sorted(const WaveLds& s, int S, int k, 
   // a tie holds up its launch: 2,048 additive pairs of 1,024 normal scores took 27.1 us where this and the
   // grid's ranks below went entry by entry over up to 256 survivors in four registers a lane, 14.2 now, the
   // workgroup kernel 18.3; scores in steps of 1/4 44 -> 22, 20 there.)
-  bool tie = false;
 #pragma unroll
   for (int r = 0; r < R; ++r)
     if (lane + kWave * r < S) s.code[rank[r]] = lane + kWave * r;
   wave_lds_order();
+  uint64_t lost[R], any = 0ull;
 #pragma unroll
-  for (int r = 0; r < R; ++r)
-    if (lane + kWave * r < S) tie |= s.code[rank[r]] != static_cast<uint32_t>(lane + kWave * r);
-  if (__ballot(tie) != 0ull) {
+  for (int r = 0; r < R; ++r) {
+    lost[r] = __ballot(lane + kWave * r < S && s.code[rank[r]] != static_cast<uint32_t>(lane + kWave * r));
+    any |= lost[r];
+  }
+  if (any != 0ull && !wave_claim_places<R>(s, S, k, lost, idx, rank)) {
 #pragma unroll 2
     for (int u = 0; u < S; u += 4) {
       const uint4 ok = *reinterpret_cast<const uint4*>(s.skey + u), oi = *reinterpret_cast<const uint4*>(s.sidx + u);
@@ -1261,12 +1312,12 @@ __device__ __forceinline__ void wave_axis(f32x4 (&v)[NV], const float* __restric
 }
 
 // The S grid survivors (fp64 scores in s.cg, lane + 64 r's slot in id[r]) ranked (score desc, slot
-// asc).
+// asc), the first m of them exactly.
 template <int R>
-__device__ __forceinline__ void wave_rank_grid(const WaveLds& s, int S, const double (&g)[R],
+__device__ __forceinline__ void wave_rank_grid(const WaveLds& s, int S, int m, const double (&g)[R],
                                                const int32_t (&id)[R], int (&rank)[R]) {
   const int lane = threadIdx.x & (kWave - 1);
-  bool nan = false, tie = false;                          // (a tie: a rank claimed twice)
+  bool nan = false;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     rank[r] = 0;
@@ -1284,12 +1335,16 @@ __device__ __forceinline__ void wave_rank_grid(const WaveLds& s, int S, const do
   for (int r = 0; r < R; ++r)
     if (lane + kWave * r < S) s.code[rank[r]] = lane + kWave * r;
   wave_lds_order();
+  uint64_t lost[R], any = 0ull;
 #pragma unroll
-  for (int r = 0; r < R; ++r)
-    if (lane + kWave * r < S) tie |= s.code[rank[r]] != static_cast<uint32_t>(lane + kWave * r);
+  for (int r = 0; r < R; ++r) {
+    lost[r] = __ballot(lane + kWave * r < S && s.code[rank[r]] != static_cast<uint32_t>(lane + kWave * r));
+    any |= lost[r];
+  }
   const bool nans = __ballot(nan) != 0ull;
-  if (!nans && __ballot(tie) == 0ull) return;
+  if (!nans && any == 0ull) return;
   wave_lds_order();
+  if (!nans && wave_claim_places<R>(s, S, m, lost, id, rank)) return;
 #pragma unroll
   for (int r = 0; r < R; ++r)
     if (lane + kWave * r < S) s.code[lane + kWave * r] = static_cast<uint32_t>(id[r]);
@@ -1317,6 +1372,73 @@ __device__ __forceinline__ void wave_rank_grid(const WaveLds& s, int S, const do
       rank[r] += static_cast<int>(ok > me) + static_cast<int>((ok == me) & (oi < id[r]));
     }
   }
+}
+
+// The S > 2 kWave survivors of the additive grid, whose codes are in s.ab, cut to the m best where those
+// equal to the m-th in fp32 are one score (ties of many: quantised or repeated scores), else to those that
+// reach it in fp32.  Their new number.  2,060 pairs of 1,024 normal scores, k = 33, m = 64: 19.2 us, 27.6 where
+// all were ranked (the workgroup kernel 29.9); scores in steps of 1/4 28, 43 (33.5).
+__device__ __forceinline__ int wave_cut_additive(const WaveLds& s, int S, int n, int m) {
+  constexpr int R = kWaveCap / kWave;
+  const int lane = threadIdx.x & (kWave - 1);
+  uint32_t code[R], key[R];
+  double g[R];
+  int id[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool on = lane + kWave * r < S;
+    code[r] = on ? s.ab[lane + kWave * r] : 0u;
+    const int a = static_cast<int>(code[r] >> 8), b = static_cast<int>(code[r] & 0xFFu);
+    g[r] = static_cast<double>(s.ax_sc[a]) + static_cast<double>(s.ax_sc[64 + b]);
+    key[r] = on ? order_key(static_cast<float>(g[r])) : 0u;
+    id[r] = on ? s.ax_idx[a] * n + s.ax_idx[64 + b] : 0x7FFFFFFF;
+  }
+  const uint32_t theta = wave_kth32<R>(key, m);
+  int gt = 0, ge = 0;
+  double at = __builtin_nan("");                          // a score equal to the m-th in fp32
+  uint64_t eq[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool on = lane + kWave * r < S;
+    gt += __popcll(__ballot(on && key[r] > theta));
+    eq[r] = __ballot(on && key[r] == theta);
+    ge += __popcll(eq[r]);
+    if (eq[r] != 0ull) {                                  // (wave-uniform)
+      const uint64_t v = __builtin_bit_cast(uint64_t, g[r]);
+      const int from = __builtin_ctzll(eq[r]);
+      const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(v), from);
+      const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(v >> 32), from);
+      at = __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+    }
+  }
+  ge += gt;
+  int lim = 0x7FFFFFFE;                                   // the highest slot taken among the equal ones
+  bool one = ge > m;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    one = one && (__ballot(g[r] == at || (g[r] != g[r] && at != at)) & eq[r]) == eq[r];
+  if (one) {                                              // the lowest slots among them
+    const int need = m - gt;
+    lim = 0;
+    for (int b = 25; b >= 0; --b) {                       // largest y with fewer than need below it
+      const int c = lim | (1 << b);
+      int below = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) below += __popcll(__ballot(id[r] < c) & eq[r]);
+      if (below < need) lim = c;
+    }
+  }
+  wave_lds_order();
+  int pos = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool take = lane + kWave * r < S && (key[r] > theta || (key[r] == theta && id[r] <= lim));
+    const uint64_t mk = __ballot(take);
+    if (take) s.ab[pos + mask_rank(mk)] = static_cast<uint16_t>(code[r]);
+    pos += __popcll(mk);
+  }
+  wave_lds_order();
+  return pos;
 }
 
 struct WaveArgs {
@@ -1354,7 +1476,7 @@ __device__ __forceinline__ void wave_finish(const WaveArgs& A, const WaveLds& s,
   for (int r = 0; r < R; ++r)
     if (lane + kWave * r < S) s.cg[lane + kWave * r] = g[r];
   wave_lds_order();
-  wave_rank_grid<R>(s, S, g, id, rank);
+  wave_rank_grid<R>(s, S, A.m, g, id, rank);
   const size_t o = pair * A.m;
   float e_of[R];
   float inv_of = 1.0f;
@@ -1475,6 +1597,8 @@ __global__ __launch_bounds__(wave_items(TUCKER) * kWave, NV <= 12 ? 4 : 3) void 
       S += __popcll(mk);
     }
     wave_lds_order();
+    // (a rank of that many costs more)
+    if (S > 2 * kWave) S = wave_cut_additive(s, S, A.n, m);
   } else {
     // ---- exact per-slice scores of the selected keys (eq. (4)), fp32: G = 4, 8 or 16 lanes to an
     // (axis, key) row, L of them to a slice, each striding its slice's 16-byte pieces by L, eight

@@ -56,6 +56,10 @@ def scores(kind, cfg, g):
     sel = torch.randn((2, cfg.T, cfg.heads, cfg.n_keys), device="cuda", generator=g)
     if kind == "ties":                                # some 30 distinct values: massive ties
         sel = (sel * 4).round() / 4
+    elif kind == "few ties":                          # groups of a few equal scores
+        sel = sel.bfloat16().float()
+    elif kind == "twins":                             # every score twice, every pair four times
+        sel[..., 1::2] = sel[..., ::2]
     elif kind == "equal":
         sel.zero_()
         sel[:, 1::2] = -0.0
@@ -85,7 +89,7 @@ ADDITIVE = [(2048, 1, 512, 32, 32), (1030, 2, 1024, 33, 64), (700, 3, 772, 1, 1)
 OPPOSITE = [(2048, 1, 512, 2, 2), (2048, 1, 512, 32, 32), (1030, 2, 1024, 33, 64), (2049, 1, 2044, 60, 40)]
 
 
-@pytest.mark.parametrize("kind", ["normal", "ties", "equal", "few", "inf", "lowest", "masked", "all masked"])
+@pytest.mark.parametrize("kind", ["normal", "ties", "few ties", "twins", "equal", "few", "inf", "lowest", "masked", "all masked"])
 @pytest.mark.parametrize("T,heads,n,k,m", ADDITIVE)
 def test_additive(T, heads, n, k, m, kind):
     print(f"[case] wave additive T={T} H={heads} n={n} k={k} m={m} {kind}", flush=True)
@@ -117,7 +121,7 @@ TUCKER = [(512, 4, 2048, 64, 64, 2, 1, 128), (1024, 2, 1792, 42, 42, 2, 2, 448),
           (700, 3, 1020, 16, 1, 1, 1, 20), (1024, 2, 2048, 64, 64, 1, 1, 64), (4097, 2, 4480, 30, 50, 2, 4, 40)]
 
 
-@pytest.mark.parametrize("kind", ["normal", "ties", "zero", "near-rank-1", "nan", "masked", "all masked", "huge",
+@pytest.mark.parametrize("kind", ["normal", "ties", "twins", "zero", "near-rank-1", "nan", "masked", "all masked", "huge",
                                   "overflow"])
 @pytest.mark.parametrize("T,heads,n,k,m,rank,cores,dk", TUCKER)
 def test_tucker(T, heads, n, k, m, rank, cores, dk, kind):
@@ -132,6 +136,9 @@ def test_tucker(T, heads, n, k, m, rank, cores, dk, kind):
         q = [x.sign() for x in q]
         K = [x.sign() for x in K]
         core = core.sign()
+    elif kind == "twins":                             # every key twice
+        for x in K:
+            x[:, 1::2] = x[:, ::2]
     elif kind == "zero":                              # padding tokens
         q[0][::2] = 0.0
         q[1][::3] = 0.0
