@@ -9,13 +9,13 @@
 //  * token_bwd_kernel walks the entries that are alone on their row token by token, with the token's
 //    d_pooled row in registers: it reads the entry's value row for the weight gradient and writes its
 //    gradient row (w_e d_pooled) there and then;
-//  * the runs of several entries are cut into pieces of at most 64 entries; row_bwd_kernel reads a
+//  * the runs of several entries are cut into pieces of at most 64 entries; the row kernels read a
 //    piece's value row once, and each entry's d_pooled row for the entry's weight gradient and for the
-//    row's sum.  A piece adds its sum into its row, or, where it continues a run, stores a partial row
-//    that seg_join_kernel adds in order.
-// Where a call touches so few rows that they stay in the L2s, and for narrow rows, token_bwd_kernel takes
-// the weight gradients of all entries, and the rows are summed by another walk, of column slices of
-// d_pooled that stay in the L2s.
+//    row's sum (row_dot).  A piece adds its sum into its row, or, where it continues a run, stores a
+//    partial row that seg_join_kernel adds in order.
+// Where rows repeat in few pieces or stay in the L2s (RowRule), and for narrow rows, token_bwd_kernel takes
+// the weight gradients of all entries, and the rows are summed by another walk, a few columns at a time
+// (row_walk).
 // Every row has one writer and a fixed summation order: the result does not depend on timing, and
 // no float atomics are needed.  The compact form writes one gradient row per run (distinct row)
 // from zero instead of adding into a dense table.
@@ -292,20 +292,27 @@ __global__ __launch_bounds__(THREADS) void piece_write_kernel(
 
 int list_chunks(int M) { return (M + kListChunk - 1) / kListChunk; }
 
-// Whether the runs of several entries are summed by slices.  Where a call touches few distinct rows (at
-// most `few`, kFewBytes of them) its entries find them in the L2s token by token, and their runs are long
-// enough to be walked once for every slice; otherwise a row is better read once for its run (row_dot)
-// than once for each of its entries.  Few pieces are walked by slices all the same: a wave each, which
-// goes through all columns of a wide row, they leave the chip short of waves.
-// Compact form, slices / row_dot (us): 4,096 tokens of 256 entries on rows of 1 KiB, 4,096 rows 351 / 395,
+// Whether the token kernel takes the weight gradients of the runs of several entries too, and their rows are
+// summed by columns (row_walk); otherwise a row is read once for its run (row_dot) and not for each of its
+// entries.  By token where a call touches few distinct rows (at most `few`, kFewBytes of them: the entries find
+// them in the L2s) and d_pooled lies by slice, and where rows repeat (four entries a row, of `entries`) in few
+// pieces: a wave each, which goes through all columns of a wide row, they leave the chip short of waves.  Calls
+// of at most kTinyCall entries, where nothing but the chain of loads counts, all go by token (a row to a wave).
+// Compact form, by token / row_dot (us): 4,096 tokens of 256 entries on rows of 1 KiB, 4,096 rows 351 / 395,
 // 7,600 in clusters 383 / 392, 16,384 561 / 446, 32,768 529 / 453, 65,536 588 / 453, 262,144 714 / 571; 2,048
 // tokens of 64 entries on rows of 2 KiB, 2,048 rows in clusters 115 / 153, 4,096 117 / 140, 16,384 (18,000
-// pieces) 148 / 126; 512 tokens of 84 on rows of 7 KiB, 2,688 rows in clusters (3,400 pieces) 161 / 252; of
-// 5 KiB, 4,096 rows (4,700) 140 / 146.
-constexpr uint32_t kFewBytes = 8u << 20, kFewPieces = 8192;
-__device__ __forceinline__ bool by_slices(const uint32_t* __restrict__ counts, uint32_t few) {
-  return few > 0 && (counts[2] <= few || counts[0] <= kFewPieces);
-}
+// pieces) 148 / 126; 4,096 tokens of 64 on 8,192 rows (12,300 pieces) 193 / 226; 512 tokens of 84 on rows of 7
+// KiB, 2,688 rows in clusters (3,400 pieces) 161 / 252; of 8 KiB in four blocks (d_pooled as it is), 1,000 rows
+// 112 / 242, 2,688 154 / 187, but 88,000 (7,500 pieces of two entries) 284 / 182 on rows of 7 KiB.
+constexpr uint32_t kFewBytes = 8u << 20, kFewPieces = 14336;
+constexpr int kTinyCall = 4096;
+struct RowRule {
+  uint32_t few, entries;
+  __device__ __forceinline__ bool repeats(const uint32_t* __restrict__ counts) const { return 4 * counts[2] <= entries; }
+  __device__ __forceinline__ bool by_token(const uint32_t* __restrict__ counts) const {
+    return counts[2] <= few || (counts[0] <= kFewPieces && repeats(counts));
+  }
+};
 
 // ---------------------------------------------------------------- value rows, token by token
 
@@ -336,9 +343,11 @@ __device__ __forceinline__ float group_total(float x) {
 // where the block changes; narrower rows are read L lanes each, 64 / L entries at once, with their
 // d_pooled rows from cache.  Entry j of a group's current 64 leaves its partial weight gradients in
 // LDS ([group][wave][core][j]), which are added in wave order behind a barrier per 64 entries.
-// SLICED, where the others are summed by slices: the wave that takes a block's first entry also leaves its d_pooled columns in `sliced`, by
-// column slice (row_bwd_kernel).  Wide rows are split between waves (CW = 4 at 4096 bf16 columns) because the d_pooled row of a
-// whole one takes 64 registers beside the value row: three waves per SIMD, one row in flight each.
+// SLICED, where all weight gradients are taken here: the wave that takes a block's first entry also leaves
+// its d_pooled columns in `sliced`, by column slice (row_walk).  Wide rows are split between waves (CW = 4
+// at 4096 bf16 columns) because the d_pooled row of a whole one takes 64 registers beside the value row:
+// three waves per SIMD, one row in flight each.  (Rows of 5 and 7 KiB, which do not split evenly, stay whole
+// all the same: 512 tokens of 84 lone rows 198 and 266 us the call, 300 and 368 in one kernel with the sums.)
 // Bound by HBM: each value row is read once and each lone entry's gradient row written once.  At
 // 2,048 tokens of 64 rows of 2 KiB (121,600 distinct) it moves 764 MB in 158 us, 4.8 TB/s, the rate
 // of a large device copy; at 512 tokens of 84 rows of 8 KiB 1.06 GB in 224 us.  A wave per row read
@@ -351,7 +360,7 @@ __global__ __launch_bounds__(THREADS) void token_bwd_kernel(
     const float* __restrict__ w, const int32_t* __restrict__ perm, uint32_t n_values, int expand,
     int cores, const float* __restrict__ d_pooled, const uint32_t* __restrict__ info,
     float* __restrict__ d_rows, float* __restrict__ dw, float* __restrict__ sliced,
-    int slice_cols, const uint32_t* __restrict__ counts, uint32_t few) {
+    int slice_cols, const uint32_t* __restrict__ counts, RowRule rule) {
   using TR = Chunk<Elem>;
   constexpr int EPC = TR::kElems;
   constexpr int SUB = kWave / L;                   // entries a wave reads at once
@@ -370,7 +379,7 @@ __global__ __launch_bounds__(THREADS) void token_bwd_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   int32_t *rows = lds + NWAVES * cores * kWave, *blk = rows + bag, *order = blk + bag;
   // which entries: all where the others' rows are summed without the value rows, else those alone on theirs
-  const bool all = L != kWave || (SLICED && by_slices(counts, few));
+  const bool all = L != kWave || rule.by_token(counts);
   int n_mine = bag;
   if (expand > 1) {
     __shared__ int bcount[kMaxExpand], total;
@@ -648,27 +657,29 @@ struct RowArgs {
 // j + 2 S, ... of a piece are one group's, added in order; the S groups then meet by a fixed tree.  GL
 // lanes of 16 bytes take an entry, 64 / GL = S groups at once.
 // Bound by the re-reads of d_pooled: a run's tokens are random, so its rows come from all over.
-// SLICED: d_pooled is read from the copy that token_bwd_kernel left by column slice, [slice]
-// [pooled row][4 GL columns], slice s by XCD s % 8 (workgroups go to XCDs round-robin): an XCD
-// then reads a few columns of every row, a contiguous block that its 4 MiB L2 holds.  (The same
-// slices read from d_pooled itself lie a row apart, on two of the L2's sixteen channels.)  Otherwise
-// (rows below 1 KiB) a wave walks all columns of its piece.  At 4,096 tokens of 256 entries on 7,600 rows
+// COLUMNS: 4 GL columns at a time, slice s of them by XCD s % 8 (workgroups go to XCDs round-robin), from the
+// copy that token_bwd_kernel left by column slice, [slice][pooled row][4 GL columns], where there is one: an
+// XCD then reads a few columns of every row, a contiguous block that its 4 MiB L2 holds.  (The same
+// slices of d_pooled itself lie a row apart, on two of the L2's sixteen channels.  Where pieces are few they
+// still leave more waves to the chip than whole rows: 512 tokens of 84 entries on 1,000 rows of 8 KiB 112
+// us the call, 177 with a wave to a whole row.)  Otherwise (rows below 1 KiB, tiny calls) a wave walks all
+// columns of its piece.  At 4,096 tokens of 256 entries on 7,600 rows
 // (2 KiB of d_pooled an entry): 146 us beside the token kernel's 108, against 342 us for one kernel that
 // did both from d_pooled as it is.  8,192 waves 169 us, 32,768 146; two entries in flight a lane group
 // 252, eight 153; slices of half the columns (2 MiB of d_pooled an XCD) no faster.
-template <int GL, bool SLICED>
+template <int GL, bool COLUMNS>
 __device__ __forceinline__ void row_walk(const RowArgs& A) {
   constexpr int S = kWave / GL, kCols = 4 * GL;
   const int lane = threadIdx.x & (kWave - 1);
   const int sub = lane / GL;
   const int dv = A.dv, cores = A.cores, per_core = dv / cores;
-  // sliced: each XCD walks the whole list for its own slices
-  const uint32_t xcds = SLICED ? 8u : 1u;
+  // by columns: each XCD walks the whole list for its own slices
+  const uint32_t xcds = COLUMNS ? 8u : 1u;
   const uint32_t first = (blockIdx.x / xcds) * NWAVES + threadIdx.x / kWave;
   const uint32_t step = (gridDim.x / xcds) * NWAVES;
-  const int c_first = SLICED ? static_cast<int>(blockIdx.x & 7u) * kCols : 0;
+  const int c_first = COLUMNS ? static_cast<int>(blockIdx.x & 7u) * kCols : 0;
   const uint32_t n_pieces = A.counts[0];
-  for (int c0 = c_first; c0 < (SLICED ? dv : 1); c0 += 8 * kCols) {
+  for (int c0 = c_first; c0 < (COLUMNS ? dv : 1); c0 += 8 * kCols) {
     walk_pieces(A.sorted, static_cast<int>(*A.n_sorted), A.rec, A.list, n_pieces, first, step,
                 [&](uint32_t k, const RowPiece& cur, const PieceEnds& e) {
       const int n_e = e.n_e;
@@ -676,12 +687,13 @@ __device__ __forceinline__ void row_walk(const RowArgs& A) {
       const int my_prow = static_cast<int>(cur.rec.x);
       const int my_we = static_cast<int>(cur.rec.y);
       float* row = A.row_of(cur, e);
-      for (int c = c0; c < (SLICED ? c0 + 1 : dv); c += kCols) {
+      for (int c = c0; c < (COLUMNS ? c0 + 1 : dv); c += kCols) {
         const int col = c + (lane % GL) * 4;
         const int core = cores > 1 ? col / per_core : 0;   // four columns lie in one core's slice
-        const float* src = SLICED ? A.sliced + static_cast<size_t>(c0 / kCols) * A.pooled_rows * kCols + (col - c0)
-                                  : A.d_pooled + col;
-        const int pitch = SLICED ? kCols : dv;
+        const bool copy = COLUMNS && A.sliced != nullptr;
+        const float* src = copy ? A.sliced + static_cast<size_t>(c0 / kCols) * A.pooled_rows * kCols + (col - c0)
+                                : A.d_pooled + col;
+        const int pitch = copy ? kCols : dv;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         f32x4 old = {0.f, 0.f, 0.f, 0.f};
         if (e.starts && e.ends && !A.compact && sub == 0) old = *reinterpret_cast<const f32x4*>(row + col);
@@ -837,21 +849,27 @@ __device__ __forceinline__ void row_dot(const RowArgs& A, const Elem* __restrict
   });
 }
 
-// Rows of 1 KiB and more, with their weight gradients, unless the next kernel takes them (few: 0 where
-// it is not launched).  Kept apart: row_dot's registers would leave its walk three waves per SIMD of five.
-template <typename Elem, int S>
+// Rows of 1 KiB and more: with their weight gradients, or, where these are the token kernel's, by columns.
+// In one launch with one group of entries (110 registers at most); an empty launch takes 3 us.
+template <typename Elem, int GL>
 __global__ __launch_bounds__(THREADS) void row_bwd_kernel(RowArgs A, const Elem* __restrict__ values, int cpl,
-                                                          uint32_t few) {
-  if (!by_slices(A.counts, few)) row_dot<Elem, S>(A, values, cpl);
+                                                          RowRule rule) {
+  if (rule.by_token(A.counts)) row_walk<GL, true>(A);
+  else row_dot<Elem, 1>(A, values, cpl);
 }
 
-// ... by slices of 4 GL columns; all weight gradients are the token kernel's then.
+// d_pooled by slice: row_dot's registers for S groups would leave the walk three waves per SIMD of five.
+template <typename Elem, int S>
+__global__ __launch_bounds__(THREADS) void row_bwd_dots_kernel(RowArgs A, const Elem* __restrict__ values, int cpl,
+                                                               RowRule rule) {
+  if (!rule.by_token(A.counts)) row_dot<Elem, S>(A, values, cpl);
+}
 template <int GL>
-__global__ __launch_bounds__(THREADS) void row_bwd_sliced_kernel(RowArgs A, uint32_t few) {
-  if (by_slices(A.counts, few)) row_walk<GL, true>(A);
+__global__ __launch_bounds__(THREADS) void row_bwd_sliced_kernel(RowArgs A, RowRule rule) {
+  if (rule.by_token(A.counts)) row_walk<GL, true>(A);
 }
 
-// Narrower rows, GL lanes an entry.
+// Narrower rows, GL lanes an entry; and tiny calls' rows of any width.
 template <int GL>
 __global__ __launch_bounds__(THREADS) void row_bwd_narrow_kernel(RowArgs A) {
   row_walk<GL, false>(A);
@@ -1397,7 +1415,7 @@ template <typename Elem>
 hipError_t launch_tokens(const Elem* values, uint32_t n_values, int dv, int T, int bag,
                          const int32_t* idx, const float* w, const int32_t* perm, int expand, int cores,
                          const float* d_pooled, const uint32_t* info, float* d_rows, bool dense,
-                         float* dw, float* sliced, int slice_cols, const uint32_t* counts, uint32_t few,
+                         float* dw, float* sliced, int slice_cols, const uint32_t* counts, RowRule rule,
                          hipStream_t s) {
   const int chunks = dv * static_cast<int>(sizeof(Elem)) / 16;
   const size_t lds = static_cast<size_t>(NWAVES) * cores * kWave * 4 + static_cast<size_t>(bag) * 12;
@@ -1407,7 +1425,7 @@ hipError_t launch_tokens(const Elem* values, uint32_t n_values, int dv, int T, i
 #define UMEM_TOKENS_AS(LL, CC, CW, SLICED, DENSE)                                                  \
   hipLaunchKernelGGL((token_bwd_kernel<Elem, LL, CC, CW, SLICED, DENSE>), grid, block, lds, s, values, \
                      dv, bag, idx, w, perm, n_values, expand, cores, d_pooled, info, d_rows, dw,  \
-                     sliced, slice_cols, counts, few)
+                     sliced, slice_cols, counts, rule)
 #define UMEM_TOKENS(LL, CC, CW)                                                                   \
   do {                                                                                            \
     int split = 1;                                                                                \
@@ -1440,27 +1458,33 @@ hipError_t launch_tokens(const Elem* values, uint32_t n_values, int dv, int T, i
   return hipGetLastError();
 }
 
-// The runs of several entries.  few: as by_slices takes it (0: there is no copy by slices); cols:
-// the slices' columns (256 without); a wave's share of a wide row's chunks as launch_tokens deals them.
+// The runs of several entries.  slices: RowRule's forms may differ between dense and compact form; cols: the
+// columns that row_walk takes at a time; a wave's share of a wide row's chunks as launch_tokens deals them.
 template <typename Elem>
-hipError_t launch_rows(const RowArgs& A, const Elem* values, int cols, uint32_t few, hipStream_t s) {
+hipError_t launch_rows(const RowArgs& A, const Elem* values, int M, bool slices, int cols, RowRule rule,
+                       hipStream_t s) {
   const dim3 grid(kRowWaves / NWAVES), block(THREADS);
   const int chunks = A.dv * static_cast<int>(sizeof(Elem)) / 16;
   const int cpl = chunks == 256 ? 2 : chunks == 384 ? 3 : chunks == 512 ? 2 : chunks / kWave;
 #define UMEM_NARROW(GL) hipLaunchKernelGGL(row_bwd_narrow_kernel<GL>, grid, block, 0, s, A)
-#define UMEM_ROWS(S, GL)                                                                           \
+#define UMEM_ROWS(S, GL)                                                                          \
   do {                                                                                            \
-    hipLaunchKernelGGL((row_bwd_kernel<Elem, S>), grid, block, 0, s, A, values, cpl, few);          \
-    if (few > 0) hipLaunchKernelGGL(row_bwd_sliced_kernel<GL>, grid, block, 0, s, A, few);          \
+    if (slices) {                                                                                 \
+      hipLaunchKernelGGL((row_bwd_dots_kernel<Elem, S>), grid, block, 0, s, A, values, cpl, rule); \
+      hipLaunchKernelGGL(row_bwd_sliced_kernel<GL>, grid, block, 0, s, A, rule);                  \
+    } else {                                                                                      \
+      hipLaunchKernelGGL((row_bwd_kernel<Elem, GL>), grid, block, 0, s, A, values, cpl, rule);    \
+    }                                                                                             \
   } while (0)
-  if (chunks >= kWave) {
+  if (chunks >= kWave && M > kTinyCall) {
     switch (cols) {
       case 32: UMEM_ROWS(8, 8); break;
       case 64: UMEM_ROWS(4, 16); break;
       case 128: UMEM_ROWS(2, 32); break;
-      case 256: UMEM_ROWS(1, 64); break;
-      default: return hipErrorInvalidValue;
+      default: UMEM_ROWS(1, 64); break;
     }
+  } else if (chunks >= kWave) {
+    UMEM_NARROW(64);
   } else {
     switch (A.dv / 4) {                                     // dv a power of two
       case 1: UMEM_NARROW(1); break;
@@ -1538,22 +1562,26 @@ hipError_t launch_gather_backward(int64_t n_values, int dv, int vdtype, const vo
   // lanes (1 KiB) and room beside the partial rows (which the dense form's heads take)
   const bool keep = 4 * static_cast<int64_t>(M) >= n_values;
   const int64_t pooled_rows = static_cast<int64_t>(T) * expand;
-  const bool slices = keep && dv * (vdtype == UMEM_F32 ? 4 : 2) >= 1024 && pooled_rows <= static_cast<int64_t>(nseg) &&
+  const bool slices = keep && M > kTinyCall && dv * (vdtype == UMEM_F32 ? 4 : 2) >= 1024 && pooled_rows <= static_cast<int64_t>(nseg) &&
                       pooled_rows * dv * 4 > (INT64_C(4) << 20);
   if (!(slices && compact)) sliced = nullptr;
-  // (the dense form adds in the compact form's groups: the same sums, bit for bit)
-  const int cols = slices ? slice_columns(pooled_rows, dv) : 256;
-  const uint32_t few = sliced == nullptr ? 0u : kFewBytes / (static_cast<uint32_t>(dv) * (vdtype == UMEM_F32 ? 4 : 2));
+  // Where one form may take the other kernel than the other form, both add in the same groups of entries:
+  // the same sums, bit for bit.
+  const int cols = slice_columns(pooled_rows, dv);
+  // (with several cores the walk by slices gathers an entry's weight anew for every slice: 4,096 tokens of 256
+  // entries on 7,600 rows of 1 KiB, two cores, 548 us, by row_dot 424)
+  const RowRule rule{M <= kTinyCall ? ~0u : sliced == nullptr || c > 1 ? 0u : kFewBytes / (static_cast<uint32_t>(dv) * (vdtype == UMEM_F32 ? 4 : 2)),
+                     static_cast<uint32_t>(M)};
   e = vdtype == UMEM_F32
           ? launch_tokens(static_cast<const float*>(values), nv, dv, T, bag, idx, w, pm, expand, c,
-                          d_pooled, info, d_values, !compact, dw, sliced, cols, counts, few, s)
+                          d_pooled, info, d_values, !compact, dw, sliced, cols, counts, rule, s)
           : launch_tokens(static_cast<const uint16_t*>(values), nv, dv, T, bag, idx, w, pm, expand, c,
-                          d_pooled, info, d_values, !compact, dw, sliced, cols, counts, few, s);
+                          d_pooled, info, d_values, !compact, dw, sliced, cols, counts, rule, s);
   if (e != hipSuccess) return e;
   const RowArgs ra{sorted, sp.n, rec, info, list, counts, heads, w, c, dv, compact ? 1 : 0,
                    static_cast<size_t>(pooled_rows), d_pooled, sliced, d_values, dw, partial, heads_part};
-  e = vdtype == UMEM_F32 ? launch_rows(ra, static_cast<const float*>(values), cols, few, s)
-                         : launch_rows(ra, static_cast<const uint16_t*>(values), cols, few, s);
+  e = vdtype == UMEM_F32 ? launch_rows(ra, static_cast<const float*>(values), M, slices, cols, rule, s)
+                         : launch_rows(ra, static_cast<const uint16_t*>(values), M, slices, cols, rule, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(seg_join_kernel, dim3(kJoinWaves / NWAVES), dim3(THREADS), 0, s, sorted, sp.n, dv,
                      partial, heads_part, d_values, list, heads, counts, 0, 0, nullptr, compact ? info : nullptr);

@@ -160,8 +160,8 @@ GATHER_BWD_SHAPES = [
     (512, CF.BF16, 1, 100, 41, 1, 1),         # one row for all: a run of 65 segments
     (768, CF.F32, 1, 64, 1400, 2, 900),       # 24 slices of 32 columns, two cores
     (512, CF.BF16, 4, 256, 520, 1, 700),      # eight slices of 64 columns, virtual blocks
-    # ... where the distinct rows pass 8 MiB and the pieces 8,192: their weight gradients with the rows'
-    # sums, in the slices' groups of entries (eight, four, two), over several chunks and shares of a
+    # ... where the distinct rows pass 8 MiB and (some) the pieces 14,336: their weight gradients with the
+    # rows' sums, in the slices' groups of entries (eight, four, two), over several chunks and shares of a
     # row, two to eight cores
     (512, CF.BF16, 4, 256, 520, 1, 8192),
     (512, CF.BF16, 4, 256, 520, 1, 20000),
@@ -170,6 +170,18 @@ GATHER_BWD_SHAPES = [
     (2560, CF.BF16, 1, 65, 470, 5, 9000),
     (3072, CF.BF16, 4, 256, 90, 3, 8500),
     (4096, CF.BF16, 4, 256, 80, 8, 8000),
+    (768, CF.F32, 1, 64, 1400, 2, 20000),
+    (512, CF.BF16, 4, 256, 520, 2, 14000),
+    # d_pooled as it is, by columns of it: rows that repeat in few pieces, one to eight cores, widths that
+    # leave some XCDs short of a slice
+    (2048, CF.F32, 4, 84, 100, 2, 200),
+    (3584, CF.BF16, 1, 84, 100, 1, 300),
+    (2560, CF.BF16, 1, 84, 100, 5, 100),
+    (4096, CF.BF16, 4, 84, 90, 8, 60),
+    (1280, CF.F32, 1, 84, 100, 1, 40000),     # rows mostly alone: with the weight gradients
+    # the largest tiny call and the smallest beyond
+    (2560, CF.BF16, 1, 64, 64, 5, 30),
+    (768, CF.F32, 1, 65, 64, 1, 900),
 ]
 
 
