@@ -857,7 +857,7 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
 constexpr int kWaveCap = 256;            // survivors of an axis or of the grid
 constexpr int kWavePieces = 128;         // 16-byte pieces of an axis (sets of the grid) that hold them
 // Pairs (waves) per workgroup: alone where a pair's rare slow steps would hold its neighbours' LDS
-// (16,384 Tucker pairs 161 us, 166 with two, 162 - 173 with four), four where they share a table.
+// (16,384 Tucker pairs 161 us, 166 with two, 162 - 173 with four; now 141), four where they share a table.
 constexpr int wave_items(bool tucker) { return tucker ? 1 : 4; }
 constexpr int kWaveMaxK = 64, kWaveMaxM = 64;
 constexpr int kWaveMaxKeys = 18 * 256;
@@ -1870,16 +1870,15 @@ hipError_t launch_select(const umem_desc& d, int T, const float* sel, const floa
   if (tucker && n_cand > KK_MAX) return hipErrorInvalidValue;
   const size_t lds = select_lds_bytes(n_cand, tucker, pooled ? d.dv : 0);
   const int64_t pairs = static_cast<int64_t>(T) * d.heads;
-  // A wave per pair from two waves per SIMD on: fewer leave its chain of steps (about 12 us, 25 with
+  // A wave per pair from two waves per SIMD on: fewer leave its chain of steps (about 11 us, 23 with
   // the Tucker grid) longer than the workgroup kernel's, which spreads a pair over eight waves.
-  // Measured (us, wave / workgroup kernel): additive, k = m = 32, 1,024 keys, 1,024 / 2,048 / 4,096
-  // pairs 11.7 / 10.8, 17.4 / 18.1, 22.4 / 32.5; 4,480 keys 20.5 / 16.1, 22.2 / 26.3, 44.6 / 46.9;
-  // Tucker, k = m = 64, 2,048 keys 26.6 / 33.9, 31.3 / 52.6, 43.8 / 95.5; k = m = 42, 448 dims
-  // 39.8 / 36.2, 49.4 / 58.8, 94.5 / 109.2.  Beyond 2,048 keys the scores take 48 to 72 registers (four
-  // waves per SIMD up to 3,072 keys, three beyond, and the additive forms keep two or three registers in
-  // scratch) and too few loads are in flight where the scores come from HBM: 3,000
-  // keys 28.3 / 23.5 at 2,048 pairs, 43.5 / 79.1 at 8,192; 4,480 keys 68.0 / 88.7 at 8,192, but the
-  // 1,024-token decode forward (2,048 pairs) 76.0 against 71.6.
+  // Measured (us, wave / workgroup kernel): additive, k = m = 32, 1,024 keys, 512 / 1,024 / 2,048 / 4,096
+  // pairs 11.4 / 8.9, 11.8 / 11.6, 13.0 / 19.4, 17.2 / 33.6; 4,480 keys 15.7 / 10.3, 16.8 / 16.3, 23.1 / 27.0,
+  // 40.9 / 48.3; Tucker, k = m = 64, 2,048 keys 23.5 / 17.5, 26.1 / 30.0, 30.7 / 49.7, 41.9 / 91.5; k = m = 42,
+  // 448 dims 33.8 / 21.7, 36.3 / 35.8, 46.1 / 57.7, 87.7 / 106.  Beyond 2,048 keys the scores take 48 to 72
+  // registers (four waves per SIMD up to 3,072 keys, three beyond, and the additive forms keep two or three
+  // registers in scratch) and too few loads are in flight where the scores come from HBM: there the
+  // 1,024-token decode forward (2,048 pairs of 4,480 keys) took 76.0 against 71.6; 8,192 pairs 69.2 / 90.6.
   const int64_t wave_pairs = d.n_keys > 2048 ? 8192 : 2048;
   if (pooled == nullptr && pairs >= wave_pairs && d.n_keys % 4 == 0 && d.n_keys <= kWaveMaxKeys &&
       d.topk <= kWaveMaxK && d.rank <= kWaveRank && d.n_keys >= 8 * d.topk && d.topm <= kWaveMaxM &&
